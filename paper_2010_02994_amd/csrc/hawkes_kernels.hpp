@@ -605,6 +605,18 @@ __global__ void __launch_bounds__(kThreads) k_pass2(const ReqDesc* __restrict__ 
 // folded into their float64 accumulators every kRowFold = 32 steps.
 // Everything stored outside the wave is float64.
 constexpr int kColSteps = 32 / kRowsPerLane;
+constexpr float kNoPair = -INFINITY;                          // exponent of a pair that does not interact
+constexpr float kHalfLog2e = (float)(0.5 * 1.4426950408889634074);   // mA = mB
+
+// A constant of the pair loop in a vector register.  A float32 operation with
+// a scalar-register operand issues at half the rate of one on vector registers
+// or literals (measured: 52 against 100 lanes per CU and clock for a multiply
+// or an add, 56 against 80 for a fused multiply-add), and the exponents take
+// four such operations per pair.
+__device__ __forceinline__ float in_vgpr(float v) {
+  asm("" : "+v"(v));
+  return v;
+}
 constexpr int kRowFold = 32;
 static_assert(kColSteps * kRowsPerLane <= 32 && kRowFold <= 32 && kRowFold % kColSteps == 0 && 64 % kRowFold == 0,
               "float32 micro-partials hold at most 32 terms");
@@ -618,7 +630,7 @@ __device__ __forceinline__ void pass1_tile_mixed(Pass1Rows<D, true>& S, const ty
                                                  double* __restrict__ acc_w, int tile_base, const KParams& kp) {
   constexpr int R = kRowsPerLane;
   const int lane = threadIdx.x & 63;
-  const float mA = kp.mA, mB = kp.mB, mG = kp.mG, mW = kp.mW, sh = kp.S;
+  const float mW = in_vgpr(kp.mW), mG = in_vgpr(kp.mG), sh = in_vgpr(kp.S);
   const typename Traits<D, true>::Rec* __restrict__ my = cols + lane;
   // The exponents of kRateExpSteps consecutive steps are formed first and
   // their exps issued back to back, so no exp result is consumed by the very
@@ -651,8 +663,12 @@ __device__ __forceinline__ void pass1_tile_mixed(Pass1Rows<D, true>& S, const ty
           const float dt = S.t[r] - col.v[D];
           r2v[s][r] = r2;
           dtv[s][r] = dt;
-          ebv[s][r] = __builtin_fmaf(-mB, dt * dt, __builtin_fmaf(-mA, r2, sh));
-          esv[s][r] = __builtin_fmaf(-mW, dt, __builtin_fmaf(-mG, r2, sh));
+          // an inactive pair's exponents start at -inf, so both exps are 0
+          // (|dt|, so that -inf meets no +inf; active pairs have dt > 0): one
+          // select for the two terms, and none on their sums
+          const float z0 = !MASK || (tile_base + ((lane + k0 + s) & 63)) < S.first[r] ? sh : kNoPair;
+          ebv[s][r] = __builtin_fmaf(-kHalfLog2e, dt * dt, __builtin_fmaf(-kHalfLog2e, r2, z0));
+          esv[s][r] = __builtin_fmaf(-mW, MASK ? __builtin_fabsf(dt) : dt, __builtin_fmaf(-mG, r2, z0));
         }
       }
 #pragma unroll
@@ -664,17 +680,11 @@ __device__ __forceinline__ void pass1_tile_mixed(Pass1Rows<D, true>& S, const ty
         }
 #pragma unroll
       for (int s = 0; s < KS; ++s) {
-        const int k = k0 + s;
         float cK, cR, cU;
 #pragma unroll
         for (int r = 0; r < R; ++r) {
           const float r2 = r2v[s][r], dt = dtv[s][r], dt2 = dt * dt;
-          float eb = ebv[s][r], es = esv[s][r];
-          if (MASK) {
-            const bool act = (tile_base + ((lane + k) & 63)) < S.first[r];
-            eb = act ? eb : 0.f;
-            es = act ? es : 0.f;
-          }
+          const float eb = ebv[s][r], es = esv[s][r];
           S.a[r][0] += eb;
           if (RU) {
             S.a[r][1] = eb * r2 + S.a[r][1];
@@ -820,7 +830,7 @@ __device__ __forceinline__ void pass2_tile_mixed(Pass2Rows<D, true>& S, const ty
                                                  double* __restrict__ acc_w, int tile_base, const KParams& kp) {
   constexpr int R = kRowsPerLane;
   const int lane = threadIdx.x & 63;
-  const float mA = kp.mA, mB = kp.mB, mG = kp.mG, mW = kp.mW, sh = kp.S;
+  const float mW = in_vgpr(kp.mW), mG = in_vgpr(kp.mG), sh = in_vgpr(kp.S);
   const typename Traits<D, true>::Rec* __restrict__ my = cols + lane;
   // exponents of kGradExpSteps steps first, exps back to back, then the
   // steps in order (as in the rate pass)
@@ -852,8 +862,9 @@ __device__ __forceinline__ void pass2_tile_mixed(Pass2Rows<D, true>& S, const ty
             r2[s][r] = q == 0 ? dx[s][r][q] * dx[s][r][q] : dx[s][r][q] * dx[s][r][q] + r2[s][r];
           }
           dt[s][r] = S.t[r] - col.v[D];
-          eb[s][r] = __builtin_fmaf(-mB, dt[s][r] * dt[s][r], __builtin_fmaf(-mA, r2[s][r], sh));
-          es[s][r] = __builtin_fmaf(-mW, dt[s][r], __builtin_fmaf(-mG, r2[s][r], sh));
+          const float z0 = !MASK || (tile_base + ((lane + k0 + s) & 63)) < S.first[r] ? sh : kNoPair;
+          eb[s][r] = __builtin_fmaf(-kHalfLog2e, dt[s][r] * dt[s][r], __builtin_fmaf(-kHalfLog2e, r2[s][r], z0));
+          es[s][r] = __builtin_fmaf(-mW, MASK ? __builtin_fabsf(dt[s][r]) : dt[s][r], __builtin_fmaf(-mG, r2[s][r], z0));
         }
       }
 #pragma unroll
@@ -865,16 +876,10 @@ __device__ __forceinline__ void pass2_tile_mixed(Pass2Rows<D, true>& S, const ty
         }
 #pragma unroll
       for (int s = 0; s < KS; ++s) {
-        const int k = k0 + s;
         float cgr[D];
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-          float ebr = eb[s][r], esr = es[s][r];
-          if (MASK) {
-            const bool act = (tile_base + ((lane + k) & 63)) < S.first[r];
-            ebr = act ? ebr : 0.f;
-            esr = act ? esr : 0.f;
-          }
+          const float ebr = eb[s][r], esr = es[s][r];
           // background weight of the pair with both endpoints' 1/lambda; its
           // r^2 and dt^2 moments give the rate pass's R and U terms of the
           // tau_x and tau_t gradients
