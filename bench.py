@@ -29,7 +29,7 @@ METRIC = "pair-interactions/s for Hawkes loglik+grad (FP64 vs mixed); serve p50/
 STAGES = ["prep", "pack", "pass1", "reduce1", "fix1", "final1", "pass2", "fix2", "reduce2"]
 KERNEL_NAMES = {"pass1": "k_pass1", "pass2": "k_pass2"}
 PROFILED_NAMES = {("pass1", "mixed"): "hawkes::k_pass1_mixed<2, false>", ("pass2", "mixed"): "hawkes::k_pass2_mixed<2>",
-                  ("pass1", "fp64"): "hawkes::k_pass1<2, false>", ("pass2", "fp64"): "hawkes::k_pass2<2, false>"}
+                  ("pass1", "fp64"): "hawkes::k_pass1<2, false, 1>", ("pass2", "fp64"): "hawkes::k_pass2<2, false, 1>"}
 
 # Peaks of the chip (256 CUs at 2.4 GHz).  FP32 vector: 157.3 TFLOP/s.  The
 # v_exp_f32 issue rate is 32 lanes per CU per clock (measured by the peaks
@@ -140,8 +140,7 @@ def main():
     stream = torch.cuda.current_stream(dev).cuda_stream
 
     def run(prec: str, steps: int, warmup: int, stage_steps: int, per_step: dict | None = None):
-        """Time `steps` calls of hawkes_grad (the product path: the fix-up and
-        finalize chain overlaps pass 2 on a side stream), bracketed by device
+        """Time `steps` calls of hawkes_grad (the product path), bracketed by device
         synchronizations, with a pair of HIP events on the call's stream
         around every call (per_step receives their median, quartiles and
         mean); then take the per-stage breakdown from `stage_steps` calls of
@@ -296,7 +295,7 @@ def main():
            "async_note": "hawkes_grad_async calls enqueued back to back, one synchronization at the end",
            "stage_ms": {k: round(float(v), 4) for k, v in zip(STAGES, stage_ms)},
            "stage_ms_note": "stages timed in sequence on one stream (hawkes_grad_timed); ms_per_step is "
-                            "hawkes_grad, where fix1, final1 and fix2 overlap pass2 on a side stream",
+                            "hawkes_grad; pack runs in prep, fix1 and final1 in pass2, fix2 in reduce2",
            "fp64": fp64,
            "exact_culling": culling,
            "speedup_mixed_vs_fp64": (value / fp64["value"]) if fp64 else None,

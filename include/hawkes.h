@@ -91,16 +91,15 @@ int hawkes_loglik(const double* x, const double* t, int64_t n, int d, const hawk
  * kernel writes them to a library-owned pinned host buffer of 64 bytes (one
  * per concurrent call, kept until the process ends), read after the
  * synchronization.
- * Gradient calls also use a library-owned side stream (non-blocking, default
- * priority; one per concurrent caller, kept until the process ends): the
- * float64 fix-ups and the finalize kernels run there while the gradient pass
- * runs on `stream`, and `stream` waits for them before the last kernel, so to
- * the caller all of the call's work is ordered on `stream`.  Calls on one
- * stream must come from one thread at a time.  The enqueue-only calls
- * (hawkes_grad_async, hawkes_leapfrog, hawkes_mwg_step, hawkes_bmds) may be
- * captured into a HIP graph: the side stream joins the capture through its
- * events (while capturing, a call that finds no pooled side stream runs in
- * order on `stream` instead of creating one). */
+ * All of the call's work is a chain of five kernels on `stream` (the float64
+ * fix-ups and the finalize terms are blocks of the gradient pass's launch).
+ * Calls on one stream must come from one thread at a time.  The enqueue-only
+ * calls (hawkes_grad_async, hawkes_leapfrog, hawkes_mwg_step, hawkes_bmds)
+ * may be captured into a HIP graph.  hawkes_leapfrog_bmds also uses a
+ * library-owned side stream (non-blocking, default priority; one per
+ * concurrent caller, kept until the process ends), which joins a capture
+ * through its events (while capturing, a call that finds no pooled side stream
+ * runs in order on `stream` instead of creating one). */
 int hawkes_grad(const double* x, const double* t, int64_t n, int d, const hawkes_params_t* p /* host */,
                 int prec, void* ws, size_t ws_bytes, void* stream,
                 double* loglik /* host or NULL */, double* grad_x /* device */, double* grad_params /* host or NULL */);
@@ -115,10 +114,11 @@ int hawkes_grad_async(const double* x, const double* t, int64_t n, int d, const 
 
 /* hawkes_grad plus per-stage device durations: stage_ms (host, 9 floats)
  * receives the milliseconds between HIP events recorded on the call's stream
- * before and after each kernel; every stage runs in order on that stream
- * (no side stream), in launch order: prep, pack, pass1 (rates), reduce1,
- * fix-up 1 (with the flagged-row list), finalize, pass2 (gradient), fix-up 2
- * (with the finalize reduction), reduce2.  Used by the benchmark to price
+ * before and after each kernel, in launch order: prep (validation and packing),
+ * pack, pass1 (rates), reduce1, fix-up 1, finalize, pass2 (gradient, with the
+ * fix-ups and the finalize terms), fix-up 2, reduce2 (with the final sums).
+ * The stages that run inside another's kernel (pack, fix-up 1, finalize,
+ * fix-up 2) read as the time between two adjacent events.  Used by the benchmark to price
  * each kernel against its roofline; the numerical results equal hawkes_grad's. */
 int hawkes_grad_timed(const double* x, const double* t, int64_t n, int d, const hawkes_params_t* p /* host */,
                       int prec, void* ws, size_t ws_bytes, void* stream,
@@ -151,8 +151,7 @@ int hawkes_diagnostics(const void* ws /* device */, size_t ws_bytes, int64_t n, 
  * hipMalloc.  The workspace is a library-owned static device array of
  * HAWKES_NOALLOC_SCRATCH_BYTES per GPU (each GPU the library runs on holds
  * its own copy until the process ends), so the call allocates nothing and
- * creates no stream: the fix-up and finalize kernels share `stream` unless
- * a side stream is already pooled, and the scalars come back through a
+ * creates no stream; the scalars come back through a
  * pooled pinned buffer only if one already exists (else by a copy).  Limit: hawkes_workspace_bytes(n, d,
  * prec) <= HAWKES_NOALLOC_SCRATCH_BYTES (about n <= 18,000 at d = 2), else
  * HAWKES_ENOMEM and nothing runs.  Every call on one GPU shares its array,

@@ -1,8 +1,10 @@
 """Build libhawkes.so for gfx950 in-tree with hipcc (no JIT, no torch extension)."""
 from __future__ import annotations
 
+import concurrent.futures
 import os
 import subprocess
+import tempfile
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
@@ -31,9 +33,23 @@ def _run(cmd):
 
 
 def build_library() -> str:
-    srcs = [os.path.join(CSRC, f) for f in ("hawkes.hip", "serve.hip", "mwg.hip", "hmc.hip", "bmds.hip", "noalloc.hip")]
-    tmp = LIB + ".tmp"
-    _run([_hipcc(), *HIPFLAGS, "-fPIC", "-shared", "-lpthread", *srcs, "-o", tmp])
+    """Compiles the sources to objects in parallel (launch.hip once per
+    dimension, 1 to 8) and links them."""
+    units = [(f, ()) for f in ("hawkes.hip", "serve.hip", "mwg.hip", "hmc.hip", "bmds.hip", "noalloc.hip")]
+    units += [("launch.hip", (f"-DHK_D={d}",)) for d in range(1, 9)]
+    with tempfile.TemporaryDirectory(prefix="hawkes_build_") as tmpdir:
+        objs = [os.path.join(tmpdir, f"{i}.o") for i in range(len(units))]
+
+        def compile_one(i):
+            src, defs = units[i]
+            _run([_hipcc(), *HIPFLAGS, *defs, "-fPIC", "-c", os.path.join(CSRC, src), "-o", objs[i]])
+
+        # the longest compilations first
+        order = sorted(range(len(units)), key=lambda i: units[i][0] not in ("bmds.hip", "launch.hip"))
+        with concurrent.futures.ThreadPoolExecutor(max_workers=min(8, os.cpu_count() or 1)) as pool:
+            list(pool.map(compile_one, order))
+        tmp = LIB + ".tmp"
+        _run([_hipcc(), "--offload-arch=gfx950", "-shared", "-lpthread", *objs, "-o", tmp])
     os.replace(tmp, LIB)
     return LIB
 

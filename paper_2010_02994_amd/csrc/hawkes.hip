@@ -14,7 +14,6 @@
 #include "../../include/hawkes.h"
 #include "hawkes_common.hpp"
 #include "hawkes_internal.hpp"
-#include "hawkes_kernels.hpp"
 
 namespace hawkes {
 
@@ -61,14 +60,36 @@ static int tiles_per_item(int64_t n) {
   int64_t tiles = 0;
   for (int b = 0; b < nb; ++b) tiles += (std::min<int64_t>(n, (int64_t)(b + 1) * kBandRows) + kTile - 1) / kTile;
   // about kTargetItems work items (several rounds of the chip's workgroups,
-  // so the last round's idle tail is a small share; at N = 50,000 four tiles
-  // per item measured fastest against 3, 5, 6, 8 and 16); at small N, where
-  // that would leave one tile per item, up to four tiles per item (fewer row
-  // partials for the reductions to read; measured best at N = 4,000-10,000)
+  // so the last round's idle tail is a small share; at N = 50,000 four to six
+  // tiles per item measured within 0.6 %, 8 the same, 3 and 12 1.5 % and 2.7 %
+  // slower); below that, fewer tiles per item as long as the chip is not full
+  // of waves, at the price of more row partials for the reductions: one tile up
+  // to 3,900 tiles (N = 10,000 mixed: 119 us against 127, 137 and 133 with 2, 3
+  // and 4; N = 15,000: 184 against 189 with 2), two up to 7,800 (N = 20,000:
+  // 284 us against 292 with 1 and 300 with 4), then four
   const int64_t fill = (tiles + kTargetItems - 1) / kTargetItems;
-  const int64_t small = std::min<int64_t>(4, (tiles + 159) / 160);
+  const int64_t small = std::min<int64_t>(4, (tiles + 3899) / 3900);
   return (int)std::max<int64_t>(1, std::max(fill, small));
 }
+
+// Step groups per tile of the pair passes (PassLds): two for float64 calls of
+// up to 700 tiles (N <= ~6,400), whose items leave most SIMDs with one wave or
+// none.  Synchronous calls at D = 2, one against two groups: N = 1,000 75.8 and
+// 66.3 us, 2,925 78.4 and 68.9, 5,000 101.8 and 96.4, 10,000 221.9 and 219.8,
+// 30,000 1,240 and 1,264; four groups gain 1 us at N <= 2,925 and lose beyond.
+// At D = 6 the groups measured equal at N = 4,733 (122 us) and slower above
+// (their rows' state needs more registers than a 512-thread workgroup leaves),
+// and in mixed precision, whose chains are short, within 4 % either way at
+// N <= 5,000 and slower above: neither is split.
+static int split_for(int64_t n, int nb, int d, bool mixed) {
+  int64_t tiles = 0;
+  for (int b = 0; b < nb; ++b) tiles += (std::min<int64_t>(n, (int64_t)(b + 1) * kBandRows) + kTile - 1) / kTile;
+  return !mixed && d <= kMaxSplitD && tiles <= 700 ? 2 : 1;
+}
+
+// Most (flagged row, segment) partials of an evaluation: the largest
+// cnt * fix_segments(cnt) over cnt <= n.
+static int64_t fix_slots(int64_t n) { return std::max<int64_t>(n, std::min<int64_t>(16 * n, 8192)); }
 
 bool make_layout(int64_t n, int d, int prec, Layout& Lo) {
   const int base = prec & ~HAWKES_CULL;
@@ -82,6 +103,7 @@ bool make_layout(int64_t n, int d, int prec, Layout& Lo) {
   Lo.n_pad = Lo.nb * kBandRows;
   Lo.L = tiles_per_item(n);
   Lo.b_fine = fine_bands(n, Lo.nb, Lo.L);
+  Lo.split = split_for(n, Lo.nb, d, Lo.mixed);
   Lo.items = 0;
   for (int b = 0; b < Lo.nb; ++b) {
     const int64_t nt = (std::min<int64_t>(n, (int64_t)(b + 1) * kBandRows) + kTile - 1) / kTile;
@@ -96,10 +118,9 @@ bool make_layout(int64_t n, int d, int prec, Layout& Lo) {
   auto take = [&](size_t bytes) { const size_t at = o; o = align256(o + bytes); return at; };
   Lo.off_desc = take(sizeof(ReqDesc));
   Lo.off_status = take(sizeof(int) * kStSlots);
-  Lo.off_dconst = take(sizeof(double) * 16);
   Lo.off_out8 = take(sizeof(double) * 8);
+  Lo.off_bad = take(sizeof(int) * (size_t)(Lo.n_pad / kEvBlock));
   Lo.off_items = take(sizeof(IPair) * (size_t)Lo.items);
-  Lo.off_band = take(sizeof(IPair) * (size_t)Lo.nb);
   Lo.off_rec = take(real * rw * (size_t)Lo.n_pad);
   Lo.off_first = take(sizeof(int) * (size_t)Lo.n_pad);
   Lo.off_ps = take(real * (size_t)Lo.n_pad);
@@ -107,16 +128,13 @@ bool make_layout(int64_t n, int d, int prec, Layout& Lo) {
   Lo.off_prow = take(sizeof(double) * (size_t)Lo.items * std::max(6, d) * kBandRows);
   Lo.off_pcol = take(sizeof(double) * (size_t)Lo.nb * std::max(3, d) * Lo.n_pad);
   Lo.off_sums = take(sizeof(double) * 6 * (size_t)n);
-  Lo.off_sigma = take(sizeof(double) * (size_t)n);
   Lo.off_flags = take(sizeof(int) * (size_t)n);
   Lo.off_list = take(sizeof(int) * (size_t)n);
   Lo.off_listpos = take(sizeof(int) * (size_t)n);
   Lo.off_bcount = take(sizeof(int) * (size_t)Lo.nsblk);
   Lo.off_bstage = take(sizeof(int) * (size_t)Lo.nsblk * kRedEv);
-  Lo.off_logl = take(sizeof(double) * (size_t)n);
   Lo.off_bpart = take(sizeof(double) * 8 * (size_t)Lo.nblk);
-  Lo.off_gfix = take(sizeof(double) * (size_t)d * n);
-  Lo.off_fixpart = take(sizeof(double) * 8 * kFixSeg * (size_t)n);
+  Lo.off_fixpart = take(sizeof(double) * kFixStride * (size_t)fix_slots(n));
   Lo.off_mompart = take(sizeof(double) * 2 * (size_t)Lo.items);
   Lo.total = o;
   return true;
@@ -225,24 +243,20 @@ ReqDesc make_desc(const Layout& Lo, const KParams& kp, const double* x, const do
   r.grad_x = grad_x;
   r.out8 = out8;
   r.status = at<int>(ws, Lo.off_status);
-  r.dconst = at<double>(ws, Lo.off_dconst);
+  r.bad = at<int>(ws, Lo.off_bad);
   r.items = at<IPair>(ws, Lo.off_items);
-  r.band = at<IPair>(ws, Lo.off_band);
   r.rec = at<void>(ws, Lo.off_rec);
   r.first = at<int>(ws, Lo.off_first);
   r.ps = at<void>(ws, Lo.off_ps);
   r.prow = at<void>(ws, Lo.off_prow);
   r.pcol = at<void>(ws, Lo.off_pcol);
   r.sums = at<double>(ws, Lo.off_sums);
-  r.sigma = at<double>(ws, Lo.off_sigma);
   r.flags = at<int>(ws, Lo.off_flags);
   r.list = at<int>(ws, Lo.off_list);
   r.listpos = at<int>(ws, Lo.off_listpos);
   r.bcount = at<int>(ws, Lo.off_bcount);
   r.bstage = at<int>(ws, Lo.off_bstage);
-  r.logl = at<double>(ws, Lo.off_logl);
   r.bpart = at<double>(ws, Lo.off_bpart);
-  r.gfix = at<double>(ws, Lo.off_gfix);
   r.fixpart = at<double>(ws, Lo.off_fixpart);
   r.mompart = at<double>(ws, Lo.off_mompart);
   // mixed gradient calls form the background moments' gradient terms in the
@@ -258,22 +272,20 @@ struct StageTimer {
   int used = 0;
 };
 static thread_local StageTimer* g_timer = nullptr;
-// Set while a call must create nothing (hawkes_grad_noalloc): only a side
-// stream already in the pool may be used, else the call runs on one stream.
+// Set while a call must create nothing (hawkes_grad_noalloc): the scalars come
+// back through a pinned buffer only if one is already pooled.
 static thread_local bool g_no_create = false;
 void set_no_create(bool on) { g_no_create = on; }
 
-static inline void mark(hipStream_t s, int stage) {
+void mark_stage(hipStream_t s, int stage) {
   if (g_timer) {
     (void)hipEventRecord(g_timer->ev[stage], s);
     g_timer->used = stage + 1;
   }
 }
 
-// A side stream and two events.  In a gradient call the fix-up and finalize
-// kernels (fix1, final1, fix2) run on the side
-// stream while pass 2 runs on the caller's stream: pass 2 reads nothing they
-// write, and k_reduce2, which reads both, waits for the side chain.
+// A side stream and two events, for callers that run independent work beside
+// an evaluation (the joint trajectories' MDS pass).
 // Forks are held exclusively while a call enqueues (an event re-recorded by
 // another thread between record and wait would order the wrong work) and
 // returned afterwards; the stream work they ordered needs nothing more.  One
@@ -378,98 +390,24 @@ static PinnedPool& pinned_pool() {
   return *p;
 }
 
-// The phases over every request of a batch (all with the same D and
-// precision).  reqs: device array of descriptors; totals: grid sizes.
-// fk == nullptr: everything in order on s (used when stages are timed).
-// one != nullptr: a single request whose descriptor the first kernel writes
-// to reqs[0].
-template <int D, bool MIX>
-static bool launch_phases(const ReqDesc* reqs, int nreq, const BatchGrid& g, bool grad, hipStream_t s,
-                          const Fork* fk, const ReqDesc* one) {
-  bool ok = true;
-  mark(s, 0);
-  if (one) k_init_one<D><<<1, 1024, 0, s>>>(*one, const_cast<ReqDesc*>(reqs));
-  else k_init<D><<<nreq, 1024, 0, s>>>(reqs);
-  mark(s, 1);
-  k_pack<D, MIX><<<g.pad_blocks, kEvBlock, 0, s>>>(reqs, nreq);
-  mark(s, 2);
-  if constexpr (MIX) {
-    if (grad) k_pass1_mixed<D, false><<<g.items, kThreads, 0, s>>>(reqs, nreq);
-    else k_pass1_mixed<D, true><<<g.items, kThreads, 0, s>>>(reqs, nreq);
-  } else {
-    k_pass1<D, MIX><<<g.items, kThreads, 0, s>>>(reqs, nreq);
-  }
-  mark(s, 3);
-  k_reduce1<D, MIX><<<g.red_blocks, kRedThreads, 0, s>>>(reqs, nreq);
-  mark(s, 4);
-  const bool fork = grad && fk != nullptr;
-  hipStream_t a = s;   // stream of the fix-up and finalize chain
-  if (fork) {
-    ok = ok && hipEventRecord(fk->ready, s) == hipSuccess;
-    ok = ok && hipStreamWaitEvent(fk->side, fk->ready, 0) == hipSuccess;
-    a = fk->side;
-  }
-  k_fix1<D><<<dim3(kFixGrid, nreq), 256, 0, a>>>(reqs);
-  mark(a, 5);
-  k_final1<D, MIX><<<g.ev_blocks, kEvBlock, 0, a>>>(reqs, nreq);
-  mark(a, 6);
-  if (!grad) {
-    mark(a, 7);
-    k_fix2<D><<<nreq, kEvBlock, 0, a>>>(reqs, nreq, 0);   // the finalize reduction alone
-    mark(a, 8);
-    return ok;
-  }
-  // finalize reduction + both gradient fix-up sweeps
-  const int fix2_blocks = nreq + g.ev_blocks + kFixGrid * nreq;
-  if (fork) {
-    k_fix2<D><<<fix2_blocks, kEvBlock, 0, a>>>(reqs, nreq, g.ev_blocks);
-    ok = ok && hipEventRecord(fk->done, a) == hipSuccess;
-  }
-  if constexpr (MIX) k_pass2_mixed<D><<<g.items, kThreads, 0, s>>>(reqs, nreq);
-  else k_pass2<D, MIX><<<g.items, kThreads, 0, s>>>(reqs, nreq);
-  mark(s, 7);
-  if (fork) ok = ok && hipStreamWaitEvent(s, fk->done, 0) == hipSuccess;
-  else k_fix2<D><<<fix2_blocks, kEvBlock, 0, s>>>(reqs, nreq, g.ev_blocks);
-  mark(s, 8);
-  k_reduce2<D, MIX><<<g.red_blocks, kRedThreads, 0, s>>>(reqs, nreq);
-  mark(s, 9);
-  return ok;
-}
-
-template <bool MIX>
-static bool dispatch_d(int d, const ReqDesc* reqs, int nreq, const BatchGrid& g, bool grad, hipStream_t s,
-                       const Fork* fk, const ReqDesc* one) {
-  switch (d) {
-    case 1: return launch_phases<1, MIX>(reqs, nreq, g, grad, s, fk, one);
-    case 2: return launch_phases<2, MIX>(reqs, nreq, g, grad, s, fk, one);
-    case 3: return launch_phases<3, MIX>(reqs, nreq, g, grad, s, fk, one);
-    case 4: return launch_phases<4, MIX>(reqs, nreq, g, grad, s, fk, one);
-    case 5: return launch_phases<5, MIX>(reqs, nreq, g, grad, s, fk, one);
-    case 6: return launch_phases<6, MIX>(reqs, nreq, g, grad, s, fk, one);
-    case 7: return launch_phases<7, MIX>(reqs, nreq, g, grad, s, fk, one);
-    case 8: return launch_phases<8, MIX>(reqs, nreq, g, grad, s, fk, one);
-  }
-  return false;
-}
-
 // Enqueue a batch whose descriptors already sit in device memory (block
 // offsets filled in), or, with one != nullptr, a single request whose
-// descriptor the first kernel copies to dev_reqs[0].  Gradient batches fork
-// onto a side stream unless the stages are being timed.  Returns
-// HAWKES_EDEVICE if a launch failed.
-int launch_batch(int d, int mixed, const ReqDesc* dev_reqs, int nreq, const BatchGrid& g, bool grad,
+// descriptor the first kernel copies to dev_reqs[0].  Returns HAWKES_EDEVICE if
+// a launch failed.
+int launch_batch(int d, int mixed, int split, const ReqDesc* dev_reqs, int nreq, const BatchGrid& g, bool grad,
                  hipStream_t s, const ReqDesc* one) {
   (void)hipGetLastError();
-  int dev = -1;
-  Fork* fk = nullptr;
-  if (grad && g_timer == nullptr && hipGetDevice(&dev) == hipSuccess) {
-    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    const bool capturing = hipStreamIsCapturing(s, &cs) == hipSuccess && cs != hipStreamCaptureStatusNone;
-    fk = fork_pool().take(dev, !capturing && !g_no_create);
+  bool ok = false;
+  switch (d) {
+    case 1: ok = launch_d<1>(mixed, split, dev_reqs, nreq, g, grad, s, one); break;
+    case 2: ok = launch_d<2>(mixed, split, dev_reqs, nreq, g, grad, s, one); break;
+    case 3: ok = launch_d<3>(mixed, split, dev_reqs, nreq, g, grad, s, one); break;
+    case 4: ok = launch_d<4>(mixed, split, dev_reqs, nreq, g, grad, s, one); break;
+    case 5: ok = launch_d<5>(mixed, split, dev_reqs, nreq, g, grad, s, one); break;
+    case 6: ok = launch_d<6>(mixed, split, dev_reqs, nreq, g, grad, s, one); break;
+    case 7: ok = launch_d<7>(mixed, split, dev_reqs, nreq, g, grad, s, one); break;
+    case 8: ok = launch_d<8>(mixed, split, dev_reqs, nreq, g, grad, s, one); break;
   }
-  const bool ok = mixed ? dispatch_d<true>(d, dev_reqs, nreq, g, grad, s, fk, one)
-                        : dispatch_d<false>(d, dev_reqs, nreq, g, grad, s, fk, one);
-  if (fk) fork_pool().give(dev, fk);
   return ok && hipGetLastError() == hipSuccess ? HAWKES_OK : HAWKES_EDEVICE;
 }
 
@@ -512,7 +450,7 @@ int run_async(const double* x, const double* t, int64_t n, int d, const hawkes_p
   desc.out_host = grad_x ? out_host : nullptr;   // written by k_reduce2, which only gradient calls run
   const BatchGrid g = assign_blocks(&desc, 1);
   ReqDesc* dev = at<ReqDesc>(ws, Lo.off_desc);
-  return launch_batch(d, Lo.mixed, dev, 1, g, grad_x != nullptr, s, &desc);
+  return launch_batch(d, Lo.mixed, Lo.split, dev, 1, g, grad_x != nullptr, s, &desc);
 }
 
 int run_sync(const double* x, const double* t, int64_t n, int d, const hawkes_params_t* p, int prec, void* ws,

@@ -39,11 +39,12 @@ constexpr int kRowsPerLane = HK_ROWS_PER_LANE;  // rows each lane owns in the pa
 constexpr int kBandRows = kThreads * kRowsPerLane;  // rows per band (512)
 constexpr int kTile = 64;               // columns per tile (one wave width)
 constexpr int kMaxD = 8;
-constexpr int kFixGrid = 256;            // workgroups per request in the fix-up kernels
-constexpr int kFixSeg = 16;             // partner segments per flagged row in the fix-up kernels
+constexpr int kFixGrid = 64;             // workgroups per request for the fix-ups of flagged rows
+constexpr int kFixStride = 16;          // doubles per (flagged row, partner segment)
 constexpr int kEvBlock = 256;           // events per block of the per-event kernels
 constexpr int kRedEv = 64;              // events per workgroup of the partial-sum reductions
 constexpr int kRedWaves = 16;           // waves per reduction workgroup (each sums a stride of partials)
+constexpr int kRedThreads = 64 * kRedWaves;
 // float32 pair passes: steps whose exps are issued together (rate, gradient)
 // Waves per SIMD the mixed passes are compiled for: the register budget
 // (512 / waves per lane) must hold the rows' state, which grows with D, or
@@ -51,6 +52,9 @@ constexpr int kRedWaves = 16;           // waves per reduction workgroup (each s
 // records take fewer waves.
 constexpr int rate_waves(int d, bool ru) { return ru && d >= 2 ? 4 : HK_RATE_WAVES_PER_EU; }
 constexpr int grad_waves(int d) { return d <= 2 ? HK_GRAD_WAVES_PER_EU : d <= 4 ? 5 : d <= 6 ? 4 : 3; }
+// Step groups of the float64 passes (see PassLds): dimensions above
+// kMaxSplitD have no split form.
+constexpr int kMaxSplitD = 4;
 // Column tiles of a work item of band `band`.
 __host__ __device__ inline int item_tiles(int band, int b_fine, int L) { return band < b_fine ? 1 : L; }
 
@@ -84,7 +88,7 @@ __device__ __forceinline__ void block_sum_n(T (&v)[NV], T* sh) {
 }
 
 // Status words kept in each request's workspace.
-enum StatusSlot { kStData = 0, kStZero = 1, kStFlagCount = 2, kStSlots = 16 };
+enum StatusSlot { kStData = 0, kStFlagCount = 1, kStSlots = 16 };
 
 // Constants of one evaluation (host-computed from the parameters and sizes).
 struct KParams {
@@ -134,31 +138,27 @@ struct ReqDesc {
   double* grad_x;   // null: rate pass and finalize only
   double* out8;     // [loglik, 6 parameter gradients, status]
   int* status;
-  double* dconst;
-  IPair* items;
-  IPair* band;
+  int* bad;         // per prepare block: its events fail the data checks
+  IPair* items;     // work items: (band, run of column tiles in it)
   void* rec;
   int* first;
   void* ps;
   void* prow;       // row partials: float (mixed) or double
   void* pcol;
   double* sums;
-  double* sigma;
   int* flags;
   int* list;
   int* listpos;
   int* bcount;
   int* bstage;
-  double* logl;
   double* bpart;
-  double* gfix;
   double* fixpart;
-  double* terms;    // optional, n x 4: per-event terms written by k_final1 (null: none)
+  double* terms;    // optional, n x 4: per-event terms (null: none)
   double* mompart;  // items x 2: per-item moment sums of the mixed gradient pass
   double* out_host; // optional host-pinned copy of out8, written by the gradient call's last kernel (null: none)
   int blk_items;    // first block of this request in a pair-pass launch
   int blk_ev;       // first block in a per-event launch (kEvBlock events per block)
-  int blk_pad;      // first block in the pack launch (n_pad / kEvBlock blocks)
+  int blk_pad;      // first block in the prepare launch (n_pad / kEvBlock blocks)
   int blk_red;      // first block in a reduction launch (kRedEv events per block)
 };
 

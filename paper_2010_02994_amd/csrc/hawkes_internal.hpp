@@ -14,10 +14,9 @@ namespace hawkes {
 struct Layout {
   int64_t n = 0;
   int d = 0, mixed = 0, cull = 0;
-  int nb = 0, n_pad = 0, L = 1, b_fine = 0, items = 0, nblk = 0, nsblk = 0;
-  size_t off_desc, off_status, off_dconst, off_out8, off_items, off_band, off_rec, off_first, off_ps, off_prow,
-      off_pcol, off_sums, off_sigma, off_flags, off_list, off_listpos, off_bcount, off_bstage, off_logl, off_bpart,
-      off_gfix, off_fixpart, off_mompart, total;
+  int nb = 0, n_pad = 0, L = 1, b_fine = 0, split = 1, items = 0, nblk = 0, nsblk = 0;
+  size_t off_desc, off_status, off_out8, off_bad, off_items, off_rec, off_first, off_ps, off_prow, off_pcol, off_sums, off_flags,
+      off_list, off_listpos, off_bcount, off_bstage, off_bpart, off_fixpart, off_mompart, total;
 };
 
 struct BatchGrid {
@@ -33,8 +32,9 @@ KParams make_kparams(const Layout& Lo, const hawkes_params_t* p);
 ReqDesc make_desc(const Layout& Lo, const KParams& kp, const double* x, const double* t, void* ws, double* out8,
                   double* grad_x);
 BatchGrid assign_blocks(ReqDesc* descs, int nreq);
-int launch_batch(int d, int mixed, const ReqDesc* dev_reqs, int nreq, const BatchGrid& g, bool grad, hipStream_t s,
-                 const ReqDesc* one = nullptr);
+// split: the step groups of every request's pair passes (Layout::split).
+int launch_batch(int d, int mixed, int split, const ReqDesc* dev_reqs, int nreq, const BatchGrid& g, bool grad,
+                 hipStream_t s, const ReqDesc* one = nullptr);
 // Enqueue one full evaluation (validation, rate pass, finalize and, when
 // grad_x is not null, the gradient pass) with no host synchronization.
 // out_host (gradient calls only; may be null): device-visible pinned memory
@@ -46,8 +46,8 @@ int run_async(const double* x, const double* t, int64_t n, int d, const hawkes_p
 int run_sync(const double* x, const double* t, int64_t n, int d, const hawkes_params_t* p, int prec, void* ws,
              size_t ws_bytes, void* stream, double* loglik, double* grad_x, double* grad_params,
              double* terms = nullptr);
-// While on (per host thread), gradient calls create no side stream or event:
-// they use one already pooled, or run every kernel on the caller's stream.
+// While on (per host thread), gradient calls create no pinned buffer: they use
+// one already pooled, or copy their scalars back.
 void set_no_create(bool on);
 // A side stream and two events, from a per-device pool kept for the life of
 // the process.  A fork is held exclusively while a call enqueues and given
@@ -59,6 +59,14 @@ struct Fork {
 };
 Fork* fork_take(int dev, bool allow_create);
 void fork_give(int dev, Fork* f);
+
+// The phases of a batch for dimension D (launch.hip, one object per D).
+template <int D>
+bool launch_d(int mixed, int split, const ReqDesc* reqs, int nreq, const BatchGrid& g, bool grad, hipStream_t s,
+              const ReqDesc* one);
+// While the stages are being timed (hawkes_grad_timed): records the event
+// before stage `stage` on s.
+void mark_stage(hipStream_t s, int stage);
 
 // Enqueue one Bayesian MDS evaluation; accumulate: grad_x += its location
 // gradient instead of grad_x = it.  phase 0: everything on s; phase 1: the

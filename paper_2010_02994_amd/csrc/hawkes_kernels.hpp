@@ -16,7 +16,7 @@
 // exponent is formed in base 2 with a constant shift S (terms carry a factor
 // 2^S), exp is v_exp_f32, and per-tile float32 partials fold into float64.
 // Rows whose rate sits below the shifted window are recomputed in float64 by
-// the fix-up kernels (k_fix1, k_fix2), so no event loses range.
+// the fix-ups (fix_rows, k_reduce2), so no event loses range.
 #pragma once
 #include <type_traits>
 
@@ -45,19 +45,6 @@ __device__ __forceinline__ float exp_pair(float z) { return __builtin_amdgcn_exp
 #ifndef HK_FP64_UNROLL
 #define HK_FP64_UNROLL 4   // column steps per loop trip in the float64 passes
 #endif
-
-__device__ __forceinline__ double block_max_256(double v, double* sh) {
-  const int tid = threadIdx.x;
-  sh[tid] = v;
-  __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if (tid < s) sh[tid] = fmax(sh[tid], sh[tid + s]);
-    __syncthreads();
-  }
-  double r = sh[0];
-  __syncthreads();
-  return r;
-}
 
 // Pointers taken from a request descriptor are generic; casting them to the
 // global address space lets the compiler emit global (not flat) memory
@@ -113,121 +100,107 @@ __device__ __forceinline__ int find_req(const ReqDesc* __restrict__ reqs, int nr
   return lo;
 }
 
-// ------------------------------------------------------------ prepare / pack
+// ------------------------------------------------------------ work items
 
-// One workgroup of 1024 threads per request: clears the status words, takes
-// the float32 origin of the mixed path (spatial midpoint of the first and last
-// events, temporal midpoint of the time range; any origin inside the data's
-// extent keeps the offsets within the range), t_N, and writes the work-item
-// table of the pair passes.  Items run band-major from the last (longest)
-// band to the first.  Data validation happens in k_pack.
-template <int D>
-__device__ __forceinline__ void init_block(const ReqDesc& rq) {
-  const auto x = glb(rq.x);
-  const auto t = glb(rq.t);
-  const int n = rq.kp.n, nb = rq.kp.nb, L = rq.kp.L, b_fine = rq.kp.b_fine;
-  __shared__ int s_wsum[1024 / 64];
-  const int tid = threadIdx.x;
-  if (tid == 0) {
-    glb(rq.status)[kStData] = 0;
-    glb(rq.status)[kStZero] = 0;
-    glb(rq.status)[kStFlagCount] = 0;
-    glb(rq.dconst)[0] = t[n - 1];                       // t_N for sorted input
-    for (int k = 0; k < D; ++k) glb(rq.dconst)[1 + k] = 0.5 * (x[k] + x[(int64_t)(n - 1) * D + k]);
-    glb(rq.dconst)[1 + kMaxD] = 0.5 * (t[0] + t[n - 1]);
-  }
-  // the bands in rounds of 1024 positions (position p = band nb - 1 - p):
-  // every thread counts one band's items, an exclusive scan over the round
-  // (wave shuffles, then the earlier waves' totals) gives each band its first
-  // item, and the waves then write the round's items, each band's by
-  // consecutive lanes
-  __shared__ int s_b[1024], s_base[1024], s_ch[1024];
-  const int lane = tid & 63, wv = tid >> 6;
-  int carry = 0;   // items of the earlier rounds
-  for (int r0 = 0; r0 < nb; r0 += 1024) {
-    const int pos = r0 + tid;
-    int b = 0, ch = 0;
-    if (pos < nb) {
-      b = nb - 1 - pos;
-      const int row_end = min(n, (b + 1) * kBandRows);
-      const int nt = (row_end + kTile - 1) / kTile;
-      const int Lb = item_tiles(b, b_fine, L);
-      ch = (nt + Lb - 1) / Lb;
-    }
-    int incl = ch;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-      const int v = __shfl_up(incl, off);
-      if (lane >= off) incl += v;
-    }
-    if (lane == 63) s_wsum[wv] = incl;
-    __syncthreads();
-    int base = carry + incl - ch, total = 0;
-    for (int w2 = 0; w2 < 1024 / 64; ++w2) {
-      if (w2 < wv) base += s_wsum[w2];
-      total += s_wsum[w2];
-    }
-    s_b[tid] = b;
-    s_base[tid] = base;
-    s_ch[tid] = ch;
-    if (pos < nb) {
-      glb(rq.band)[b].x = base;
-      glb(rq.band)[b].y = ch;
-    }
-    __syncthreads();
-    const int cnt = min(1024, nb - r0);
-    for (int p = wv; p < cnt; p += 1024 / 64) {
-      const int bp = s_b[p], bs = s_base[p], cp = s_ch[p];
-      for (int c = lane; c < cp; c += 64) {
-        glb(rq.items)[bs + c].x = bp;
-        glb(rq.items)[bs + c].y = c;
+// Inclusive scan over the wave's lanes (DPP row shifts and broadcasts).
+__device__ __forceinline__ int wave_scan(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);   // row_shr:1
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);   // row_shr:2
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);   // row_shr:4
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);   // row_shr:8
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);   // row_bcast:15 into rows 1 and 3
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);   // row_bcast:31 into rows 2 and 3
+  return v;
+}
+
+// Work items of band b: runs of item_tiles(b) column tiles.
+__device__ __forceinline__ int band_items(const KParams& kp, int b) {
+  const int nt = (min(kp.n, (b + 1) * kBandRows) + kTile - 1) / kTile;
+  const int Lb = item_tiles(b, kp.b_fine, kp.L);
+  return (nt + Lb - 1) / Lb;
+}
+
+// Items run band-major from the last (longest) band to the first.  The prepare
+// launch's waves write the table, 64 consecutive items each: a wave finds its
+// first item's band by scanning the bands' counts, 64 at a time, and its lanes
+// walk on from there.  (Every workgroup of the passes finding its own band
+// this way, with no table, cost them 3 % at N = 50,000: two integer divisions
+// and a scan per wave against one load.)
+__device__ __forceinline__ void write_items(const ReqDesc& rq, int wave_id, int waves) {
+  const KParams& kp = rq.kp;
+  const int lane = threadIdx.x & 63;
+  for (int it0 = wave_id * 64; it0 < kp.items; it0 += waves * 64) {
+    int band = 0, before = it0;   // band of item it0, items before it in that band
+    for (int p0 = 0; p0 < kp.nb; p0 += 64) {
+      const int b = kp.nb - 1 - (p0 + lane);
+      const int ch = b >= 0 ? band_items(kp, b) : 0;
+      const int incl = wave_scan(ch);
+      const unsigned long long past = __ballot(incl > before);
+      if (past != 0) {
+        const int l = __builtin_ctzll(past);
+        before -= __builtin_amdgcn_readlane(incl, l) - __builtin_amdgcn_readlane(ch, l);
+        band = kp.nb - 1 - (p0 + l);
+        break;
       }
+      before -= __builtin_amdgcn_readlane(incl, 63);
     }
-    carry += total;
-    __syncthreads();   // s_wsum and the round's tables are reused
+    int chunk = before + lane;
+    for (int n_b = band_items(kp, band); chunk >= n_b && band > 0; n_b = band_items(kp, band)) {
+      chunk -= n_b;
+      --band;
+    }
+    if (it0 + lane < kp.items) {
+      glb(rq.items)[it0 + lane].x = band;
+      glb(rq.items)[it0 + lane].y = chunk;
+    }
   }
 }
 
-template <int D>
-__global__ void __launch_bounds__(1024) k_init(const ReqDesc* __restrict__ reqs) {
-  init_block<D>(reqs[blockIdx.x]);
+// First item of band b: the items of the bands after it.
+__device__ __forceinline__ int band_first_item(const KParams& kp, int b) {
+  const int lane = threadIdx.x & 63;
+  int sum = 0;
+  for (int c = b + 1 + lane; c < kp.nb; c += 64) sum += band_items(kp, c);
+  return __builtin_amdgcn_readlane(wave_scan(sum), 63);
 }
 
-// Single-request form: the descriptor arrives as a kernel argument, is
-// written to device memory for the later kernels, and drives the set-up.
-template <int D>
-__global__ void __launch_bounds__(1024) k_init_one(ReqDesc d, ReqDesc* __restrict__ dst) {
-  if (threadIdx.x == 0) *dst = d;
-  init_block<D>(d);
-}
+// ------------------------------------------------------------ prepare
 
-// Packed records and tie groups.  first[i] is the first index with t == t[i]
-// (sorted input), so for j < i: t_j < t_i  <=>  j < first[i].  Padded rows get
-// first = 0, which makes every pair with them inactive.
+// Validation, packed records and tie groups; one thread per padded event.
+// The mixed path's float32 origin is the spatial midpoint of the first and
+// last events (any origin inside the data's extent keeps the offsets within
+// the range).  first[i] is the first index with t == t[i] (sorted input), so
+// for j < i: t_j < t_i  <=>  j < first[i].  Padded rows get first = 0, which
+// makes every pair with them inactive.  Each block leaves its own "bad data"
+// word (k_reduce1 joins them: the rate pass between them reads nothing out of
+// bounds whatever the data).
 template <int D, bool MIX>
-__global__ void __launch_bounds__(kEvBlock) k_pack(const ReqDesc* __restrict__ reqs, int nreq) {
+__device__ __forceinline__ void prep_event(const ReqDesc& rq, int blk) {
   using Tr = Traits<D, MIX>;
   using Real = typename Tr::Real;
-  const int r = find_req(reqs, nreq, blockIdx.x, 2);
-  const ReqDesc& rq = reqs[r];
-  const int i = (blockIdx.x - rq.blk_pad) * kEvBlock + threadIdx.x;
+  const int i = blk * kEvBlock + threadIdx.x;
   const int n = rq.kp.n;
-  if (i >= rq.kp.n_pad) return;
+  const auto x = glb(rq.x);
   const auto t = glb(rq.t);
   typename Tr::Rec rr;
 #pragma unroll
   for (int k = 0; k < Tr::RW; ++k) rr.v[k] = Real(0);
   int f = 0;
+  bool bad = false;
   if (i < n) {
     const double ti = t[i];
-    bool bad = !isfinite(ti) || ti < 0.0 || (i > 0 && !(ti >= t[i - 1]));
-#pragma unroll
-    for (int k = 0; k < D; ++k) bad = bad || !isfinite(glb(rq.x)[(int64_t)i * D + k]);
-    if (bad) atomicOr(rq.status + kStData, 1);   // rare path: generic address is fine
+    const double tp = i > 0 ? t[i - 1] : -INFINITY;
+    bad = !isfinite(ti) || ti < 0.0 || !(ti >= tp);
 #pragma unroll
     for (int k = 0; k < D; ++k) {
-      const double v = glb(rq.x)[(int64_t)i * D + k];
-      rr.v[k] = MIX ? Real((v - glb(rq.dconst)[1 + k]) * rq.kp.inv_tx) : Real(v);
+      const double v = x[(int64_t)i * D + k];
+      bad = bad || !isfinite(v);
+      if constexpr (MIX) {
+        const double c = 0.5 * (x[k] + x[(int64_t)(n - 1) * D + k]);
+        rr.v[k] = Real((v - c) * rq.kp.inv_tx);
+      } else {
+        rr.v[k] = Real(v);
+      }
     }
     // mixed: time relative to the first event of the event's column tile
     rr.v[D] = MIX ? Real((ti - t[(int64_t)(i / kTile) * kTile]) * rq.kp.inv_tt) : Real(ti);
@@ -235,7 +208,7 @@ __global__ void __launch_bounds__(kEvBlock) k_pack(const ReqDesc* __restrict__ r
     // (then a lower_bound of ti in t[0..i], a chain of dependent loads that
     // only tied events pay)
     int lo = 0, hi = i;
-    if (i == 0 || t[i - 1] < ti) lo = i;
+    if (tp < ti) lo = i;
     while (lo < hi) {
       const int mid = (lo + hi) >> 1;
       if (t[mid] < ti) lo = mid + 1; else hi = mid;
@@ -249,22 +222,42 @@ __global__ void __launch_bounds__(kEvBlock) k_pack(const ReqDesc* __restrict__ r
   }
   glb(rq.first)[i] = f;
   glb(static_cast<Real*>(rq.ps))[i] = Real(0);
+  write_items(rq, blk * (kEvBlock / 64) + (threadIdx.x >> 6), rq.kp.n_pad / 64);
+  const int any = __syncthreads_or(bad ? 1 : 0);
+  if (threadIdx.x == 0) {
+    glb(rq.bad)[blk] = any;
+    if (blk == 0) glb(rq.status)[kStFlagCount] = 0;
+  }
+}
+
+template <int D, bool MIX>
+__global__ void __launch_bounds__(kEvBlock) k_prep(const ReqDesc* __restrict__ reqs, int nreq) {
+  const ReqDesc& rq = reqs[find_req(reqs, nreq, blockIdx.x, 2)];
+  prep_event<D, MIX>(rq, blockIdx.x - rq.blk_pad);
+}
+
+// Single-request form: the descriptor arrives as a kernel argument and is
+// written to device memory for the later kernels.
+template <int D, bool MIX>
+__global__ void __launch_bounds__(kEvBlock) k_prep_one(ReqDesc d, ReqDesc* __restrict__ dst) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) *dst = d;
+  prep_event<D, MIX>(d, blockIdx.x);
 }
 
 // ------------------------------------------------------------ pair passes
 
-// Stage one tile of 64 records into LDS (16-byte chunks).
-template <typename Rec>
+// Stage one tile of 64 records into LDS (16-byte chunks), NT threads.
+template <typename Rec, int NT>
 struct TileStage {
   static constexpr int kChunks = 64 * (int)sizeof(Rec) / 16;
-  static constexpr int kPer = (kChunks + kThreads - 1) / kThreads;
+  static constexpr int kPer = (kChunks + NT - 1) / NT;
   Chunk16 r[kPer];
   template <typename P>
   __device__ __forceinline__ void load(P src, int tile) {
     const HK_GLOBAL Chunk16* s = (const HK_GLOBAL Chunk16*)(src + (int64_t)tile * kTile);
 #pragma unroll
     for (int k = 0; k < kPer; ++k) {
-      const int c = threadIdx.x + k * kThreads;
+      const int c = threadIdx.x + k * NT;
       if (c < kChunks) { r[k].a = s[c].a; r[k].b = s[c].b; r[k].c = s[c].c; r[k].d = s[c].d; }
     }
   }
@@ -272,11 +265,74 @@ struct TileStage {
     Chunk16* s = reinterpret_cast<Chunk16*>(dst);
 #pragma unroll
     for (int k = 0; k < kPer; ++k) {
-      const int c = threadIdx.x + k * kThreads;
+      const int c = threadIdx.x + k * NT;
       if (c < kChunks) s[c] = r[k];
     }
   }
 };
+
+// Step groups (float64 passes).  A work item is a row band against a run of
+// column tiles, and a tile is a chain of 64 steps per wave (a step: the lane's
+// rows against one column each).  At small N there are few items, so the chip
+// holds a wave or two per SIMD and the chain's latency, not its issue, is the
+// pass's time.  SP step groups of kWaves waves then share each tile: group h
+// takes the steps [64 h / SP, 64 (h + 1) / SP) of the same rows and columns,
+// and the groups' row sums are added in group order in LDS, so the partials
+// that leave the workgroup, and the reductions' work, stay those of one group.
+// split_for (hawkes.hip) says when.
+//
+// Every wave keeps its own column slots (a slot that two waves added to would
+// depend on their timing).  Unsplit passes double-buffer them (one barrier per
+// tile); split ones, whose workgroups do one tile or two, keep one buffer and
+// a second barrier, so that several workgroups fit a CU's LDS.
+template <int SP, int NQ, int QR = 0>
+struct PassLds {
+  static constexpr int kBufs = SP > 1 ? 1 : 2;
+  static constexpr int kColumns = kBufs * SP * kWaves * NQ * kTile;
+  static constexpr int kRowsOut = SP > 1 ? kBandRows * QR : 0;
+  // the groups' row sums reuse the column slots once these are written out
+  static constexpr int kDoubles = kColumns > kRowsOut ? kColumns : kRowsOut;
+};
+
+// The column sums of a tile, fixed-order over the waves' slots, to the band's
+// column partials; CLEAR leaves the slots at zero for the next tile.
+template <int SP, int NQ, bool CLEAR, typename P>
+__device__ __forceinline__ void store_columns(double* __restrict__ acc, P pcol, const KParams& kp, int band, int tile) {
+  for (int e = threadIdx.x; e < NQ * kTile; e += SP * kThreads) {
+    const int q = e >> 6, c = e & 63;
+    double sum = 0.0;
+#pragma unroll
+    for (int w = 0; w < SP * kWaves; ++w) {
+      sum += acc[(w * NQ + q) * kTile + c];
+      if (CLEAR) acc[(w * NQ + q) * kTile + c] = 0.0;
+    }
+    pcol[((int64_t)band * NQ + q) * kp.n_pad + tile * kTile + c] = sum;
+  }
+}
+
+// Adds the step groups' row sums in group order; group 0 ends with the totals.
+// `own` is this thread's slot base (row of the band), v its QR x R values.
+template <int SP, int QR>
+__device__ __forceinline__ void add_groups(double (&v)[kRowsPerLane][QR], double* __restrict__ lds, int group) {
+  const int own = (threadIdx.x & (kThreads - 1));
+#pragma unroll
+  for (int g = 1; g < SP; ++g) {
+    __syncthreads();   // the slots' last readers are done
+    if (group == g) {
+#pragma unroll
+      for (int r = 0; r < kRowsPerLane; ++r)
+#pragma unroll
+        for (int q = 0; q < QR; ++q) lds[(r * QR + q) * kThreads + own] = v[r][q];
+    }
+    __syncthreads();
+    if (group == 0) {
+#pragma unroll
+      for (int r = 0; r < kRowsPerLane; ++r)
+#pragma unroll
+        for (int q = 0; q < QR; ++q) v[r][q] += lds[(r * QR + q) * kThreads + own];
+    }
+  }
+}
 
 // Pass 1: rates and the moments the parameter gradient needs.
 template <int D, bool MIX>
@@ -289,19 +345,19 @@ struct Pass1Rows {
   double acc[R][6];    // float64 running sums (mixed path only)
 };
 
-template <int D, bool MIX, bool MASK>
+template <int D, bool MIX, bool MASK, int SP>
 __device__ __forceinline__ void pass1_tile(Pass1Rows<D, MIX>& S, const typename Traits<D, MIX>::Rec* __restrict__ cols,
                                            typename Traits<D, MIX>::ColT* __restrict__ acc_w, int tile_base,
-                                           const KParams& kp, const double* __restrict__ tab) {
+                                           const KParams& kp, const double* __restrict__ tab, int k_begin) {
   using Real = typename Traits<D, MIX>::Real;
   constexpr int R = kRowsPerLane;
   const int lane = threadIdx.x & 63;
   // base-2 (mixed) or natural (float64) exponent scales
   static_assert(!MIX, "the float32 passes use the lane-rotation kernels");
   const Real cb = Real(kp.alpha), ct = Real(kp.beta), cg = Real(kp.gamma), cw = Real(kp.omega);
-#pragma unroll HK_FP64_UNROLL
-  for (int k = 0; k < 64; ++k) {
-    const int c = lane ^ k;
+#pragma unroll SP > 1 ? 2 : HK_FP64_UNROLL
+  for (int kk = 0; kk < 64 / SP; ++kk) {
+    const int c = lane ^ (k_begin + kk);
     const auto col = cols[c];
     Real cK, cR, cU;
 #pragma unroll
@@ -340,27 +396,29 @@ __device__ __forceinline__ void pass1_tile(Pass1Rows<D, MIX>& S, const typename 
   }
 }
 
-template <int D, bool MIX>
-__global__ void __launch_bounds__(kThreads) k_pass1(const ReqDesc* __restrict__ reqs, int nreq) {
+template <int D, bool MIX, int SP>
+__global__ void __launch_bounds__(SP* kThreads) __attribute__((amdgpu_waves_per_eu(SP > 1 ? 4 : 1))) k_pass1(const ReqDesc* __restrict__ reqs, int nreq) {
   using Rec = typename Traits<D, false>::Rec;
   using Real = double;
-  using ColT = double;
   constexpr int R = kRowsPerLane;
   constexpr int NQ = 3;
+  constexpr int QR = 6;
+  using Lds = PassLds<SP, NQ, QR>;
   __shared__ Rec s_rec[2][kTile];
-  __shared__ ColT s_acc[2][kWaves][NQ][kTile];
+  __shared__ double s_acc[Lds::kDoubles];
   __shared__ double s_exptab[kExpTab];   // 2^(j/kExpTab) for exp_tab
   fill_exp_table(s_exptab);
-  const int rid = find_req(reqs, nreq, blockIdx.x, 0);
+  const int blk = blockIdx.x;
+  const int rid = find_req(reqs, nreq, blk, 0);
   const ReqDesc& rq = reqs[rid];
-  if (uni(glb(rq.status)[kStData]) != 0) return;
   const KParams& kp = rq.kp;
   const auto rec = glb(static_cast<const Rec*>(rq.rec));
   const auto first = glb(rq.first);
-  const auto pcol = glb(static_cast<ColT*>(rq.pcol));
-  const int item = blockIdx.x - rq.blk_items;
+  const auto pcol = glb(static_cast<double*>(rq.pcol));
+  const int item = blk - rq.blk_items;
   const int band = uni(glb(rq.items)[item].x), chunk = uni(glb(rq.items)[item].y);
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int slot = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int wave = slot % kWaves, group = slot / kWaves;   // rows, step group
   const int row_base = band * kBandRows;
   const int row_end = min(kp.n, row_base + kBandRows);
   const int nt_band = (row_end + kTile - 1) / kTile;
@@ -385,43 +443,40 @@ __global__ void __launch_bounds__(kThreads) k_pass1(const ReqDesc* __restrict__ 
 #pragma unroll
     for (int q = 0; q < 6; ++q) { S.a[r][q] = Real(0); S.acc[r][q] = 0.0; }
   }
-  {
-    ColT* z = &s_acc[0][0][0][0];
-    for (int e = threadIdx.x; e < 2 * kWaves * NQ * kTile; e += kThreads) z[e] = ColT(0);
-  }
-  TileStage<Rec> stage;
+  for (int e = threadIdx.x; e < Lds::kColumns; e += SP * kThreads) s_acc[e] = 0.0;
+  TileStage<Rec, SP * kThreads> stage;
   stage.load(rec, tile0);
   for (int tile = tile0; tile < tile1; ++tile) {
     const int buf = (tile - tile0) & 1;
     stage.store(&s_rec[buf][0]);
     __syncthreads();
     if (tile + 1 < tile1) stage.load(rec, tile + 1);
-    for (int e = threadIdx.x; tile > tile0 && e < NQ * kTile; e += kThreads) {
-      // column sums of the previous tile: fixed-order sum over the waves
-      const int q = e >> 6, c = e & 63;
-      ColT s = ColT(0);
-#pragma unroll
-      for (int w = 0; w < kWaves; ++w) { s += s_acc[buf ^ 1][w][q][c]; s_acc[buf ^ 1][w][q][c] = ColT(0); }
-      pcol[((int64_t)band * NQ + q) * kp.n_pad + (tile - 1) * kTile + c] = s;
-    }
+    double* acc = s_acc + (Lds::kBufs > 1 ? buf : 0) * (Lds::kColumns / Lds::kBufs);
+    double* acc_w = acc + slot * NQ * kTile;
+    // column sums of the previous tile
+    if (SP == 1 && tile > tile0)
+      store_columns<SP, NQ, true>(s_acc + (buf ^ 1) * (Lds::kColumns / Lds::kBufs), pcol, kp, band, tile - 1);
     const bool full = !partial_band && (tile + 1) * kTile <= first_min;
     if (tile_culled<D, MIX>(t_row0, &s_rec[buf][0], tile, kp)) {
       // nothing to add: the tile's column sums stay zero
     } else if (full) {
-      pass1_tile<D, MIX, false>(S, s_rec[buf], &s_acc[buf][wave][0][0], tile * kTile, kp, s_exptab);
+      pass1_tile<D, MIX, false, SP>(S, s_rec[buf], acc_w, tile * kTile, kp, s_exptab, group * (64 / SP));
     } else {
-      pass1_tile<D, MIX, true>(S, s_rec[buf], &s_acc[buf][wave][0][0], tile * kTile, kp, s_exptab);
+      pass1_tile<D, MIX, true, SP>(S, s_rec[buf], acc_w, tile * kTile, kp, s_exptab, group * (64 / SP));
     }
-
+    if constexpr (SP > 1) {
+      __syncthreads();
+      store_columns<SP, NQ, true>(s_acc, pcol, kp, band, tile);
+    }
   }
-  __syncthreads();
-  for (int e = threadIdx.x; e < NQ * kTile; e += kThreads) {
-    const int buf = (tile1 - 1 - tile0) & 1;
-    const int q = e >> 6, c = e & 63;
-    ColT s = ColT(0);
-#pragma unroll
-    for (int w = 0; w < kWaves; ++w) s += s_acc[buf][w][q][c];
-    pcol[((int64_t)band * NQ + q) * kp.n_pad + (tile1 - 1) * kTile + c] = s;
+  if constexpr (SP == 1) {
+    __syncthreads();
+    store_columns<SP, NQ, false>(s_acc + ((tile1 - 1 - tile0) & 1) * (Lds::kColumns / Lds::kBufs), pcol, kp, band,
+                                 tile1 - 1);
+  }
+  if constexpr (SP > 1) {
+    add_groups<SP, QR>(S.a, s_acc, group);
+    if (group != 0) return;
   }
 #pragma unroll
   for (int r = 0; r < R; ++r) {
@@ -429,6 +484,277 @@ __global__ void __launch_bounds__(kThreads) k_pass1(const ReqDesc* __restrict__ 
 #pragma unroll
     for (int q = 0; q < 6; ++q) glb(static_cast<double*>(rq.prow))[((int64_t)item * 6 + q) * kBandRows + lr] = S.a[r][q];
   }
+}
+
+// ------------------------------------------------ fix-ups and finalize blocks
+//
+// They need the rate pass's sums (k_reduce1) and nothing of the gradient pass,
+// and the gradient pass needs nothing of them, so in a gradient call they are
+// the first blocks of its launch: they fill the chip beside it, and the call's
+// chain is five launches on one stream (prepare, rate pass, reduce, gradient
+// pass, reduce) with no event between streams.  Calls without a gradient run
+// them as a launch of their own (k_side).
+
+// Sum over a 16-lane row, then over the wave, by DPP adds in a fixed order;
+// lane 63 (row_last: lane 15 of each row) ends with the sum.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_add(double v) {
+  const unsigned long long u = (unsigned long long)__double_as_longlong(v);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)u, CTRL, ROWS, 0xf, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(u >> 32), CTRL, ROWS, 0xf, false);
+  return v + __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
+}
+__device__ __forceinline__ double row_sum_last(double v) {
+  v = dpp_add<0x111, 0xf>(v);
+  v = dpp_add<0x112, 0xf>(v);
+  v = dpp_add<0x114, 0xf>(v);
+  return dpp_add<0x118, 0xf>(v);
+}
+__device__ __forceinline__ double wave_sum_last(double v) {
+  v = row_sum_last(v);
+  v = dpp_add<0x142, 0xa>(v);
+  return dpp_add<0x143, 0xc>(v);
+}
+
+// Fixed-order sums of NV (<= 64) values over the workgroup: within each wave,
+// then the waves' totals in wave order (lane q of wave 0 adds value q).  sh:
+// NV doubles per wave.  Thread 0 gets the totals; the last barrier frees sh.
+template <int NV>
+__device__ __forceinline__ void group_sum(double (&v)[NV], double* sh) {
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, nw = blockDim.x >> 6;
+#pragma unroll
+  for (int q = 0; q < NV; ++q) v[q] = wave_sum_last(v[q]);
+  if (lane == 63)
+#pragma unroll
+    for (int q = 0; q < NV; ++q) sh[wave * NV + q] = v[q];
+  __syncthreads();
+  if (wave == 0) {
+    if (lane < NV) {
+      double tot = sh[lane];
+      for (int w = 1; w < nw; ++w) tot += sh[w * NV + lane];
+      sh[lane] = tot;   // a wave's LDS operations run in order
+    }
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int q = 0; q < NV; ++q) v[q] = sh[q];
+  }
+  __syncthreads();
+}
+
+// Partner segments per flagged row: more when few rows are flagged, so that
+// their tasks still spread over the chip; never more tasks than fix_slots.
+__host__ __device__ inline int fix_segments(int cnt) {
+  return cnt <= 128 ? 16 : cnt <= 512 ? 8 : cnt <= 1024 ? 4 : cnt <= 4096 ? 2 : 1;
+}
+
+// Exact float64 recomputation of each flagged row i: the six row sums and (in
+// gradient calls) the row's own side of the location gradient,
+//   sum_j [mu_ij/tau_x^2 + (t_j < t_i) xi_ij/h^2] (x_j - x_i)   (over lambda_i),
+// over one segment of partners per task.  Each task finds its segment's
+// largest log pair term m_s and sums terms times exp(-m_s), so no term that
+// matters can underflow; the segments are merged, in order, where they are read
+// (merge_row).  fixpart[(f * segs + s) * kFixStride + q]: q < 6 the unweighted
+// sums times exp(-m_s), q = 6 m_s, q = 8 .. 8 + D the weighted vector.
+// The ordered list of flagged rows comes from k_reduce1's per-block counts
+// and staged rows: every workgroup scans the counts (each thread over a chunk
+// of consecutive blocks) and finds its tasks' rows from the scan; workgroup 0
+// of each request also writes the list, each row's list position and the
+// count, which the next kernel reads.
+template <int D>
+__device__ __forceinline__ void fix_rows(const ReqDesc& rq, int bx, int nbx, double* pool) {
+  if (uni(glb(rq.status)[kStData]) != 0) return;
+  const KParams& kp = rq.kp;
+  const int tid = threadIdx.x, nt = blockDim.x;
+  int* s_scan = reinterpret_cast<int*>(pool);            // nt
+  double* sh = pool + nt / 2;                            // (6 + D) per wave
+  int* s_wtot = reinterpret_cast<int*>(sh);              // one per wave
+  const int per = (kp.nsblk + nt - 1) / nt;
+  const int lo = min(kp.nsblk, tid * per), hi = min(kp.nsblk, lo + per);
+  int own = 0;
+  for (int b = lo; b < hi; ++b) own += glb(rq.bcount)[b];
+  int incl = wave_scan(own);
+  if ((tid & 63) == 63) s_wtot[tid >> 6] = incl;
+  __syncthreads();
+  for (int w = 0; w < (tid >> 6); ++w) incl += s_wtot[w];
+  s_scan[tid] = incl;
+  __syncthreads();
+  const int cnt = s_scan[nt - 1];
+  if (bx == 0) {
+    int pos = incl - own;
+    for (int b = lo; b < hi; ++b) {
+      const int c = glb(rq.bcount)[b];
+      for (int k = 0; k < c; ++k) {
+        const int i = glb(rq.bstage)[(int64_t)b * kRedEv + k];
+        glb(rq.list)[pos] = i;
+        glb(rq.listpos)[i] = pos;
+        ++pos;
+      }
+    }
+    if (tid == 0) glb(rq.status)[kStFlagCount] = cnt;
+  }
+  const auto x = glb(rq.x);
+  const auto t = glb(rq.t);
+  const int segs = fix_segments(cnt);
+  const int seg = (kp.n + segs - 1) / segs;
+  const double wb = kp.cbg * kp.itx2, ws = kp.cse * kp.ih2;
+  for (int64_t task = bx; task < (int64_t)cnt * segs; task += nbx) {
+    const int f = (int)(task / segs), sg = (int)(task % segs);
+    // row f of the list: the first chunk whose inclusive count exceeds f,
+    // then the block inside it
+    int c0 = 0, c1 = nt - 1;
+    while (c0 < c1) {
+      const int mid = (c0 + c1) >> 1;
+      if (s_scan[mid] > f) c1 = mid; else c0 = mid + 1;
+    }
+    int r = f - (c0 > 0 ? s_scan[c0 - 1] : 0);
+    int b = c0 * per;
+    for (int cb = glb(rq.bcount)[b]; r >= cb; cb = glb(rq.bcount)[b]) { r -= cb; ++b; }
+    const int i = glb(rq.bstage)[(int64_t)b * kRedEv + r];
+    const int j0 = sg * seg, j1 = min(kp.n, j0 + seg);
+    double xi[D];
+#pragma unroll
+    for (int q = 0; q < D; ++q) xi[q] = x[(int64_t)i * D + q];
+    const double ti = t[i];
+    double m = -INFINITY;
+    for (int j = j0 + tid; j < j1; j += nt) {
+      if (j == i) continue;
+      double r2 = 0;
+#pragma unroll
+      for (int q = 0; q < D; ++q) { const double dx = xi[q] - x[(int64_t)j * D + q]; r2 += dx * dx; }
+      const double dt = ti - t[j];
+      if (dt != 0.0) m = fmax(m, kp.log_cbg - kp.alpha * r2 - kp.beta * dt * dt);
+      if (dt > 0.0) m = fmax(m, kp.log_cse - kp.omega * dt - kp.gamma * r2);
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) m = fmax(m, __shfl_xor(m, o));
+    if ((tid & 63) == 0) sh[tid >> 6] = m;
+    __syncthreads();
+    for (int w = 0; w < (nt >> 6); ++w) m = fmax(m, sh[w]);
+    __syncthreads();
+    const double msub = m > -INFINITY ? m : 0.0;
+    double a[6 + D];
+#pragma unroll
+    for (int q = 0; q < 6 + D; ++q) a[q] = 0.0;
+    for (int j = j0 + tid; j < j1; j += nt) {
+      if (j == i) continue;
+      double dx[D], r2 = 0;
+#pragma unroll
+      for (int q = 0; q < D; ++q) { dx[q] = x[(int64_t)j * D + q] - xi[q]; r2 += dx[q] * dx[q]; }
+      const double dt = ti - t[j];
+      double c = 0.0;
+      if (dt != 0.0) {
+        const double e = exp(-kp.alpha * r2 - kp.beta * dt * dt - msub);
+        a[0] += e; a[1] += e * r2; a[2] += e * dt * dt;
+        c = wb * e;
+      }
+      if (dt > 0.0) {
+        const double e = exp(-kp.omega * dt - kp.gamma * r2 - msub);
+        a[3] += e; a[4] += e * r2; a[5] += e * dt;
+        c += ws * e;
+      }
+#pragma unroll
+      for (int q = 0; q < D; ++q) a[6 + q] += c * dx[q];
+    }
+    group_sum(a, sh);
+    if (tid == 0) {
+      const auto fp = glb(rq.fixpart) + task * kFixStride;
+#pragma unroll
+      for (int q = 0; q < 6; ++q) fp[q] = a[q];
+      fp[6] = m;
+#pragma unroll
+      for (int q = 0; q < D; ++q) fp[8 + q] = a[6 + q];
+    }
+  }
+}
+
+__device__ __forceinline__ double std_normal_cdf(double z) { return 0.5 * erfc(-z * 0.70710678118654752440); }
+__device__ __forceinline__ double std_normal_pdf(double z) { return 0.39894228040143267794 * exp(-0.5 * z * z); }
+
+// One row's terms that carry 1/lambda: log lambda and the six parameter
+// gradients' shares, from its unweighted sums times exp(-scale); v[7] counts
+// a zero rate.  Returns lambda exp(-scale).
+template <int D>
+__device__ __forceinline__ double rate_terms(const KParams& kp, const double (&s)[6], double scale, double (&v)[8]) {
+  const double lt = kp.cbg * s[0] + kp.cse * s[3];
+  const double il = 1.0 / lt;
+  v[0] += log(lt) + scale;
+  v[1] += kp.cbg_unit * s[0] * il;
+  v[2] += kp.cbg * (s[1] / (kp.tau_x * kp.tau_x * kp.tau_x) - D * s[0] / kp.tau_x) * il;
+  v[3] += kp.cbg * (s[2] / (kp.tau_t * kp.tau_t * kp.tau_t) - s[0] / kp.tau_t) * il;
+  v[4] += kp.cse_unit * s[3] * il;
+  v[5] += kp.cse * (s[3] / kp.omega - s[5]) * il;
+  v[6] += kp.cse * (s[4] / (kp.h * kp.h * kp.h) - D * s[3] / kp.h) * il;
+  v[7] += lt > 0.0 ? 0.0 : 1.0;
+  return lt;
+}
+
+// Per-event outputs: background rate per unit mu0, self-excitation rate per
+// unit theta, log lambda, and the probability that the event was triggered by
+// an earlier one (self-excitation share of the rate).
+__device__ __forceinline__ void store_terms(const ReqDesc& rq, int i, const double (&s)[6], double lt, double scale) {
+  if (rq.terms == nullptr) return;
+  const KParams& kp = rq.kp;
+  const auto tp = glb(rq.terms) + (int64_t)i * 4;
+  tp[0] = s[0] > 0.0 ? exp(log(kp.cbg_unit * s[0]) + scale) : 0.0;
+  tp[1] = s[3] > 0.0 ? exp(log(kp.cse_unit * s[3]) + scale) : 0.0;
+  tp[2] = log(lt) + scale;
+  tp[3] = kp.cse * s[3] / lt;
+}
+
+// Per event: the compensator's terms and, for rows the fix-ups do not take,
+// log lambda and the parameter gradient's; per-block fixed-order sums.
+template <int D>
+__device__ __forceinline__ void final_events(const ReqDesc& rq, int lb, double* pool) {
+  if (uni(glb(rq.status)[kStData]) != 0) return;
+  const KParams& kp = rq.kp;
+  const int i = lb * kEvBlock + threadIdx.x;
+  double v[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+  if (threadIdx.x < kEvBlock && i < kp.n) {
+    double s[6];
+#pragma unroll
+    for (int q = 0; q < 6; ++q) s[q] = glb(rq.sums)[(int64_t)i * 6 + q];
+    const double T = rq.t[kp.n - 1], ti = rq.t[i];   // t_N: the last of the sorted times
+    if (glb(rq.flags)[i] == 0) {
+      const double lt = rate_terms<D>(kp, s, kp.sigma_main, v);
+      store_terms(rq, i, s, lt, kp.sigma_main);
+    }
+    const double a = (T - ti) / kp.tau_t, b = -ti / kp.tau_t;
+    const double cdf_diff = std_normal_cdf(a) - std_normal_cdf(b);
+    const double decay = exp(-kp.omega * (T - ti));
+    const double omd = -expm1(-kp.omega * (T - ti));
+    const double dtau = -kp.mu0 / (kp.tau_t * kp.tau_t) * ((T - ti) * std_normal_pdf(a) + ti * std_normal_pdf(b));
+    v[0] -= kp.mu0 * cdf_diff + kp.theta * omd;
+    v[1] -= cdf_diff;
+    v[3] -= dtau;
+    v[4] -= omd;
+    v[5] -= kp.theta * (T - ti) * decay;
+  }
+  group_sum(v, pool);
+  if (threadIdx.x == 0)
+#pragma unroll
+    for (int q = 0; q < 8; ++q) glb(rq.bpart)[(int64_t)lb * 8 + q] = v[q];
+}
+
+// Blocks of a launch that take the fix-ups and the finalize terms.
+__host__ __device__ inline int side_blocks(int nreq, int ev_blocks) { return nreq * kFixGrid + ev_blocks; }
+
+template <int D, bool MIX>
+__device__ __forceinline__ void side_block(const ReqDesc* __restrict__ reqs, int nreq, int ev_blocks, double* pool) {
+  int b = blockIdx.x;
+  if (b < ev_blocks) {
+    const ReqDesc& rq = reqs[find_req(reqs, nreq, b, 1)];
+    final_events<D>(rq, b - rq.blk_ev, pool);
+    return;
+  }
+  b -= ev_blocks;
+  fix_rows<D>(reqs[b / kFixGrid], b % kFixGrid, kFixGrid, pool);
+}
+
+// The same blocks alone (calls without a gradient).
+template <int D, bool MIX>
+__global__ void __launch_bounds__(kEvBlock) k_side(const ReqDesc* __restrict__ reqs, int nreq, int ev_blocks) {
+  __shared__ double s_pool[kEvBlock + (kEvBlock / 64) * (8 + D)];
+  side_block<D, MIX>(reqs, nreq, ev_blocks, s_pool);
 }
 
 // Pass 2: location gradient.  For the pair (i later, j earlier)
@@ -449,18 +775,18 @@ struct Pass2Rows {
   double acc[R][D];
 };
 
-template <int D, bool MIX, bool MASK>
+template <int D, bool MIX, bool MASK, int SP>
 __device__ __forceinline__ void pass2_tile(Pass2Rows<D, MIX>& S, const typename Traits<D, MIX>::Rec* __restrict__ cols,
                                            typename Traits<D, MIX>::ColT* __restrict__ acc_w, int tile_base,
-                                           const KParams& kp, const double* __restrict__ tab) {
+                                           const KParams& kp, const double* __restrict__ tab, int k_begin) {
   using Real = typename Traits<D, MIX>::Real;
   constexpr int R = kRowsPerLane;
   const int lane = threadIdx.x & 63;
   static_assert(!MIX, "the float32 passes use the lane-rotation kernels");
   const Real cb = Real(kp.alpha), ct = Real(kp.beta), cg = Real(kp.gamma), cw = Real(kp.omega);
-#pragma unroll HK_FP64_UNROLL
-  for (int k = 0; k < 64; ++k) {
-    const int c = lane ^ k;
+#pragma unroll SP > 1 ? 2 : HK_FP64_UNROLL
+  for (int kk = 0; kk < 64 / SP; ++kk) {
+    const int c = lane ^ (k_begin + kk);
     const auto col = cols[c];
     Real cgr[D];
 #pragma unroll
@@ -495,27 +821,35 @@ __device__ __forceinline__ void pass2_tile(Pass2Rows<D, MIX>& S, const typename 
   }
 }
 
-template <int D, bool MIX>
-__global__ void __launch_bounds__(kThreads) k_pass2(const ReqDesc* __restrict__ reqs, int nreq) {
+template <int D, bool MIX, int SP>
+__global__ void __launch_bounds__(SP* kThreads) __attribute__((amdgpu_waves_per_eu(SP > 1 ? 4 : 1))) k_pass2(const ReqDesc* __restrict__ reqs, int nreq, int ev_blocks) {
   using Rec = typename Traits<D, false>::Rec;
   using Real = double;
-  using ColT = double;
   constexpr int R = kRowsPerLane;
   constexpr int NQ = D;
+  constexpr int QR = D;
+  using Lds = PassLds<SP, NQ, QR>;
   __shared__ Rec s_rec[2][kTile];
-  __shared__ ColT s_acc[2][kWaves][NQ][kTile];
+  __shared__ double s_acc[Lds::kDoubles];
   __shared__ double s_exptab[kExpTab];   // 2^(j/kExpTab) for exp_tab
+  // the fix-up and finalize blocks come first (their results are read by the
+  // next kernel only); nothing in the pair pass depends on them
+  const int blk = (int)blockIdx.x - side_blocks(nreq, ev_blocks);
+  if (blk < 0) {
+    side_block<D, false>(reqs, nreq, ev_blocks, s_acc);
+    return;
+  }
   fill_exp_table(s_exptab);
-  const int rid = find_req(reqs, nreq, blockIdx.x, 0);
+  const int rid = find_req(reqs, nreq, blk, 0);
   const ReqDesc& rq = reqs[rid];
-  if (uni(glb(rq.status)[kStData]) != 0) return;
   const KParams& kp = rq.kp;
   const auto rec = glb(static_cast<const Rec*>(rq.rec));
   const auto first = glb(rq.first);
-  const auto pcol = glb(static_cast<ColT*>(rq.pcol));
-  const int item = blockIdx.x - rq.blk_items;
+  const auto pcol = glb(static_cast<double*>(rq.pcol));
+  const int item = blk - rq.blk_items;
   const int band = uni(glb(rq.items)[item].x), chunk = uni(glb(rq.items)[item].y);
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int slot = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int wave = slot % kWaves, group = slot / kWaves;   // rows, step group
   const int row_base = band * kBandRows;
   const int row_end = min(kp.n, row_base + kBandRows);
   const int nt_band = (row_end + kTile - 1) / kTile;
@@ -540,43 +874,40 @@ __global__ void __launch_bounds__(kThreads) k_pass2(const ReqDesc* __restrict__ 
     S.ps[r] = glb(static_cast<const Real*>(rq.ps))[gi];
     S.first[r] = first[gi];
   }
-  {
-    ColT* z = &s_acc[0][0][0][0];
-    for (int e = threadIdx.x; e < 2 * kWaves * NQ * kTile; e += kThreads) z[e] = ColT(0);
-  }
-  TileStage<Rec> stage;
+  for (int e = threadIdx.x; e < Lds::kColumns; e += SP * kThreads) s_acc[e] = 0.0;
+  TileStage<Rec, SP * kThreads> stage;
   stage.load(rec, tile0);
   for (int tile = tile0; tile < tile1; ++tile) {
     const int buf = (tile - tile0) & 1;
     stage.store(&s_rec[buf][0]);
     __syncthreads();
     if (tile + 1 < tile1) stage.load(rec, tile + 1);
-    for (int e = threadIdx.x; tile > tile0 && e < NQ * kTile; e += kThreads) {
-      // column sums of the previous tile: fixed-order sum over the waves
-      const int q = e >> 6, c = e & 63;
-      ColT s = ColT(0);
-#pragma unroll
-      for (int w = 0; w < kWaves; ++w) { s += s_acc[buf ^ 1][w][q][c]; s_acc[buf ^ 1][w][q][c] = ColT(0); }
-      pcol[((int64_t)band * NQ + q) * kp.n_pad + (tile - 1) * kTile + c] = s;
-    }
+    double* acc = s_acc + (Lds::kBufs > 1 ? buf : 0) * (Lds::kColumns / Lds::kBufs);
+    double* acc_w = acc + slot * NQ * kTile;
+    // column sums of the previous tile
+    if (SP == 1 && tile > tile0)
+      store_columns<SP, NQ, true>(s_acc + (buf ^ 1) * (Lds::kColumns / Lds::kBufs), pcol, kp, band, tile - 1);
     const bool full = !partial_band && (tile + 1) * kTile <= first_min;
     if (tile_culled<D, MIX>(t_row0, &s_rec[buf][0], tile, kp)) {
       // nothing to add: the tile's column sums stay zero
     } else if (full) {
-      pass2_tile<D, MIX, false>(S, s_rec[buf], &s_acc[buf][wave][0][0], tile * kTile, kp, s_exptab);
+      pass2_tile<D, MIX, false, SP>(S, s_rec[buf], acc_w, tile * kTile, kp, s_exptab, group * (64 / SP));
     } else {
-      pass2_tile<D, MIX, true>(S, s_rec[buf], &s_acc[buf][wave][0][0], tile * kTile, kp, s_exptab);
+      pass2_tile<D, MIX, true, SP>(S, s_rec[buf], acc_w, tile * kTile, kp, s_exptab, group * (64 / SP));
     }
-
+    if constexpr (SP > 1) {
+      __syncthreads();
+      store_columns<SP, NQ, true>(s_acc, pcol, kp, band, tile);
+    }
   }
-  __syncthreads();
-  for (int e = threadIdx.x; e < NQ * kTile; e += kThreads) {
-    const int buf = (tile1 - 1 - tile0) & 1;
-    const int q = e >> 6, c = e & 63;
-    ColT s = ColT(0);
-#pragma unroll
-    for (int w = 0; w < kWaves; ++w) s += s_acc[buf][w][q][c];
-    pcol[((int64_t)band * NQ + q) * kp.n_pad + (tile1 - 1) * kTile + c] = s;
+  if constexpr (SP == 1) {
+    __syncthreads();
+    store_columns<SP, NQ, false>(s_acc + ((tile1 - 1 - tile0) & 1) * (Lds::kColumns / Lds::kBufs), pcol, kp, band,
+                                 tile1 - 1);
+  }
+  if constexpr (SP > 1) {
+    add_groups<SP, QR>(S.g, s_acc, group);
+    if (group != 0) return;
   }
 #pragma unroll
   for (int r = 0; r < R; ++r) {
@@ -732,21 +1063,21 @@ template <int D, bool RU>
 __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(rate_waves(D, RU)))) k_pass1_mixed(const ReqDesc* __restrict__ reqs, int nreq) {
   using Rec = typename Traits<D, true>::Rec;
   using Real = float;
-  using ColT = double;
   constexpr int R = kRowsPerLane;
   constexpr int NQ = RU ? 3 : 1;   // column sums
   constexpr int QR = RU ? 6 : 4;   // row sums stored per item
+  using Lds = PassLds<1, NQ>;
   __shared__ Rec s_rec[2][2 * kTile];
   __shared__ double s_trow[R * kThreads];   // the rows' event times
-  __shared__ ColT s_acc[2][kWaves][NQ][kTile];
-  const int rid = find_req(reqs, nreq, blockIdx.x, 0);
+  __shared__ double s_acc[Lds::kDoubles];
+  const int blk = blockIdx.x;
+  const int rid = find_req(reqs, nreq, blk, 0);
   const ReqDesc& rq = reqs[rid];
-  if (uni(glb(rq.status)[kStData]) != 0) return;
   const KParams& kp = rq.kp;
   const auto rec = glb(static_cast<const Rec*>(rq.rec));
   const auto first = glb(rq.first);
-  const auto pcol = glb(static_cast<ColT*>(rq.pcol));
-  const int item = blockIdx.x - rq.blk_items;
+  const auto pcol = glb(static_cast<double*>(rq.pcol));
+  const int item = blk - rq.blk_items;
   const int band = uni(glb(rq.items)[item].x), chunk = uni(glb(rq.items)[item].y);
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int row_base = band * kBandRows;
@@ -773,7 +1104,7 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(r
 #pragma unroll
     for (int q = 0; q < 6; ++q) { S.a[r][q] = Real(0); S.acc[r][q] = 0.0; }
   }
-  TileStage<Rec> stage;
+  TileStage<Rec, kThreads> stage;
   stage.load(rec, tile0);
   for (int tile = tile0; tile < tile1; ++tile) {
     const int buf = (tile - tile0) & 1;
@@ -781,45 +1112,34 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(r
     stage.store(&s_rec[buf][kTile]);
     __syncthreads();
     if (tile + 1 < tile1) stage.load(rec, tile + 1);
-    for (int e = threadIdx.x; tile > tile0 && e < NQ * kTile; e += kThreads) {
-      // column sums of the previous tile: fixed-order sum over the waves
-      const int q = e >> 6, c = e & 63;
-      ColT s = ColT(0);
-#pragma unroll
-      for (int w = 0; w < kWaves; ++w) { s += s_acc[buf ^ 1][w][q][c]; }
-      pcol[((int64_t)band * NQ + q) * kp.n_pad + (tile - 1) * kTile + c] = s;
-    }
+    double* acc_w = s_acc + (buf * kWaves + wave) * NQ * kTile;
+    // column sums of the previous tile
+    if (tile > tile0)
+      store_columns<1, NQ, false>(s_acc + (buf ^ 1) * kWaves * NQ * kTile, pcol, kp, band, tile - 1);
     const bool full = !partial_band && (tile + 1) * kTile <= first_min;
     // the wave's float64 column slots start at zero (a culled tile adds
     // exactly zero and leaves them so)
 #pragma unroll
-    for (int q = 0; q < NQ; ++q) s_acc[buf][wave][q][lane] = 0.0;
+    for (int q = 0; q < NQ; ++q) acc_w[q * kTile + lane] = 0.0;
     // row times relative to this column tile's first event
     const double t_tile = tile_origin(rq.t, tile);
 #pragma unroll
     for (int r = 0; r < R; ++r) S.t[r] = (float)((s_trow[r * kThreads + threadIdx.x] - t_tile) * kp.inv_tt);
     if (tile_culled<D, true>((float)((t_row0 - t_tile) * kp.inv_tt), &s_rec[buf][0], tile, kp)) {
     } else if (full) {
-      pass1_tile_mixed<D, false, RU>(S, s_rec[buf], &s_acc[buf][wave][0][0], tile * kTile, kp);
+      pass1_tile_mixed<D, false, RU>(S, s_rec[buf], acc_w, tile * kTile, kp);
     } else {
-      pass1_tile_mixed<D, true, RU>(S, s_rec[buf], &s_acc[buf][wave][0][0], tile * kTile, kp);
+      pass1_tile_mixed<D, true, RU>(S, s_rec[buf], acc_w, tile * kTile, kp);
     }
   }
   __syncthreads();
-  for (int e = threadIdx.x; e < NQ * kTile; e += kThreads) {
-    const int buf = (tile1 - 1 - tile0) & 1;
-    const int q = e >> 6, c = e & 63;
-    ColT s = ColT(0);
-#pragma unroll
-    for (int w = 0; w < kWaves; ++w) s += s_acc[buf][w][q][c];
-    pcol[((int64_t)band * NQ + q) * kp.n_pad + (tile1 - 1) * kTile + c] = s;
-  }
+  store_columns<1, NQ, false>(s_acc + ((tile1 - 1 - tile0) & 1) * kWaves * NQ * kTile, pcol, kp, band, tile1 - 1);
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     const int lr = wave * 64 * R + r * 64 + lane;
 #pragma unroll
     for (int q = 0; q < QR; ++q) {
-      const int src = RU ? q : (q == 0 ? 0 : q + 2);   // without RU: K, J, V, W
+      const int src = RU || q == 0 ? q : q + 2;   // without RU: K, J, V, W
       glb(static_cast<double*>(rq.prow))[((int64_t)item * QR + q) * kBandRows + lr] = S.acc[r][src];
     }
   }
@@ -914,24 +1234,30 @@ __device__ __forceinline__ void pass2_tile_mixed(Pass2Rows<D, true>& S, const ty
 }
 
 template <int D>
-__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(grad_waves(D)))) k_pass2_mixed(const ReqDesc* __restrict__ reqs, int nreq) {
+__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(grad_waves(D)))) k_pass2_mixed(const ReqDesc* __restrict__ reqs, int nreq, int ev_blocks) {
   using Rec = typename Traits<D, true>::Rec;
   using Real = float;
-  using ColT = double;
   constexpr int R = kRowsPerLane;
   constexpr int NQ = D;
+  using Lds = PassLds<1, NQ>;
   __shared__ Rec s_rec[2][2 * kTile];
   __shared__ double s_trow[R * kThreads];   // the rows' event times
-  __shared__ ColT s_acc[2][kWaves][NQ][kTile];
-  __shared__ double s_red[2 * kThreads];
-  const int rid = find_req(reqs, nreq, blockIdx.x, 0);
+  __shared__ double s_acc[Lds::kDoubles];
+  __shared__ double s_red[2 * kWaves];
+  // the fix-up and finalize blocks come first (their results are read by the
+  // next kernel only); nothing in the pair pass depends on them
+  const int blk = (int)blockIdx.x - side_blocks(nreq, ev_blocks);
+  if (blk < 0) {
+    side_block<D, true>(reqs, nreq, ev_blocks, s_acc);
+    return;
+  }
+  const int rid = find_req(reqs, nreq, blk, 0);
   const ReqDesc& rq = reqs[rid];
-  if (uni(glb(rq.status)[kStData]) != 0) return;
   const KParams& kp = rq.kp;
   const auto rec = glb(static_cast<const Rec*>(rq.rec));
   const auto first = glb(rq.first);
-  const auto pcol = glb(static_cast<ColT*>(rq.pcol));
-  const int item = blockIdx.x - rq.blk_items;
+  const auto pcol = glb(static_cast<double*>(rq.pcol));
+  const int item = blk - rq.blk_items;
   const int band = uni(glb(rq.items)[item].x), chunk = uni(glb(rq.items)[item].y);
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int row_base = band * kBandRows;
@@ -960,7 +1286,7 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(g
     S.ps[r] = glb(static_cast<const Real*>(rq.ps))[gi];
     S.first[r] = first[gi];
   }
-  TileStage<Rec> stage;
+  TileStage<Rec, kThreads> stage;
   stage.load(rec, tile0);
   for (int tile = tile0; tile < tile1; ++tile) {
     const int buf = (tile - tile0) & 1;
@@ -968,39 +1294,28 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(g
     stage.store(&s_rec[buf][kTile]);
     __syncthreads();
     if (tile + 1 < tile1) stage.load(rec, tile + 1);
-    for (int e = threadIdx.x; tile > tile0 && e < NQ * kTile; e += kThreads) {
-      // column sums of the previous tile: fixed-order sum over the waves
-      const int q = e >> 6, c = e & 63;
-      ColT s = ColT(0);
-#pragma unroll
-      for (int w = 0; w < kWaves; ++w) { s += s_acc[buf ^ 1][w][q][c]; }
-      pcol[((int64_t)band * NQ + q) * kp.n_pad + (tile - 1) * kTile + c] = s;
-    }
+    double* acc_w = s_acc + (buf * kWaves + wave) * NQ * kTile;
+    // column sums of the previous tile
+    if (tile > tile0)
+      store_columns<1, NQ, false>(s_acc + (buf ^ 1) * kWaves * NQ * kTile, pcol, kp, band, tile - 1);
     const bool full = !partial_band && (tile + 1) * kTile <= first_min;
     // the wave's float64 column slots start at zero (a culled tile adds
     // exactly zero and leaves them so)
 #pragma unroll
-    for (int q = 0; q < NQ; ++q) s_acc[buf][wave][q][lane] = 0.0;
+    for (int q = 0; q < NQ; ++q) acc_w[q * kTile + lane] = 0.0;
     // row times relative to this column tile's first event
     const double t_tile = tile_origin(rq.t, tile);
 #pragma unroll
     for (int r = 0; r < R; ++r) S.t[r] = (float)((s_trow[r * kThreads + threadIdx.x] - t_tile) * kp.inv_tt);
     if (tile_culled<D, true>((float)((t_row0 - t_tile) * kp.inv_tt), &s_rec[buf][0], tile, kp)) {
     } else if (full) {
-      pass2_tile_mixed<D, false>(S, s_rec[buf], &s_acc[buf][wave][0][0], tile * kTile, kp);
+      pass2_tile_mixed<D, false>(S, s_rec[buf], acc_w, tile * kTile, kp);
     } else {
-      pass2_tile_mixed<D, true>(S, s_rec[buf], &s_acc[buf][wave][0][0], tile * kTile, kp);
+      pass2_tile_mixed<D, true>(S, s_rec[buf], acc_w, tile * kTile, kp);
     }
   }
   __syncthreads();
-  for (int e = threadIdx.x; e < NQ * kTile; e += kThreads) {
-    const int buf = (tile1 - 1 - tile0) & 1;
-    const int q = e >> 6, c = e & 63;
-    ColT s = ColT(0);
-#pragma unroll
-    for (int w = 0; w < kWaves; ++w) s += s_acc[buf][w][q][c];
-    pcol[((int64_t)band * NQ + q) * kp.n_pad + (tile1 - 1) * kTile + c] = s;
-  }
+  store_columns<1, NQ, false>(s_acc + ((tile1 - 1 - tile0) & 1) * kWaves * NQ * kTile, pcol, kp, band, tile1 - 1);
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     const int lr = wave * 64 * R + r * 64 + lane;
@@ -1010,7 +1325,7 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(g
   }
   // the item's two moment sums, fixed-order over the workgroup
   double mom[2] = {S.momd[0], S.momd[1]};
-  block_sum_n(mom, s_red);
+  group_sum(mom, s_red);
   if (threadIdx.x == 0) {
     glb(rq.mompart)[(int64_t)item * 2 + 0] = mom[0];
     glb(rq.mompart)[(int64_t)item * 2 + 1] = mom[1];
@@ -1032,8 +1347,8 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(g
 // every load instruction reads one contiguous row of kRedEv float64 partials;
 // the waves' sums meet in LDS and wave 0 adds them in wave order (a fixed
 // order: results do not depend on timing).  Flagged rows of each workgroup are
-// staged in index order for k_fix1.
-constexpr int kRedThreads = 64 * kRedWaves;
+// staged in index order for fix_rows.
+
 static_assert(kRedEv == 64 && kBandRows % kRedEv == 0, "a reduction workgroup is one wave of events inside one band");
 
 template <int D, bool MIX>
@@ -1044,14 +1359,19 @@ __global__ void __launch_bounds__(kRedThreads) k_reduce1(const ReqDesc* __restri
   __shared__ double s_part[kRedWaves][6][kRedEv];
   const int rid = find_req(reqs, nreq, blockIdx.x, 3);
   const ReqDesc& rq = reqs[rid];
-  if (uni(glb(rq.status)[kStData]) != 0) return;
   const KParams& kp = rq.kp;
   const int lb = blockIdx.x - rq.blk_red;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  if (lb == 0) {   // the request's first workgroup joins the data checks
+    int bad = 0;
+    for (int k = threadIdx.x; k < kp.n_pad / kEvBlock; k += kRedThreads) bad |= glb(rq.bad)[k];
+    bad = __syncthreads_or(bad);
+    if (threadIdx.x == 0) glb(rq.status)[kStData] = bad != 0 ? 1 : 0;
+  }
   const int i0 = lb * kRedEv;
   const int i = i0 + lane;   // >= n only in the last band's padding (read, never written)
   const int b = i0 / kBandRows, lr = i % kBandRows;
-  const IPair bi{glb(rq.band)[b].x, glb(rq.band)[b].y};
+  const IPair bi{band_first_item(kp, b), band_items(kp, b)};
   const auto prow = glb(static_cast<const ColT*>(rq.prow));
   const auto pcol = glb(static_cast<const ColT*>(rq.pcol));
   double s[6] = {0, 0, 0, 0, 0, 0};
@@ -1103,7 +1423,6 @@ __global__ void __launch_bounds__(kRedThreads) k_reduce1(const ReqDesc* __restri
     flag = !(lam >= kp.cmax * exp2(kp.flag_floor));
 #pragma unroll
     for (int q = 0; q < 6; ++q) glb(rq.sums)[(int64_t)i * 6 + q] = s[q];
-    glb(rq.sigma)[i] = kp.sigma_main;
     glb(rq.flags)[i] = flag ? 1 : 0;
     // mixed: coordinates are in units of tau_x, so one factor tau_x moves in
     const double il = flag ? 0.0 : 1.0 / lam;
@@ -1118,380 +1437,130 @@ __global__ void __launch_bounds__(kRedThreads) k_reduce1(const ReqDesc* __restri
   if (lane == 0) glb(rq.bcount)[lb] = __popcll(m);
 }
 
-// Exact float64 recomputation of the six row sums of each flagged row.  The
-// partners are split into kFixSeg segments; each (row, segment) task finds the
-// segment's largest log pair term m_s, then sums exp(term - m_s) -- no term that
-// matters can underflow.  k_final1 merges the segments in a fixed order.
-// fixpart[(f * kFixSeg + s) * 8 + q]: q < 6 the unweighted sums times exp(-m_s), q = 6 m_s.
-// The ordered list of flagged rows comes from k_reduce1's per-block counts
-// and staged rows: every workgroup scans the counts (256 threads, each over a
-// chunk of consecutive blocks) and finds its tasks' rows from the scan;
-// workgroup 0 of each request also writes the list, each row's list position
-// and the count, which the kernels after this one read.
-template <int D>
-__global__ void __launch_bounds__(256) k_fix1(const ReqDesc* __restrict__ reqs) {
-  __shared__ double sh[6 * 256];
-  __shared__ int s_scan[256];
-  const ReqDesc& rq = reqs[blockIdx.y];
-  if (uni(glb(rq.status)[kStData]) != 0) return;
+// The merged sums of a flagged row, by the 16 lanes of one DPP row: lane g
+// holds segment g (segs <= 16; lanes without one hold nothing), all loads at
+// once.  Common scale m = max_s m_s (0 when every term is zero); the sums, in
+// a fixed order, end in the row's lane 15; every lane gets m and its own
+// segment's weight exp(m_g - m).
+struct MergedRow {
+  double s[6];   // lane 15
+  double m, w;
+};
+__device__ __forceinline__ MergedRow merge_row(const double HK_GLOBAL* fp, bool has) {
+  MergedRow r;
+  const double mg = has ? fp[6] : -INFINITY;
+  double m = mg;
+#pragma unroll
+  for (int o = 1; o < 16; o <<= 1) m = fmax(m, __shfl_xor(m, o));
+  const bool any = m > -INFINITY;
+  r.m = any ? m : 0.0;
+  r.w = mg > -INFINITY ? exp(mg - m) : 0.0;
+#pragma unroll
+  for (int q = 0; q < 6; ++q) r.s[q] = row_sum_last(has && mg > -INFINITY ? fp[q] * r.w : 0.0);
+  return r;
+}
+
+// ell, the six parameter gradients and the status of one request: the
+// finalize blocks' sums, the flagged rows' terms and (mixed gradient calls)
+// the gradient pass's two moment sums, all in a fixed order.
+// out8 = [ell, 6 gradients, status].  kRedThreads threads.
+template <int D, bool MIX>
+__device__ __forceinline__ void final_block(const ReqDesc& rq, double* pool) {
   const KParams& kp = rq.kp;
   const int tid = threadIdx.x;
-  const int per = (kp.nsblk + 255) / 256;
-  const int lo = min(kp.nsblk, tid * per), hi = min(kp.nsblk, lo + per);
-  int own = 0;
-  for (int b = lo; b < hi; ++b) own += glb(rq.bcount)[b];
-  s_scan[tid] = own;
-  __syncthreads();
-  for (int off = 1; off < 256; off <<= 1) {
-    const int v = tid >= off ? s_scan[tid - off] : 0;
-    __syncthreads();
-    s_scan[tid] += v;
-    __syncthreads();
-  }
-  const int cnt = s_scan[255];
-  if (blockIdx.x == 0) {
-    int pos = s_scan[tid] - own;
-    for (int b = lo; b < hi; ++b) {
-      const int c = glb(rq.bcount)[b];
-      for (int k = 0; k < c; ++k) {
-        const int i = glb(rq.bstage)[(int64_t)b * kRedEv + k];
-        glb(rq.list)[pos] = i;
-        glb(rq.listpos)[i] = pos;
-        ++pos;
-      }
-    }
-    if (tid == 0) glb(rq.status)[kStFlagCount] = cnt;
-  }
-  const auto x = glb(rq.x);
-  const auto t = glb(rq.t);
-  const int seg = (kp.n + kFixSeg - 1) / kFixSeg;
-  for (int task = blockIdx.x; task < cnt * kFixSeg; task += gridDim.x) {
-    const int f = task / kFixSeg, sg = task % kFixSeg;
-    // row f of the list: the first chunk whose inclusive count exceeds f,
-    // then the block inside it
-    int c0 = 0, c1 = 255;
-    while (c0 < c1) {
-      const int mid = (c0 + c1) >> 1;
-      if (s_scan[mid] > f) c1 = mid; else c0 = mid + 1;
-    }
-    int r = f - (c0 > 0 ? s_scan[c0 - 1] : 0);
-    int b = c0 * per;
-    for (int cb = glb(rq.bcount)[b]; r >= cb; cb = glb(rq.bcount)[b]) { r -= cb; ++b; }
-    const int i = glb(rq.bstage)[(int64_t)b * kRedEv + r];
-    const int j0 = sg * seg, j1 = min(kp.n, j0 + seg);
-    double xi[D];
-#pragma unroll
-    for (int q = 0; q < D; ++q) xi[q] = x[(int64_t)i * D + q];
-    const double ti = t[i];
-    double m = -INFINITY;
-    for (int j = j0 + threadIdx.x; j < j1; j += 256) {
-      if (j == i) continue;
-      double r2 = 0;
-#pragma unroll
-      for (int q = 0; q < D; ++q) { const double dx = xi[q] - x[(int64_t)j * D + q]; r2 += dx * dx; }
-      const double dt = ti - t[j];
-      if (dt != 0.0) m = fmax(m, kp.log_cbg - kp.alpha * r2 - kp.beta * dt * dt);
-      if (dt > 0.0) m = fmax(m, kp.log_cse - kp.omega * dt - kp.gamma * r2);
-    }
-    m = block_max_256(m, sh);
-    const double msub = m > -INFINITY ? m : 0.0;
-    double a[6] = {0, 0, 0, 0, 0, 0};
-    for (int j = j0 + threadIdx.x; j < j1; j += 256) {
-      if (j == i) continue;
-      double r2 = 0;
-#pragma unroll
-      for (int q = 0; q < D; ++q) { const double dx = xi[q] - x[(int64_t)j * D + q]; r2 += dx * dx; }
-      const double dt = ti - t[j];
-      if (dt != 0.0) {
-        const double e = exp(-kp.alpha * r2 - kp.beta * dt * dt - msub);
-        a[0] += e; a[1] += e * r2; a[2] += e * dt * dt;
-      }
-      if (dt > 0.0) {
-        const double e = exp(-kp.omega * dt - kp.gamma * r2 - msub);
-        a[3] += e; a[4] += e * r2; a[5] += e * dt;
-      }
-    }
-    block_sum_n(a, sh);
-    if (threadIdx.x == 0) {
-#pragma unroll
-      for (int q = 0; q < 6; ++q) glb(rq.fixpart)[((int64_t)f * kFixSeg + sg) * 8 + q] = a[q];
-      glb(rq.fixpart)[((int64_t)f * kFixSeg + sg) * 8 + 6] = m;
-    }
-  }
-}
-
-__device__ __forceinline__ double std_normal_cdf(double z) { return 0.5 * erfc(-z * 0.70710678118654752440); }
-__device__ __forceinline__ double std_normal_pdf(double z) { return 0.39894228040143267794 * exp(-0.5 * z * z); }
-
-// Per event: lambda, log lambda, compensator, log-likelihood term and the six
-// parameter-gradient terms; per-block fixed-order partials.
-template <int D, bool MIX>
-__global__ void __launch_bounds__(kEvBlock) k_final1(const ReqDesc* __restrict__ reqs, int nreq) {
-  __shared__ double sh[8 * kEvBlock];
-  const int rid = find_req(reqs, nreq, blockIdx.x, 1);
-  const ReqDesc& rq = reqs[rid];
-  if (glb(rq.status)[kStData] != 0) return;
-  const KParams& kp = rq.kp;
-  const int lb = blockIdx.x - rq.blk_ev;
-  const int i = lb * kEvBlock + threadIdx.x;
+  const bool bad = uni(glb(rq.status)[kStData]) != 0;
   double v[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  if (i < kp.n) {
-    double s[6];
-    double sg;
-    const bool fl = glb(rq.flags)[i] != 0;
-    if (fl) {
-      // merge the fix-up segments: common scale m = max_s m_s
-      const auto fp = glb(rq.fixpart) + (int64_t)glb(rq.listpos)[i] * kFixSeg * 8;
-      double m = -INFINITY;
-      for (int g = 0; g < kFixSeg; ++g) m = fmax(m, fp[g * 8 + 6]);
-      for (int q = 0; q < 6; ++q) s[q] = 0.0;
-      if (m > -INFINITY) {
-        for (int g = 0; g < kFixSeg; ++g) {
-          const double mg = fp[g * 8 + 6];
-          if (mg > -INFINITY) {
-            const double w = exp(mg - m);
-            for (int q = 0; q < 6; ++q) s[q] += fp[g * 8 + q] * w;
-          }
-        }
-        sg = m;
-      } else {
-        sg = 0.0;
-      }
-    } else {
-#pragma unroll
-      for (int q = 0; q < 6; ++q) s[q] = glb(rq.sums)[(int64_t)i * 6 + q];
-      sg = glb(rq.sigma)[i];
-    }
-    const double lt = kp.cbg * s[0] + kp.cse * s[3];   // lambda * exp(-sigma)
-    const double L = log(lt) + sg;
-    const double T = glb(rq.dconst)[0], ti = rq.t[i];
-    const double a = (T - ti) / kp.tau_t, b = -ti / kp.tau_t;
-    const double cdf_diff = std_normal_cdf(a) - std_normal_cdf(b);
-    const double decay = exp(-kp.omega * (T - ti));
-    const double omd = -expm1(-kp.omega * (T - ti));
-    const double Lam = kp.mu0 * cdf_diff + kp.theta * omd;
-    const double dtau = -kp.mu0 / (kp.tau_t * kp.tau_t) * ((T - ti) * std_normal_pdf(a) + ti * std_normal_pdf(b));
-    const double il = 1.0 / lt;
-    v[0] = L - Lam;
-    v[1] = kp.cbg_unit * s[0] * il - cdf_diff;
-    v[2] = kp.cbg * (s[1] / (kp.tau_x * kp.tau_x * kp.tau_x) - D * s[0] / kp.tau_x) * il;
-    v[3] = kp.cbg * (s[2] / (kp.tau_t * kp.tau_t * kp.tau_t) - s[0] / kp.tau_t) * il - dtau;
-    v[4] = kp.cse_unit * s[3] * il - omd;
-    v[5] = kp.cse * (s[3] / kp.omega - s[5]) * il - kp.theta * (T - ti) * decay;
-    v[6] = kp.cse * (s[4] / (kp.h * kp.h * kp.h) - D * s[3] / kp.h) * il;
-    v[7] = lt > 0.0 ? 0.0 : 1.0;
-    glb(rq.logl)[i] = L;
-    if (rq.terms != nullptr) {
-      // background rate per unit mu0, self-excitation rate per unit theta,
-      // log lambda, and the probability that the event was triggered by an
-      // earlier one (self-excitation share of the rate)
-      const auto tp = glb(rq.terms) + (int64_t)i * 4;
-      tp[0] = s[0] > 0.0 ? exp(log(kp.cbg_unit * s[0]) + sg) : 0.0;
-      tp[1] = s[3] > 0.0 ? exp(log(kp.cse_unit * s[3]) + sg) : 0.0;
-      tp[2] = L;
-      tp[3] = kp.cse * s[3] * il;
-    }
-  }
-  block_sum_n(v, sh);
-  if (threadIdx.x == 0)
-#pragma unroll
-    for (int q = 0; q < 8; ++q) glb(rq.bpart)[(int64_t)lb * 8 + q] = v[q];
-}
-
-// Sum the per-block partials in block order (one workgroup per request);
-// out8 = [ell, 6 gradients, status].  Runs as the first blocks of k_fix2.
-__device__ __forceinline__ void final2_block(const ReqDesc& rq, double* sh) {
-  double v[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  const int bad = glb(rq.status)[kStData];
-  if (bad == 0) {
-    for (int b = threadIdx.x; b < rq.kp.nblk; b += 256)
+  double mom[2] = {0, 0};
+  if (!bad) {
+    for (int b = tid; b < kp.nblk; b += kRedThreads)
 #pragma unroll
       for (int q = 0; q < 8; ++q) v[q] += glb(rq.bpart)[(int64_t)b * 8 + q];
+    if (MIX && !kp.ru1) {
+      // the background moments' terms of d ell/d tau_x and d ell/d tau_t, from
+      // the gradient pass's item sums: sum over pairs of
+      // w r'^2 = sum_n c_bg R_n / (tau_x^3 lambda_n) and w dt'^2 tau_x / tau_t =
+      // sum_n c_bg U_n / (tau_t^3 lambda_n) over the unflagged rows (flagged
+      // rows carry their exact R and U from the fix-up instead)
+      for (int it = tid; it < kp.items; it += kRedThreads) {
+        mom[0] += glb(rq.mompart)[(int64_t)it * 2 + 0];
+        mom[1] += glb(rq.mompart)[(int64_t)it * 2 + 1];
+      }
+    }
+    const int cnt = uni(glb(rq.status)[kStFlagCount]);
+    const int segs = fix_segments(cnt);
+    const int g = tid & 15;
+    for (int f0 = 0; f0 < cnt; f0 += kRedThreads / 16) {
+      const int f = f0 + (tid >> 4);
+      const bool row = f < cnt;
+      const MergedRow mr =
+          merge_row(glb(rq.fixpart) + ((int64_t)(row ? f : 0) * segs + min(g, segs - 1)) * kFixStride, row && g < segs);
+      if (row && g == 15) {
+        const double lt = rate_terms<D>(kp, mr.s, mr.m, v);
+        store_terms(rq, glb(rq.list)[f], mr.s, lt, mr.m);
+      }
+    }
   }
-  block_sum_n(v, sh);
-  if (threadIdx.x == 0) {
-    const auto out8 = glb(rq.out8);
-    if (bad != 0) {
-      for (int q = 0; q < 7; ++q) out8[q] = NAN;
-      out8[7] = -3.0;   // HAWKES_EDATA
-    } else if (v[7] > 0.0) {
-      glb(rq.status)[kStZero] = 1;
-      out8[0] = -INFINITY;
-      for (int q = 1; q < 7; ++q) out8[q] = NAN;
-      out8[7] = -4.0;
+  v[2] += mom[0];
+  v[3] += mom[1] * kp.tau_x / kp.tau_t;
+  group_sum(v, pool);
+  if (tid == 0) {
+    double o[8];
+    if (bad || v[7] > 0.0) {
+      o[0] = bad ? NAN : -INFINITY;
+      for (int q = 1; q < 7; ++q) o[q] = NAN;
+      o[7] = bad ? -3.0 : -4.0;   // HAWKES_EDATA, HAWKES_EZERORATE
     } else {
-      for (int q = 0; q < 7; ++q) out8[q] = v[q];
-      out8[7] = 0.0;
+      for (int q = 0; q < 7; ++q) o[q] = v[q];
+      o[7] = 0.0;
+    }
+    for (int q = 0; q < 8; ++q) {
+      glb(rq.out8)[q] = o[q];
+      if (rq.out_host) rq.out_host[q] = o[q];
     }
   }
 }
 
-// Location-gradient fix-up for flagged rows j: the j-side coefficient of
-// every pair (j, i), c = mu_ij/(lambda_j tau_x^2) + [t_i < t_j] xi_ji/(lambda_j h^2),
-// formed as exp(log-term - log lambda_j) in float64.
-// Sweep B (one thread per event i): sum over flagged j of c (x_j - x_i).
-template <int D>
-__device__ __forceinline__ void fix2b_block(const ReqDesc* __restrict__ reqs, int nreq, int blk) {
-  const int rid = find_req(reqs, nreq, blk, 1);
-  const ReqDesc& rq = reqs[rid];
-  const KParams& kp = rq.kp;
-  const int i = (blk - rq.blk_ev) * kEvBlock + threadIdx.x;
-  if (i >= kp.n || glb(rq.status)[kStData] != 0) return;
-  const auto x = glb(rq.x);
-  const auto t = glb(rq.t);
-  const int cnt = glb(rq.status)[kStFlagCount];
-  double g[D], xi[D];
-#pragma unroll
-  for (int q = 0; q < D; ++q) { g[q] = 0.0; xi[q] = x[(int64_t)i * D + q]; }
-  const double ti = t[i];
-  for (int f = 0; f < cnt; ++f) {
-    const int j = glb(rq.list)[f];
-    if (j == i) continue;
-    double dx[D], r2 = 0;
-#pragma unroll
-    for (int q = 0; q < D; ++q) { dx[q] = x[(int64_t)j * D + q] - xi[q]; r2 += dx[q] * dx[q]; }
-    const double dt = t[j] - ti;   // > 0 when j is the later event
-    const double Lj = glb(rq.logl)[j];
-    if (Lj == -INFINITY) continue;   // lambda_j = 0: the call reports a zero rate
-    double c = 0.0;
-    if (dt != 0.0) c += exp(kp.log_cbg - kp.alpha * r2 - kp.beta * dt * dt - Lj) * kp.itx2;
-    if (dt > 0.0) c += exp(kp.log_cse - kp.omega * dt - kp.gamma * r2 - Lj) * kp.ih2;
-#pragma unroll
-    for (int q = 0; q < D; ++q) g[q] += c * dx[q];
-  }
-#pragma unroll
-  for (int q = 0; q < D; ++q) glb(rq.gfix)[(int64_t)i * D + q] = g[q];
-}
-
-// Sweep A (tasks = flagged row x partner segment): partial sums over the
-// segment's events i of c (x_i - x_j) for flagged row j, merged by k_reduce2.
-template <int D>
-__device__ __forceinline__ void fix2a_block(const ReqDesc& rq, int bx, int nbx, double* sh) {
-  if (uni(glb(rq.status)[kStData]) != 0) return;
-  const KParams& kp = rq.kp;
-  const auto x = glb(rq.x);
-  const auto t = glb(rq.t);
-  const int cnt = glb(rq.status)[kStFlagCount];
-  const int seg = (kp.n + kFixSeg - 1) / kFixSeg;
-  for (int task = bx; task < cnt * kFixSeg; task += nbx) {
-    const int f = task / kFixSeg, sg = task % kFixSeg;
-    const int j = glb(rq.list)[f];
-    const int i0 = sg * seg, i1 = min(kp.n, i0 + seg);
-    double xj[D];
-#pragma unroll
-    for (int q = 0; q < D; ++q) xj[q] = x[(int64_t)j * D + q];
-    const double tj = t[j], Lj = glb(rq.logl)[j];
-    if (Lj == -INFINITY) continue;   // lambda_j = 0: the call reports a zero rate
-    double g[D];
-#pragma unroll
-    for (int q = 0; q < D; ++q) g[q] = 0.0;
-    for (int i = i0 + threadIdx.x; i < i1; i += 256) {
-      if (i == j) continue;
-      double dx[D], r2 = 0;
-#pragma unroll
-      for (int q = 0; q < D; ++q) { dx[q] = x[(int64_t)i * D + q] - xj[q]; r2 += dx[q] * dx[q]; }
-      const double dt = tj - t[i];
-      double c = 0.0;
-      if (dt != 0.0) c += exp(kp.log_cbg - kp.alpha * r2 - kp.beta * dt * dt - Lj) * kp.itx2;
-      if (dt > 0.0) c += exp(kp.log_cse - kp.omega * dt - kp.gamma * r2 - Lj) * kp.ih2;
-#pragma unroll
-      for (int q = 0; q < D; ++q) g[q] += c * dx[q];
-    }
-    block_sum_n(g, sh);
-    if (threadIdx.x == 0)
-#pragma unroll
-      for (int q = 0; q < D; ++q) glb(rq.fixpart)[((int64_t)f * kFixSeg + sg) * 8 + q] = g[q];
-  }
-}
-
-// The finalize reduction and both gradient fix-up sweeps in one launch
-// (none reads what another writes): blocks [0, nreq) reduce each request's
-// finalize partials, the next ev_blocks take sweep B, and kFixGrid blocks
-// per request take sweep A.
-template <int D>
-__global__ void __launch_bounds__(kEvBlock) k_fix2(const ReqDesc* __restrict__ reqs, int nreq, int ev_blocks) {
-  static_assert(kEvBlock == 256, "the finalize reduction uses 256 threads");
-  __shared__ double sh[8 * kEvBlock];
-  int b = blockIdx.x;
-  if (b < nreq) {
-    final2_block(reqs[b], sh);
-    return;
-  }
-  b -= nreq;
-  if (b < ev_blocks) {
-    fix2b_block<D>(reqs, nreq, b);
-    return;
-  }
-  b -= ev_blocks;
-  fix2a_block<D>(reqs[b / kFixGrid], b % kFixGrid, kFixGrid, sh);
+template <int D, bool MIX>
+__global__ void __launch_bounds__(kRedThreads) k_final(const ReqDesc* __restrict__ reqs) {
+  __shared__ double s_pool[kRedWaves * 8];
+  final_block<D, MIX>(reqs[blockIdx.x], s_pool);
 }
 
 // grad_x = row partials + column partials + fix-up terms, in a fixed order
-// (workgroups, waves and the LDS meeting as in k_reduce1).
+// (workgroups, waves and the LDS meeting as in k_reduce1); the first nreq
+// workgroups take final_block instead.
+//
+// Fix-up terms.  For a flagged row j and any event i the j-side coefficient
+// c = mu_ij/(lambda_j tau_x^2) + [t_i < t_j] xi_ji/(lambda_j h^2) is formed in
+// float64 as exp(log-term - log lambda_j): every event adds c (x_j - x_i) over
+// the flagged rows (the workgroup merges kFixChunk rows at a time into LDS,
+// its waves take every kRedWaves-th of them), and a flagged row adds its own
+// merged vector.
+constexpr int kFixChunk = kRedThreads / 16;   // 16 lanes merge a row
+
 template <int D, bool MIX>
 __global__ void __launch_bounds__(kRedThreads) k_reduce2(const ReqDesc* __restrict__ reqs, int nreq) {
-  using ColT = double;   // partials are float64 in both precisions
-  __shared__ double s_part[kRedWaves][D][kRedEv];
-  const int rid = find_req(reqs, nreq, blockIdx.x, 3);
-  const ReqDesc& rq = reqs[rid];
-  const KParams& kp = rq.kp;
-  // the request's first workgroup completes out8 (and its host copy)
-  const bool head = (int)blockIdx.x == rq.blk_red;
-  if (uni(glb(rq.status)[kStData]) != 0) {
-    if (head && rq.out_host && threadIdx.x < 8) rq.out_host[threadIdx.x] = glb(rq.out8)[threadIdx.x];
+  __shared__ double s_pool[kRedWaves * D * kRedEv];
+  __shared__ double s_own[kRedEv][D];   // this workgroup's flagged rows: their merged vectors
+  static_assert(kFixChunk * (D + 2) <= kRedWaves * D * kRedEv, "a chunk of flagged rows fits the pool");
+  if ((int)blockIdx.x < nreq) {
+    final_block<D, MIX>(reqs[blockIdx.x], s_pool);
     return;
   }
-  if (MIX && !kp.ru1 && head) {
-    // the background moments' terms of d ell/d tau_x and d ell/d tau_t, from
-    // the gradient pass's item sums in item order: sum over pairs of
-    // w r'^2 = sum_n c_bg R_n / (tau_x^3 lambda_n) and w dt'^2 tau_x / tau_t =
-    // sum_n c_bg U_n / (tau_t^3 lambda_n) over the unflagged rows (flagged
-    // rows carry their exact R and U from the fix-up instead)
-    __shared__ double s_mom[kRedThreads];
-    double m0 = 0.0, m1 = 0.0;
-    for (int it = threadIdx.x; it < kp.items; it += kRedThreads) {
-      m0 += glb(rq.mompart)[(int64_t)it * 2 + 0];
-      m1 += glb(rq.mompart)[(int64_t)it * 2 + 1];
-    }
-    s_mom[threadIdx.x] = m0;
-    __syncthreads();
-    for (int h = kRedThreads / 2; h > 0; h >>= 1) {
-      if ((int)threadIdx.x < h) s_mom[threadIdx.x] += s_mom[threadIdx.x + h];
-      __syncthreads();
-    }
-    m0 = s_mom[0];
-    __syncthreads();
-    s_mom[threadIdx.x] = m1;
-    __syncthreads();
-    for (int h = kRedThreads / 2; h > 0; h >>= 1) {
-      if ((int)threadIdx.x < h) s_mom[threadIdx.x] += s_mom[threadIdx.x + h];
-      __syncthreads();
-    }
-    m1 = s_mom[0];
-    if (threadIdx.x == 0 && glb(rq.out8)[7] == 0.0) {
-      glb(rq.out8)[2] += m0;
-      glb(rq.out8)[3] += m1 * kp.tau_x / kp.tau_t;
-    }
-  }
-  if (head && rq.out_host && threadIdx.x == 0)   // the thread that added the moment terms
-#pragma unroll
-    for (int q = 0; q < 8; ++q) rq.out_host[q] = glb(rq.out8)[q];
-  if (rq.grad_x == nullptr) return;
-  const auto grad_x = glb(rq.grad_x);
-  const int lb = blockIdx.x - rq.blk_red;
+  const int blk = blockIdx.x - nreq;
+  const ReqDesc& rq = reqs[find_req(reqs, nreq, blk, 3)];
+  const KParams& kp = rq.kp;
+  if (uni(glb(rq.status)[kStData]) != 0 || rq.grad_x == nullptr) return;
+  const int lb = blk - rq.blk_red;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int i0 = lb * kRedEv;
   const int i = i0 + lane;   // >= n only in the last band's padding (read, never written)
-  if (uni(glb(rq.status)[kStZero]) != 0) {
-    if (wave == 0 && i < kp.n)
-#pragma unroll
-      for (int q = 0; q < D; ++q) grad_x[(int64_t)i * D + q] = NAN;
-    return;
-  }
+  const auto grad_x = glb(rq.grad_x);
+  const int cnt = uni(glb(rq.status)[kStFlagCount]);
   const int b = i0 / kBandRows, lr = i % kBandRows;
-  const IPair bi{glb(rq.band)[b].x, glb(rq.band)[b].y};
-  const auto prow = glb(static_cast<const ColT*>(rq.prow));
-  const auto pcol = glb(static_cast<const ColT*>(rq.pcol));
+  const IPair bi{band_first_item(kp, b), band_items(kp, b)};
+  const auto prow = glb(static_cast<const double*>(rq.prow));
+  const auto pcol = glb(static_cast<const double*>(rq.pcol));
   double s[D];
 #pragma unroll
   for (int q = 0; q < D; ++q) s[q] = 0.0;
@@ -1507,26 +1576,79 @@ __global__ void __launch_bounds__(kRedThreads) k_reduce2(const ReqDesc* __restri
 #pragma unroll
     for (int q = 0; q < D; ++q) s[q] += p[(int64_t)q * kp.n_pad];
   }
+  int zero = 0;
+  const int segs = fix_segments(cnt);
+  if (cnt > 0) {
+    const auto x = glb(rq.x);
+    const auto t = glb(rq.t);
+    const int ic = min(i, kp.n - 1);
+    double xi[D];
 #pragma unroll
-  for (int q = 0; q < D; ++q) s_part[wave][q][lane] = s[q];
+    for (int q = 0; q < D; ++q) xi[q] = x[(int64_t)ic * D + q];
+    const double ti = t[ic];
+    const int g = threadIdx.x & 15, row = threadIdx.x >> 4;
+    for (int f0 = 0; f0 < cnt; f0 += kFixChunk) {
+      const int fn = min(kFixChunk, cnt - f0);
+      __syncthreads();
+      if ((wave << 2) < fn) {   // whole waves, four rows each
+        const bool in = row < fn;
+        const int f = f0 + (in ? row : 0);
+        const auto fp = glb(rq.fixpart) + ((int64_t)f * segs + min(g, segs - 1)) * kFixStride;
+        const int j = glb(rq.list)[f];
+        const MergedRow mr = merge_row(fp, in && g < segs);
+        const double lt = kp.cbg * mr.s[0] + kp.cse * mr.s[3];   // lane 15
+        if (in && g == 15) {
+          zero |= lt > 0.0 ? 0 : 1;
+          double* e = s_pool + row * (D + 2);
+          e[0] = log(lt) + mr.m;
+          e[1] = t[j];
+#pragma unroll
+          for (int q = 0; q < D; ++q) e[2 + q] = x[(int64_t)j * D + q];
+        }
+        if (__any(in && j >= i0 && j < i0 + kRedEv)) {
+          const bool have = in && g < segs && mr.w > 0.0;
+#pragma unroll
+          for (int q = 0; q < D; ++q) {
+            const double v = row_sum_last(have ? fp[8 + q] * mr.w : 0.0);
+            if (in && g == 15 && j >= i0 && j < i0 + kRedEv) s_own[j - i0][q] = v / lt;
+          }
+        }
+      }
+      __syncthreads();
+      for (int k = wave; k < fn; k += kRedWaves) {
+        const double* e = s_pool + k * (D + 2);
+        double dx[D], r2 = 0;
+#pragma unroll
+        for (int q = 0; q < D; ++q) { dx[q] = e[2 + q] - xi[q]; r2 += dx[q] * dx[q]; }
+        const double dt = e[1] - ti;   // > 0 when the flagged row is the later event
+        const double Lj = e[0];
+        double c = 0.0;   // the pair of a row with itself has dt = 0
+        if (dt != 0.0) c += exp(kp.log_cbg - kp.alpha * r2 - kp.beta * dt * dt - Lj) * kp.itx2;
+        if (dt > 0.0) c += exp(kp.log_cse - kp.omega * dt - kp.gamma * r2 - Lj) * kp.ih2;
+#pragma unroll
+        for (int q = 0; q < D; ++q) s[q] += c * dx[q];
+      }
+    }
+    zero = __syncthreads_or(zero);
+  }
+  double* s_part = s_pool;   // [wave][q][event]
+#pragma unroll
+  for (int q = 0; q < D; ++q) s_part[(wave * D + q) * kRedEv + lane] = s[q];
   __syncthreads();
   if (wave != 0 || i >= kp.n) return;
 #pragma unroll
   for (int q = 0; q < D; ++q) {
-    double v = s_part[0][q][lane];
+    double v = s_part[q * kRedEv + lane];
 #pragma unroll
-    for (int w = 1; w < kRedWaves; ++w) v += s_part[w][q][lane];
-    s[q] = v + glb(rq.gfix)[(int64_t)i * D + q];
+    for (int w = 1; w < kRedWaves; ++w) v += s_part[(w * D + q) * kRedEv + lane];
+    s[q] = v;
   }
-  if (glb(rq.flags)[i] != 0) {
-    const auto fp = glb(rq.fixpart) + (int64_t)glb(rq.listpos)[i] * kFixSeg * 8;
-    for (int g = 0; g < kFixSeg; ++g)
+  if (cnt > 0 && glb(rq.flags)[i] != 0) {
 #pragma unroll
-      for (int q = 0; q < D; ++q) s[q] += fp[g * 8 + q];
+    for (int q = 0; q < D; ++q) s[q] += s_own[lane][q];
   }
 #pragma unroll
-  for (int q = 0; q < D; ++q) grad_x[(int64_t)i * D + q] = s[q];
+  for (int q = 0; q < D; ++q) grad_x[(int64_t)i * D + q] = zero ? NAN : s[q];   // NaN: some rate is zero
 }
-
 
 }  // namespace hawkes

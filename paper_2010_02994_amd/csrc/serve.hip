@@ -99,6 +99,7 @@ struct Request {
   int prec = 0;
   double* grad_x = nullptr;
   size_t foot = 0, off = 0;
+  int split = 1;         // step groups of its pair passes (Layout::split)
   bool admitted = false, done = false;
   hawkes_result_t res{};
 };
@@ -234,14 +235,15 @@ bool admit_and_launch(hawkes_server* S) {
   for (auto& b : S->batches) {
     if (b.busy || S->pending.empty()) continue;
     std::vector<Request*> take;
-    int cls_d = -1, cls_p = -1, cls_b = -1;
+    int cls_d = -1, cls_p = -1, cls_b = -1, cls_s = -1;
     bool cls_g = false;
     for (auto it = S->pending.begin(); it != S->pending.end();) {
       Request* r = *it;
       const Dataset& ds = S->datasets[r->ds];
       if (S->active >= S->max_slots) break;
-      if (cls_d < 0) { cls_d = ds.d; cls_p = r->prec; cls_g = r->grad_x != nullptr; cls_b = size_band(ds.n); }
-      if (ds.d != cls_d || r->prec != cls_p || (r->grad_x != nullptr) != cls_g || size_band(ds.n) != cls_b) {
+      if (cls_d < 0) { cls_d = ds.d; cls_p = r->prec; cls_g = r->grad_x != nullptr; cls_b = size_band(ds.n); cls_s = r->split; }
+      if (ds.d != cls_d || r->prec != cls_p || (r->grad_x != nullptr) != cls_g || size_band(ds.n) != cls_b ||
+          r->split != cls_s) {
         ++it;
         continue;
       }
@@ -288,7 +290,7 @@ bool admit_and_launch(hawkes_server* S) {
       if (hipMemcpyAsync(b.dev_desc, b.host_desc, sizeof(ReqDesc) * b.nreq, hipMemcpyHostToDevice, b.stream) !=
           hipSuccess)
         st = HAWKES_EDEVICE;
-      if (st == HAWKES_OK) st = launch_batch(cls_d, (cls_p & ~HAWKES_CULL) == HAWKES_MIXED, b.dev_desc, b.nreq, g, grad, b.stream);
+      if (st == HAWKES_OK) st = launch_batch(cls_d, (cls_p & ~HAWKES_CULL) == HAWKES_MIXED, cls_s, b.dev_desc, b.nreq, g, grad, b.stream);
       if (st == HAWKES_OK &&
           hipMemcpyAsync(b.host_out, b.dev_out, sizeof(double) * 8 * b.nreq, hipMemcpyDeviceToHost, b.stream) !=
               hipSuccess)
@@ -445,6 +447,9 @@ int hawkes_serve_submit(hawkes_server_t* S, int32_t dataset_id, const double* x,
   r->prec = prec;
   r->grad_x = grad_x;
   r->foot = foot;
+  hawkes::Layout Lo;
+  hawkes::make_layout(ds.n, ds.d, prec, Lo);   // foot > 0: the sizes are valid
+  r->split = Lo.split;
   r->res.status = HAWKES_EPENDING;
   r->res.t_submit_ns = now_ns();
   S->pending.push_back(r);

@@ -1,0 +1,78 @@
+"""GPU parity where the call chain changes form: counts of rows that the
+float64 fix-ups take (their partner segments, the 64-row chunks in which they
+are merged, none and all), and the sizes either side of the float64 passes'
+step groups.  Oracle, metrics and tolerances of tests/gpu_util.py."""
+import numpy as np
+import pytest
+
+from paper_2010_02994_amd import workloads as W
+from tests.gpu_util import check, oracle_ref, run_gpu, say
+
+pytestmark = pytest.mark.gpu
+
+
+def isolated_case(seed, core, far, spacing):
+    """`core` events within half a bandwidth of the origin (the first and last
+    events among them, so that the float32 origin sits there) and `far` events
+    on a square grid around them, each `spacing` bandwidths from its nearest
+    neighbour: their rates are about exp(-spacing^2 / 2)."""
+    rng = np.random.default_rng(seed)
+    m = int(np.ceil(np.sqrt(far))) + 3
+    g = np.stack(np.meshgrid(*[np.arange(-m, m + 1)] * 2), axis=-1).reshape(-1, 2).astype(float)
+    g = g[np.abs(g).max(axis=1) >= 1]
+    g = g[np.argsort((g**2).sum(axis=1), kind="stable")][:far] * spacing
+    x = np.concatenate([0.1 * rng.standard_normal((core, 2)), g])
+    x = x[rng.permutation(len(x))]
+    at = np.flatnonzero(np.abs(x).max(axis=1) < spacing / 2)
+    if core >= 2:   # core events first and last
+        for end, j in ((0, at[0]), (len(x) - 1, at[-1])):
+            x[[end, j]] = x[[j, end]]
+    t = np.sort(rng.uniform(0.0, 2.0, size=len(x)))
+    return x, t, np.array([0.5, 1.0, 10.0, 0.4, 0.2, 1.0])
+
+
+@pytest.mark.parametrize("prec,spacing", [("mixed", 20.0), ("fp64", 37.0)])
+@pytest.mark.parametrize("core,far", [(200, 1), (190, 63), (130, 65), (200, 130), (70, 520), (40, 1100)])
+def test_flagged_row_counts(prec, spacing, core, far):
+    import torch
+
+    from paper_2010_02994_amd import api
+    x, t, p = isolated_case(core + far, core, far, spacing)
+    say(f"case flagged rows core={core} far={far} prec={prec}")
+    got = run_gpu(x, t, p, prec)
+    info, flags = api.diagnostics(torch.tensor(x, device="cuda:0"), torch.tensor(t, device="cuda:0"), p, prec=prec)
+    # the core's own rows stand far above the window, the isolated ones below
+    assert info["flagged_rows"] == far
+    assert np.array_equal(flags != 0, np.abs(x).max(axis=1) > spacing / 2)
+    check(prec, got, oracle_ref(x, t, p), p, label=f"far{far}")
+
+
+@pytest.mark.parametrize("prec,spacing", [("mixed", 17.0), ("fp64", 37.0)])
+def test_every_row_flagged(prec, spacing):
+    """No event within reach of another: every row takes the fix-ups."""
+    import torch
+
+    from paper_2010_02994_amd import api
+    x, t, p = isolated_case(5, 0, 96, spacing)
+    say(f"case every row flagged prec={prec}")
+    got = run_gpu(x, t, p, prec)
+    info, _ = api.diagnostics(torch.tensor(x, device="cuda:0"), torch.tensor(t, device="cuda:0"), p, prec=prec)
+    assert info["flagged_rows"] == len(t)
+    check(prec, got, oracle_ref(x, t, p), p, label="all")
+
+
+@pytest.mark.parametrize("seed,n,d,ties", [(31, 70, 1, 3), (32, 577, 4, 0), (33, 1100, 3, 40), (34, 6144, 2, 5),
+                                           (35, 6145, 2, 5), (36, 900, 5, 2)])
+def test_float64_step_groups(seed, n, d, ties):
+    """Float64 calls with two step groups per tile (up to 700 tiles, d <= 4) and
+    just outside: gradient, and the rate pass alone (loglik)."""
+    import torch
+
+    from paper_2010_02994_amd import api
+    w = W.random_case(seed, n, d, ties=ties, t_span=max(3.0, n / 40))
+    say(f"case step groups n={n} d={d} ties={ties}")
+    ref = oracle_ref(w.x, w.t, w.params)
+    got = run_gpu(w.x, w.t, w.params, "fp64")
+    check("fp64", got, ref, w.params, label=w.name)
+    ll = api.loglik(torch.tensor(w.x, device="cuda:0"), torch.tensor(w.t, device="cuda:0"), w.params, prec="fp64")
+    assert abs(ll - ref.ll) <= 1e-10 * abs(ref.ll)
