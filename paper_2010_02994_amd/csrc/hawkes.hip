@@ -87,10 +87,6 @@ static int split_for(int64_t n, int nb, int d, bool mixed) {
   return !mixed && d <= kMaxSplitD && tiles <= 700 ? 2 : 1;
 }
 
-// Most (flagged row, segment) partials of an evaluation: the largest
-// cnt * fix_segments(cnt) over cnt <= n.
-static int64_t fix_slots(int64_t n) { return std::max<int64_t>(n, std::min<int64_t>(16 * n, 8192)); }
-
 bool make_layout(int64_t n, int d, int prec, Layout& Lo) {
   const int base = prec & ~HAWKES_CULL;
   if (n < 2 || n > (int64_t(1) << 30) || d < 1 || d > kMaxD || (base != HAWKES_FP64 && base != HAWKES_MIXED))
@@ -134,7 +130,7 @@ bool make_layout(int64_t n, int d, int prec, Layout& Lo) {
   Lo.off_bcount = take(sizeof(int) * (size_t)Lo.nsblk);
   Lo.off_bstage = take(sizeof(int) * (size_t)Lo.nsblk * kRedEv);
   Lo.off_bpart = take(sizeof(double) * 8 * (size_t)Lo.nblk);
-  Lo.off_fixpart = take(sizeof(double) * kFixStride * (size_t)fix_slots(n));
+  Lo.off_fixpart = take(sizeof(double) * kFixStride * (size_t)n);
   Lo.off_mompart = take(sizeof(double) * 2 * (size_t)Lo.items);
   Lo.total = o;
   return true;
@@ -259,9 +255,9 @@ ReqDesc make_desc(const Layout& Lo, const KParams& kp, const double* x, const do
   r.bpart = at<double>(ws, Lo.off_bpart);
   r.fixpart = at<double>(ws, Lo.off_fixpart);
   r.mompart = at<double>(ws, Lo.off_mompart);
-  // mixed gradient calls form the background moments' gradient terms in the
-  // gradient pass; every other call accumulates them in the rate pass
-  r.kp.ru1 = (Lo.mixed && grad_x != nullptr) ? 0 : 1;
+  // gradient calls form the background moments' gradient terms in the gradient
+  // pass; the others accumulate them in the rate pass
+  r.kp.ru1 = grad_x != nullptr ? 0 : 1;
   return r;
 }
 

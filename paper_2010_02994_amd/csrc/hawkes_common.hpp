@@ -39,8 +39,8 @@ constexpr int kRowsPerLane = HK_ROWS_PER_LANE;  // rows each lane owns in the pa
 constexpr int kBandRows = kThreads * kRowsPerLane;  // rows per band (512)
 constexpr int kTile = 64;               // columns per tile (one wave width)
 constexpr int kMaxD = 8;
-constexpr int kFixGrid = 64;             // workgroups per request for the fix-ups of flagged rows
-constexpr int kFixStride = 16;          // doubles per (flagged row, partner segment)
+constexpr int kFixGrid = 128;            // workgroups per request for the fix-ups of flagged rows
+constexpr int kFixStride = 9 + 2 * kMaxD;   // doubles per flagged row
 constexpr int kEvBlock = 256;           // events per block of the per-event kernels
 constexpr int kRedEv = 64;              // events per workgroup of the partial-sum reductions
 constexpr int kRedWaves = 16;           // waves per reduction workgroup (each sums a stride of partials)
@@ -124,7 +124,7 @@ struct KParams {
   // in time than cull_dt (in the records' time units) adds exactly zero
   int cull;
   int ru1;                    // the rate pass accumulates the background moments R, U (else the gradient pass
-                              // forms their parameter-gradient terms; mixed gradient calls)
+                              // forms their parameter-gradient terms: gradient calls)
   float cull_dtf;             // mixed records: bandwidth units of tau_t
   double cull_dt;             // float64 records: time units
 };
@@ -162,7 +162,7 @@ struct ReqDesc {
   int blk_red;      // first block in a reduction launch (kRedEv events per block)
 };
 
-// Float64 exp of the pair passes and the Metropolis kernels, by Tang's table-driven method (P. T. P. Tang,
+// Float64 exp of the pair passes, the Metropolis and the MDS kernels, by Tang's table-driven method (P. T. P. Tang,
 // ACM Trans. Math. Softw. 15(2), 1989) with 2^8 table entries tab[j] = 2^(j/256)
 // held in LDS: z = (256 m + j) ln2/256 + r with |r| <= ln2/512, and
 // exp(z) = 2^m tab[j] (1 + p(r)), p the Taylor polynomial of expm1 of degree 4,

@@ -345,72 +345,85 @@ struct Pass1Rows {
   double acc[R][6];    // float64 running sums (mixed path only)
 };
 
-template <int D, bool MIX, bool MASK, int SP>
-__device__ __forceinline__ void pass1_tile(Pass1Rows<D, MIX>& S, const typename Traits<D, MIX>::Rec* __restrict__ cols,
-                                           typename Traits<D, MIX>::ColT* __restrict__ acc_w, int tile_base,
-                                           const KParams& kp, const double* __restrict__ tab, int k_begin) {
-  using Real = typename Traits<D, MIX>::Real;
+// A pair that does not interact (MASK): its exponent's high word becomes that
+// of a huge negative number, so the exp is 0 (one select instead of two).
+__device__ __forceinline__ double masked_exponent(bool active, double z) {
+  constexpr int kHuge = (int)0xfe37e43c;   // -1e300
+  return __hiloint2double(active ? __double2hiint(z) : kHuge, __double2loint(z));
+}
+
+// RU: also accumulate the background moments R and U (see k_pass1_mixed).
+template <int D, bool MASK, bool RU, int SP>
+__device__ __forceinline__ void pass1_tile(Pass1Rows<D, false>& S, const typename Traits<D, false>::Rec* __restrict__ cols,
+                                           double* __restrict__ acc_w, int tile_base, const KParams& kp,
+                                           const double* __restrict__ tab, int k_begin) {
   constexpr int R = kRowsPerLane;
   const int lane = threadIdx.x & 63;
-  // base-2 (mixed) or natural (float64) exponent scales
-  static_assert(!MIX, "the float32 passes use the lane-rotation kernels");
-  const Real cb = Real(kp.alpha), ct = Real(kp.beta), cg = Real(kp.gamma), cw = Real(kp.omega);
+  const double cb = kp.alpha, ct = kp.beta, cg = kp.gamma, cw = kp.omega;
 #pragma unroll SP > 1 ? 2 : HK_FP64_UNROLL
   for (int kk = 0; kk < 64 / SP; ++kk) {
     const int c = lane ^ (k_begin + kk);
     const auto col = cols[c];
-    Real cK, cR, cU;
+    double cK, cR, cU;
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-      Real r2 = 0;
+      double r2 = 0;
 #pragma unroll
       for (int q = 0; q < D; ++q) {
-        const Real dx = S.x[r][q] - col.v[q];
-        r2 = dx * dx + r2;
+        const double dx = S.x[r][q] - col.v[q];
+        r2 = q == 0 ? dx * dx : __builtin_fma(dx, dx, r2);
       }
-      const Real dt = S.t[r] - col.v[D];
-      const Real dt2 = dt * dt;
+      const double dt = S.t[r] - col.v[D];
+      const double dt2 = dt * dt;
       // exponents as one product plus a fused multiply-add each
-      Real eb = exp_tab(-__builtin_fma(cb, r2, ct * dt2), tab);
-      Real es = exp_tab(-__builtin_fma(cg, r2, cw * dt), tab);
+      double zb = -__builtin_fma(cb, r2, ct * dt2);
+      double zs = -__builtin_fma(cg, r2, cw * dt);
       if (MASK) {
         const bool act = (tile_base + c) < S.first[r];
-        eb = act ? eb : Real(0);
-        es = act ? es : Real(0);
+        zb = masked_exponent(act, zb);
+        zs = masked_exponent(act, zs);
       }
+      const double eb = exp_tab(zb, tab);
+      const double es = exp_tab(zs, tab);
       // raw r2, dt^2 and dt moments
       S.a[r][0] += eb;
-      S.a[r][1] = eb * r2 + S.a[r][1];
-      S.a[r][2] = eb * dt2 + S.a[r][2];
+      if (RU) {
+        S.a[r][1] = __builtin_fma(eb, r2, S.a[r][1]);
+        S.a[r][2] = __builtin_fma(eb, dt2, S.a[r][2]);
+      }
       S.a[r][3] += es;
-      S.a[r][4] = es * r2 + S.a[r][4];
-      S.a[r][5] = es * dt + S.a[r][5];
+      S.a[r][4] = __builtin_fma(es, r2, S.a[r][4]);
+      S.a[r][5] = __builtin_fma(es, dt, S.a[r][5]);
       // column contributions summed over this lane's rows
       cK = r == 0 ? eb : cK + eb;
-      cR = r == 0 ? eb * r2 : eb * r2 + cR;
-      cU = r == 0 ? eb * dt2 : eb * dt2 + cU;
+      if (RU) {
+        cR = r == 0 ? eb * r2 : __builtin_fma(eb, r2, cR);
+        cU = r == 0 ? eb * dt2 : __builtin_fma(eb, dt2, cU);
+      }
     }
     atomicAdd(&acc_w[0 * 64 + c], cK);
-    atomicAdd(&acc_w[1 * 64 + c], cR);
-    atomicAdd(&acc_w[2 * 64 + c], cU);
+    if (RU) {
+      atomicAdd(&acc_w[1 * 64 + c], cR);
+      atomicAdd(&acc_w[2 * 64 + c], cU);
+    }
   }
 }
 
-template <int D, bool MIX, int SP>
+template <int D, bool RU, int SP>
 __global__ void __launch_bounds__(SP* kThreads) __attribute__((amdgpu_waves_per_eu(SP > 1 ? 4 : 1))) k_pass1(const ReqDesc* __restrict__ reqs, int nreq) {
   using Rec = typename Traits<D, false>::Rec;
   using Real = double;
   constexpr int R = kRowsPerLane;
-  constexpr int NQ = 3;
-  constexpr int QR = 6;
+  constexpr int NQ = RU ? 3 : 1;   // column sums
+  constexpr int QR = RU ? 6 : 4;   // row sums stored per item
   using Lds = PassLds<SP, NQ, QR>;
   __shared__ Rec s_rec[2][kTile];
   __shared__ double s_acc[Lds::kDoubles];
   __shared__ double s_exptab[kExpTab];   // 2^(j/kExpTab) for exp_tab
-  fill_exp_table(s_exptab);
   const int blk = blockIdx.x;
   const int rid = find_req(reqs, nreq, blk, 0);
   const ReqDesc& rq = reqs[rid];
+  fill_exp_table(s_exptab);   // the tiles' first barrier comes before its first use
   const KParams& kp = rq.kp;
   const auto rec = glb(static_cast<const Rec*>(rq.rec));
   const auto first = glb(rq.first);
@@ -457,12 +470,12 @@ __global__ void __launch_bounds__(SP* kThreads) __attribute__((amdgpu_waves_per_
     if (SP == 1 && tile > tile0)
       store_columns<SP, NQ, true>(s_acc + (buf ^ 1) * (Lds::kColumns / Lds::kBufs), pcol, kp, band, tile - 1);
     const bool full = !partial_band && (tile + 1) * kTile <= first_min;
-    if (tile_culled<D, MIX>(t_row0, &s_rec[buf][0], tile, kp)) {
+    if (tile_culled<D, false>(t_row0, &s_rec[buf][0], tile, kp)) {
       // nothing to add: the tile's column sums stay zero
     } else if (full) {
-      pass1_tile<D, MIX, false, SP>(S, s_rec[buf], acc_w, tile * kTile, kp, s_exptab, group * (64 / SP));
+      pass1_tile<D, false, RU, SP>(S, s_rec[buf], acc_w, tile * kTile, kp, s_exptab, group * (64 / SP));
     } else {
-      pass1_tile<D, MIX, true, SP>(S, s_rec[buf], acc_w, tile * kTile, kp, s_exptab, group * (64 / SP));
+      pass1_tile<D, true, RU, SP>(S, s_rec[buf], acc_w, tile * kTile, kp, s_exptab, group * (64 / SP));
     }
     if constexpr (SP > 1) {
       __syncthreads();
@@ -474,15 +487,21 @@ __global__ void __launch_bounds__(SP* kThreads) __attribute__((amdgpu_waves_per_
     store_columns<SP, NQ, false>(s_acc + ((tile1 - 1 - tile0) & 1) * (Lds::kColumns / Lds::kBufs), pcol, kp, band,
                                  tile1 - 1);
   }
+  double rows[R][QR];
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+#pragma unroll
+    for (int q = 0; q < QR; ++q) rows[r][q] = S.a[r][RU || q == 0 ? q : q + 2];   // without RU: K, J, V, W
   if constexpr (SP > 1) {
-    add_groups<SP, QR>(S.a, s_acc, group);
+    add_groups<SP, QR>(rows, s_acc, group);
     if (group != 0) return;
   }
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     const int lr = wave * 64 * R + r * 64 + lane;
 #pragma unroll
-    for (int q = 0; q < 6; ++q) glb(static_cast<double*>(rq.prow))[((int64_t)item * 6 + q) * kBandRows + lr] = S.a[r][q];
+    for (int q = 0; q < QR; ++q)
+      glb(static_cast<double*>(rq.prow))[((int64_t)item * QR + q) * kBandRows + lr] = rows[r][q];
   }
 }
 
@@ -541,20 +560,17 @@ __device__ __forceinline__ void group_sum(double (&v)[NV], double* sh) {
   __syncthreads();
 }
 
-// Partner segments per flagged row: more when few rows are flagged, so that
-// their tasks still spread over the chip; never more tasks than fix_slots.
-__host__ __device__ inline int fix_segments(int cnt) {
-  return cnt <= 128 ? 16 : cnt <= 512 ? 8 : cnt <= 1024 ? 4 : cnt <= 4096 ? 2 : 1;
-}
-
 // Exact float64 recomputation of each flagged row i: the six row sums and (in
 // gradient calls) the row's own side of the location gradient,
-//   sum_j [mu_ij/tau_x^2 + (t_j < t_i) xi_ij/h^2] (x_j - x_i)   (over lambda_i),
-// over one segment of partners per task.  Each task finds its segment's
-// largest log pair term m_s and sums terms times exp(-m_s), so no term that
-// matters can underflow; the segments are merged, in order, where they are read
-// (merge_row).  fixpart[(f * segs + s) * kFixStride + q]: q < 6 the unweighted
-// sums times exp(-m_s), q = 6 m_s, q = 8 .. 8 + D the weighted vector.
+//   sum_j [mu_ij/tau_x^2 + (t_j < t_i) xi_ij/h^2] (x_j - x_i) / lambda_i,
+// one workgroup per row.  It finds the row's largest log pair term m and sums
+// terms times exp(-m), so no term that matters can underflow.  What the last
+// reduction reads of row f of the list, fixpart[f * kFixStride + q]:
+// q < 6 the unweighted sums times exp(-m), 6: m, 7: log lambda_i, 8: t_i,
+// 9 ..: x_i, 17 ..: the gradient vector.  (Rows split over 16 partner segments,
+// merged by every workgroup of the last reduction, cost it 14 us at N = 50,000
+// with about 40 flagged rows; whole rows cost nothing there, and hide behind
+// the gradient pass here: about 25 us a row and workgroup at that size.)
 // The ordered list of flagged rows comes from k_reduce1's per-block counts
 // and staged rows: every workgroup scans the counts (each thread over a chunk
 // of consecutive blocks) and finds its tasks' rows from the scan; workgroup 0
@@ -594,11 +610,8 @@ __device__ __forceinline__ void fix_rows(const ReqDesc& rq, int bx, int nbx, dou
   }
   const auto x = glb(rq.x);
   const auto t = glb(rq.t);
-  const int segs = fix_segments(cnt);
-  const int seg = (kp.n + segs - 1) / segs;
   const double wb = kp.cbg * kp.itx2, ws = kp.cse * kp.ih2;
-  for (int64_t task = bx; task < (int64_t)cnt * segs; task += nbx) {
-    const int f = (int)(task / segs), sg = (int)(task % segs);
+  for (int f = bx; f < cnt; f += nbx) {
     // row f of the list: the first chunk whose inclusive count exceeds f,
     // then the block inside it
     int c0 = 0, c1 = nt - 1;
@@ -610,13 +623,12 @@ __device__ __forceinline__ void fix_rows(const ReqDesc& rq, int bx, int nbx, dou
     int b = c0 * per;
     for (int cb = glb(rq.bcount)[b]; r >= cb; cb = glb(rq.bcount)[b]) { r -= cb; ++b; }
     const int i = glb(rq.bstage)[(int64_t)b * kRedEv + r];
-    const int j0 = sg * seg, j1 = min(kp.n, j0 + seg);
     double xi[D];
 #pragma unroll
     for (int q = 0; q < D; ++q) xi[q] = x[(int64_t)i * D + q];
     const double ti = t[i];
     double m = -INFINITY;
-    for (int j = j0 + tid; j < j1; j += nt) {
+    for (int j = tid; j < kp.n; j += nt) {
       if (j == i) continue;
       double r2 = 0;
 #pragma unroll
@@ -635,7 +647,7 @@ __device__ __forceinline__ void fix_rows(const ReqDesc& rq, int bx, int nbx, dou
     double a[6 + D];
 #pragma unroll
     for (int q = 0; q < 6 + D; ++q) a[q] = 0.0;
-    for (int j = j0 + tid; j < j1; j += nt) {
+    for (int j = tid; j < kp.n; j += nt) {
       if (j == i) continue;
       double dx[D], r2 = 0;
 #pragma unroll
@@ -657,12 +669,18 @@ __device__ __forceinline__ void fix_rows(const ReqDesc& rq, int bx, int nbx, dou
     }
     group_sum(a, sh);
     if (tid == 0) {
-      const auto fp = glb(rq.fixpart) + task * kFixStride;
+      const auto fp = glb(rq.fixpart) + (int64_t)f * kFixStride;
+      const double lt = kp.cbg * a[0] + kp.cse * a[3];
 #pragma unroll
       for (int q = 0; q < 6; ++q) fp[q] = a[q];
-      fp[6] = m;
+      fp[6] = msub;
+      fp[7] = log(lt) + msub;   // -inf: the rate is zero
+      fp[8] = ti;
 #pragma unroll
-      for (int q = 0; q < D; ++q) fp[8 + q] = a[6 + q];
+      for (int q = 0; q < D; ++q) {
+        fp[9 + q] = xi[q];
+        fp[17 + q] = a[6 + q] / lt;
+      }
     }
   }
 }
@@ -775,45 +793,49 @@ struct Pass2Rows {
   double acc[R][D];
 };
 
-template <int D, bool MIX, bool MASK, int SP>
-__device__ __forceinline__ void pass2_tile(Pass2Rows<D, MIX>& S, const typename Traits<D, MIX>::Rec* __restrict__ cols,
-                                           typename Traits<D, MIX>::ColT* __restrict__ acc_w, int tile_base,
-                                           const KParams& kp, const double* __restrict__ tab, int k_begin) {
-  using Real = typename Traits<D, MIX>::Real;
+template <int D, bool MASK, int SP>
+__device__ __forceinline__ void pass2_tile(Pass2Rows<D, false>& S, const typename Traits<D, false>::Rec* __restrict__ cols,
+                                           double* __restrict__ acc_w, int tile_base, const KParams& kp,
+                                           const double* __restrict__ tab, int k_begin) {
   constexpr int R = kRowsPerLane;
   const int lane = threadIdx.x & 63;
-  static_assert(!MIX, "the float32 passes use the lane-rotation kernels");
-  const Real cb = Real(kp.alpha), ct = Real(kp.beta), cg = Real(kp.gamma), cw = Real(kp.omega);
+  const double cb = kp.alpha, ct = kp.beta, cg = kp.gamma, cw = kp.omega;
 #pragma unroll SP > 1 ? 2 : HK_FP64_UNROLL
   for (int kk = 0; kk < 64 / SP; ++kk) {
     const int c = lane ^ (k_begin + kk);
     const auto col = cols[c];
-    Real cgr[D];
-#pragma unroll
-    for (int q = 0; q < D; ++q) cgr[q] = 0;
+    double cgr[D];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-      Real dx[D];
-      Real r2 = 0;
+      double dx[D];
+      double r2 = 0;
 #pragma unroll
       for (int q = 0; q < D; ++q) {
         dx[q] = S.x[r][q] - col.v[q];
-        r2 = dx[q] * dx[q] + r2;
+        r2 = q == 0 ? dx[q] * dx[q] : __builtin_fma(dx[q], dx[q], r2);
       }
-      const Real dt = S.t[r] - col.v[D];
+      const double dt = S.t[r] - col.v[D];
+      const double dt2 = dt * dt;
       // exponents as one product plus a fused multiply-add each
-      Real eb = exp_tab(-__builtin_fma(cb, r2, ct * (dt * dt)), tab);
-      Real es = exp_tab(-__builtin_fma(cg, r2, cw * dt), tab);
+      double zb = -__builtin_fma(cb, r2, ct * dt2);
+      double zs = -__builtin_fma(cg, r2, cw * dt);
       if (MASK) {
         const bool act = (tile_base + c) < S.first[r];
-        eb = act ? eb : Real(0);
-        es = act ? es : Real(0);
+        zb = masked_exponent(act, zb);
+        zs = masked_exponent(act, zs);
       }
-      const Real coef = eb * (S.pb[r] + col.v[D + 1]) + es * S.ps[r];
+      const double eb = exp_tab(zb, tab);
+      const double es = exp_tab(zs, tab);
+      // background weight of the pair with both endpoints' 1/lambda; its r^2
+      // and dt^2 moments give the R and U terms of the tau_x and tau_t gradients
+      const double wb = eb * (S.pb[r] + col.v[D + 1]);
+      const double coef = __builtin_fma(es, S.ps[r], wb);
+      S.mom[0] = __builtin_fma(wb, r2, S.mom[0]);
+      S.mom[1] = __builtin_fma(wb, dt2, S.mom[1]);
 #pragma unroll
       for (int q = 0; q < D; ++q) {
-        S.g[r][q] = -coef * dx[q] + S.g[r][q];
-        cgr[q] = coef * dx[q] + cgr[q];
+        S.g[r][q] = __builtin_fma(-coef, dx[q], S.g[r][q]);
+        cgr[q] = r == 0 ? coef * dx[q] : __builtin_fma(coef, dx[q], cgr[q]);
       }
     }
 #pragma unroll
@@ -821,7 +843,7 @@ __device__ __forceinline__ void pass2_tile(Pass2Rows<D, MIX>& S, const typename 
   }
 }
 
-template <int D, bool MIX, int SP>
+template <int D, int SP>
 __global__ void __launch_bounds__(SP* kThreads) __attribute__((amdgpu_waves_per_eu(SP > 1 ? 4 : 1))) k_pass2(const ReqDesc* __restrict__ reqs, int nreq, int ev_blocks) {
   using Rec = typename Traits<D, false>::Rec;
   using Real = double;
@@ -832,6 +854,7 @@ __global__ void __launch_bounds__(SP* kThreads) __attribute__((amdgpu_waves_per_
   __shared__ Rec s_rec[2][kTile];
   __shared__ double s_acc[Lds::kDoubles];
   __shared__ double s_exptab[kExpTab];   // 2^(j/kExpTab) for exp_tab
+  __shared__ double s_red[2 * SP * kWaves];
   // the fix-up and finalize blocks come first (their results are read by the
   // next kernel only); nothing in the pair pass depends on them
   const int blk = (int)blockIdx.x - side_blocks(nreq, ev_blocks);
@@ -839,9 +862,9 @@ __global__ void __launch_bounds__(SP* kThreads) __attribute__((amdgpu_waves_per_
     side_block<D, false>(reqs, nreq, ev_blocks, s_acc);
     return;
   }
-  fill_exp_table(s_exptab);
   const int rid = find_req(reqs, nreq, blk, 0);
   const ReqDesc& rq = reqs[rid];
+  fill_exp_table(s_exptab);   // the tiles' first barrier comes before its first use
   const KParams& kp = rq.kp;
   const auto rec = glb(static_cast<const Rec*>(rq.rec));
   const auto first = glb(rq.first);
@@ -861,6 +884,7 @@ __global__ void __launch_bounds__(SP* kThreads) __attribute__((amdgpu_waves_per_
   const auto t_row0 = rec[row_base].v[D];   // the band's first row (culling)
 
   Pass2Rows<D, false> S;
+  S.mom[0] = S.mom[1] = 0.0;
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     const int gi = row_base + wave * 64 * R + r * 64 + lane;
@@ -888,12 +912,12 @@ __global__ void __launch_bounds__(SP* kThreads) __attribute__((amdgpu_waves_per_
     if (SP == 1 && tile > tile0)
       store_columns<SP, NQ, true>(s_acc + (buf ^ 1) * (Lds::kColumns / Lds::kBufs), pcol, kp, band, tile - 1);
     const bool full = !partial_band && (tile + 1) * kTile <= first_min;
-    if (tile_culled<D, MIX>(t_row0, &s_rec[buf][0], tile, kp)) {
+    if (tile_culled<D, false>(t_row0, &s_rec[buf][0], tile, kp)) {
       // nothing to add: the tile's column sums stay zero
     } else if (full) {
-      pass2_tile<D, MIX, false, SP>(S, s_rec[buf], acc_w, tile * kTile, kp, s_exptab, group * (64 / SP));
+      pass2_tile<D, false, SP>(S, s_rec[buf], acc_w, tile * kTile, kp, s_exptab, group * (64 / SP));
     } else {
-      pass2_tile<D, MIX, true, SP>(S, s_rec[buf], acc_w, tile * kTile, kp, s_exptab, group * (64 / SP));
+      pass2_tile<D, true, SP>(S, s_rec[buf], acc_w, tile * kTile, kp, s_exptab, group * (64 / SP));
     }
     if constexpr (SP > 1) {
       __syncthreads();
@@ -904,6 +928,13 @@ __global__ void __launch_bounds__(SP* kThreads) __attribute__((amdgpu_waves_per_
     __syncthreads();
     store_columns<SP, NQ, false>(s_acc + ((tile1 - 1 - tile0) & 1) * (Lds::kColumns / Lds::kBufs), pcol, kp, band,
                                  tile1 - 1);
+  }
+  // the item's two moment sums, fixed-order over the workgroup
+  double mom[2] = {S.mom[0], S.mom[1]};
+  group_sum(mom, s_red);
+  if (threadIdx.x == 0) {
+    glb(rq.mompart)[(int64_t)item * 2 + 0] = mom[0];
+    glb(rq.mompart)[(int64_t)item * 2 + 1] = mom[1];
   }
   if constexpr (SP > 1) {
     add_groups<SP, QR>(S.g, s_acc, group);
@@ -1375,7 +1406,7 @@ __global__ void __launch_bounds__(kRedThreads) k_reduce1(const ReqDesc* __restri
   const auto prow = glb(static_cast<const ColT*>(rq.prow));
   const auto pcol = glb(static_cast<const ColT*>(rq.pcol));
   double s[6] = {0, 0, 0, 0, 0, 0};
-  if (!MIX || kp.ru1) {
+  if (kp.ru1) {
 #pragma unroll 2
     for (int c = wave; c < bi.y; c += kRedWaves) {
       const auto p = prow + (int64_t)(bi.x + c) * 6 * kBandRows + lr;
@@ -1437,32 +1468,9 @@ __global__ void __launch_bounds__(kRedThreads) k_reduce1(const ReqDesc* __restri
   if (lane == 0) glb(rq.bcount)[lb] = __popcll(m);
 }
 
-// The merged sums of a flagged row, by the 16 lanes of one DPP row: lane g
-// holds segment g (segs <= 16; lanes without one hold nothing), all loads at
-// once.  Common scale m = max_s m_s (0 when every term is zero); the sums, in
-// a fixed order, end in the row's lane 15; every lane gets m and its own
-// segment's weight exp(m_g - m).
-struct MergedRow {
-  double s[6];   // lane 15
-  double m, w;
-};
-__device__ __forceinline__ MergedRow merge_row(const double HK_GLOBAL* fp, bool has) {
-  MergedRow r;
-  const double mg = has ? fp[6] : -INFINITY;
-  double m = mg;
-#pragma unroll
-  for (int o = 1; o < 16; o <<= 1) m = fmax(m, __shfl_xor(m, o));
-  const bool any = m > -INFINITY;
-  r.m = any ? m : 0.0;
-  r.w = mg > -INFINITY ? exp(mg - m) : 0.0;
-#pragma unroll
-  for (int q = 0; q < 6; ++q) r.s[q] = row_sum_last(has && mg > -INFINITY ? fp[q] * r.w : 0.0);
-  return r;
-}
-
 // ell, the six parameter gradients and the status of one request: the
-// finalize blocks' sums, the flagged rows' terms and (mixed gradient calls)
-// the gradient pass's two moment sums, all in a fixed order.
+// finalize blocks' sums, the flagged rows' terms and (gradient calls) the
+// gradient pass's two moment sums, all in a fixed order.
 // out8 = [ell, 6 gradients, status].  kRedThreads threads.
 template <int D, bool MIX>
 __device__ __forceinline__ void final_block(const ReqDesc& rq, double* pool) {
@@ -1475,7 +1483,7 @@ __device__ __forceinline__ void final_block(const ReqDesc& rq, double* pool) {
     for (int b = tid; b < kp.nblk; b += kRedThreads)
 #pragma unroll
       for (int q = 0; q < 8; ++q) v[q] += glb(rq.bpart)[(int64_t)b * 8 + q];
-    if (MIX && !kp.ru1) {
+    if (!kp.ru1) {
       // the background moments' terms of d ell/d tau_x and d ell/d tau_t, from
       // the gradient pass's item sums: sum over pairs of
       // w r'^2 = sum_n c_bg R_n / (tau_x^3 lambda_n) and w dt'^2 tau_x / tau_t =
@@ -1486,22 +1494,19 @@ __device__ __forceinline__ void final_block(const ReqDesc& rq, double* pool) {
         mom[1] += glb(rq.mompart)[(int64_t)it * 2 + 1];
       }
     }
-    const int cnt = uni(glb(rq.status)[kStFlagCount]);
-    const int segs = fix_segments(cnt);
-    const int g = tid & 15;
-    for (int f0 = 0; f0 < cnt; f0 += kRedThreads / 16) {
-      const int f = f0 + (tid >> 4);
-      const bool row = f < cnt;
-      const MergedRow mr =
-          merge_row(glb(rq.fixpart) + ((int64_t)(row ? f : 0) * segs + min(g, segs - 1)) * kFixStride, row && g < segs);
-      if (row && g == 15) {
-        const double lt = rate_terms<D>(kp, mr.s, mr.m, v);
-        store_terms(rq, glb(rq.list)[f], mr.s, lt, mr.m);
-      }
+    const int cnt = glb(rq.status)[kStFlagCount];
+    for (int f = tid; f < cnt; f += kRedThreads) {
+      const auto fp = glb(rq.fixpart) + (int64_t)f * kFixStride;
+      double s[6];
+#pragma unroll
+      for (int q = 0; q < 6; ++q) s[q] = fp[q];
+      const double lt = rate_terms<D>(kp, s, fp[6], v);
+      store_terms(rq, glb(rq.list)[f], s, lt, fp[6]);
     }
   }
-  v[2] += mom[0];
-  v[3] += mom[1] * kp.tau_x / kp.tau_t;
+  // mixed sums are in bandwidth units and carry 1/tau_x, float64 ones 1/tau_x^2
+  v[2] += MIX ? mom[0] : mom[0] / kp.tau_x;
+  v[3] += MIX ? mom[1] * kp.tau_x / kp.tau_t : mom[1] * (kp.tau_x * kp.tau_x / (kp.tau_t * kp.tau_t * kp.tau_t));
   group_sum(v, pool);
   if (tid == 0) {
     double o[8];
@@ -1533,16 +1538,14 @@ __global__ void __launch_bounds__(kRedThreads) k_final(const ReqDesc* __restrict
 // Fix-up terms.  For a flagged row j and any event i the j-side coefficient
 // c = mu_ij/(lambda_j tau_x^2) + [t_i < t_j] xi_ji/(lambda_j h^2) is formed in
 // float64 as exp(log-term - log lambda_j): every event adds c (x_j - x_i) over
-// the flagged rows (the workgroup merges kFixChunk rows at a time into LDS,
-// its waves take every kRedWaves-th of them), and a flagged row adds its own
-// merged vector.
-constexpr int kFixChunk = kRedThreads / 16;   // 16 lanes merge a row
+// the flagged rows (kFixChunk at a time in LDS, every kRedWaves-th of them per
+// wave), and a flagged row adds its own vector.
+constexpr int kFixChunk = 256;
 
 template <int D, bool MIX>
 __global__ void __launch_bounds__(kRedThreads) k_reduce2(const ReqDesc* __restrict__ reqs, int nreq) {
-  __shared__ double s_pool[kRedWaves * D * kRedEv];
-  __shared__ double s_own[kRedEv][D];   // this workgroup's flagged rows: their merged vectors
-  static_assert(kFixChunk * (D + 2) <= kRedWaves * D * kRedEv, "a chunk of flagged rows fits the pool");
+  constexpr int kMeet = kRedWaves * D * kRedEv, kFlagged = kFixChunk * (D + 2);
+  __shared__ double s_pool[kMeet > kFlagged ? kMeet : kFlagged];
   if ((int)blockIdx.x < nreq) {
     final_block<D, MIX>(reqs[blockIdx.x], s_pool);
     return;
@@ -1555,7 +1558,6 @@ __global__ void __launch_bounds__(kRedThreads) k_reduce2(const ReqDesc* __restri
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int i0 = lb * kRedEv;
   const int i = i0 + lane;   // >= n only in the last band's padding (read, never written)
-  const auto grad_x = glb(rq.grad_x);
   const int cnt = uni(glb(rq.status)[kStFlagCount]);
   const int b = i0 / kBandRows, lr = i % kBandRows;
   const IPair bi{band_first_item(kp, b), band_items(kp, b)};
@@ -1577,42 +1579,19 @@ __global__ void __launch_bounds__(kRedThreads) k_reduce2(const ReqDesc* __restri
     for (int q = 0; q < D; ++q) s[q] += p[(int64_t)q * kp.n_pad];
   }
   int zero = 0;
-  const int segs = fix_segments(cnt);
   if (cnt > 0) {
-    const auto x = glb(rq.x);
-    const auto t = glb(rq.t);
     const int ic = min(i, kp.n - 1);
     double xi[D];
 #pragma unroll
-    for (int q = 0; q < D; ++q) xi[q] = x[(int64_t)ic * D + q];
-    const double ti = t[ic];
-    const int g = threadIdx.x & 15, row = threadIdx.x >> 4;
+    for (int q = 0; q < D; ++q) xi[q] = glb(rq.x)[(int64_t)ic * D + q];
+    const double ti = glb(rq.t)[ic];
     for (int f0 = 0; f0 < cnt; f0 += kFixChunk) {
       const int fn = min(kFixChunk, cnt - f0);
       __syncthreads();
-      if ((wave << 2) < fn) {   // whole waves, four rows each
-        const bool in = row < fn;
-        const int f = f0 + (in ? row : 0);
-        const auto fp = glb(rq.fixpart) + ((int64_t)f * segs + min(g, segs - 1)) * kFixStride;
-        const int j = glb(rq.list)[f];
-        const MergedRow mr = merge_row(fp, in && g < segs);
-        const double lt = kp.cbg * mr.s[0] + kp.cse * mr.s[3];   // lane 15
-        if (in && g == 15) {
-          zero |= lt > 0.0 ? 0 : 1;
-          double* e = s_pool + row * (D + 2);
-          e[0] = log(lt) + mr.m;
-          e[1] = t[j];
-#pragma unroll
-          for (int q = 0; q < D; ++q) e[2 + q] = x[(int64_t)j * D + q];
-        }
-        if (__any(in && j >= i0 && j < i0 + kRedEv)) {
-          const bool have = in && g < segs && mr.w > 0.0;
-#pragma unroll
-          for (int q = 0; q < D; ++q) {
-            const double v = row_sum_last(have ? fp[8 + q] * mr.w : 0.0);
-            if (in && g == 15 && j >= i0 && j < i0 + kRedEv) s_own[j - i0][q] = v / lt;
-          }
-        }
+      for (int e = threadIdx.x; e < fn * (D + 2); e += kRedThreads) {
+        const double v = glb(rq.fixpart)[(int64_t)(f0 + e / (D + 2)) * kFixStride + 7 + e % (D + 2)];
+        if (e % (D + 2) == 0) zero |= v > -INFINITY ? 0 : 1;
+        s_pool[e] = v;   // log lambda_j, t_j, x_j
       }
       __syncthreads();
       for (int k = wave; k < fn; k += kRedWaves) {
@@ -1645,10 +1624,10 @@ __global__ void __launch_bounds__(kRedThreads) k_reduce2(const ReqDesc* __restri
   }
   if (cnt > 0 && glb(rq.flags)[i] != 0) {
 #pragma unroll
-    for (int q = 0; q < D; ++q) s[q] += s_own[lane][q];
+    for (int q = 0; q < D; ++q) s[q] += glb(rq.fixpart)[(int64_t)glb(rq.listpos)[i] * kFixStride + 17 + q];
   }
 #pragma unroll
-  for (int q = 0; q < D; ++q) grad_x[(int64_t)i * D + q] = zero ? NAN : s[q];   // NaN: some rate is zero
+  for (int q = 0; q < D; ++q) glb(rq.grad_x)[(int64_t)i * D + q] = zero ? NAN : s[q];   // NaN: some rate is zero
 }
 
 }  // namespace hawkes

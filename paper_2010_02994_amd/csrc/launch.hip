@@ -28,7 +28,8 @@ static bool launch_phases(const ReqDesc* reqs, int nreq, const BatchGrid& g, boo
     if (grad) k_pass1_mixed<D, false><<<g.items, kThreads, 0, s>>>(reqs, nreq);
     else k_pass1_mixed<D, true><<<g.items, kThreads, 0, s>>>(reqs, nreq);
   } else {
-    k_pass1<D, MIX, SP><<<g.items, SP * kThreads, 0, s>>>(reqs, nreq);
+    if (grad) k_pass1<D, false, SP><<<g.items, SP * kThreads, 0, s>>>(reqs, nreq);
+    else k_pass1<D, true, SP><<<g.items, SP * kThreads, 0, s>>>(reqs, nreq);
   }
   mark_stage(s, 3);
   k_reduce1<D, MIX><<<g.red_blocks, kRedThreads, 0, s>>>(reqs, nreq);
@@ -44,7 +45,7 @@ static bool launch_phases(const ReqDesc* reqs, int nreq, const BatchGrid& g, boo
   mark_stage(s, 5);
   mark_stage(s, 6);
   if constexpr (MIX) k_pass2_mixed<D><<<side + g.items, kThreads, 0, s>>>(reqs, nreq, g.ev_blocks);
-  else k_pass2<D, MIX, SP><<<side + g.items, SP * kThreads, 0, s>>>(reqs, nreq, g.ev_blocks);
+  else k_pass2<D, SP><<<side + g.items, SP * kThreads, 0, s>>>(reqs, nreq, g.ev_blocks);
   mark_stage(s, 7);
   mark_stage(s, 8);
   k_reduce2<D, MIX><<<nreq + g.red_blocks, kRedThreads, 0, s>>>(reqs, nreq);
