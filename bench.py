@@ -28,8 +28,8 @@ sys.path.insert(0, ROOT)
 METRIC = "pair-interactions/s for Hawkes loglik+grad (FP64 vs mixed); serve p50/p99 ms"
 STAGES = ["prep", "pack", "pass1", "reduce1", "fix1", "final1", "pass2", "fix2", "reduce2"]
 KERNEL_NAMES = {"pass1": "k_pass1", "pass2": "k_pass2"}
-PROFILED_NAMES = {("pass1", "mixed"): "hawkes::k_pass1_mixed<2, false>", ("pass2", "mixed"): "hawkes::k_pass2_mixed<2>",
-                  ("pass1", "fp64"): "hawkes::k_pass1<2, false, 1>", ("pass2", "fp64"): "hawkes::k_pass2<2, 1>"}
+PROFILED_NAMES = {("pass1", "mixed"): "hawkes::k_pass1_mixed<2, false, false>", ("pass2", "mixed"): "hawkes::k_pass2_mixed<2, false>",
+                  ("pass1", "fp64"): "hawkes::k_pass1<2, false, 1, false>", ("pass2", "fp64"): "hawkes::k_pass2<2, 1, false>"}
 
 # Peaks of the chip (256 CUs at 2.4 GHz).  FP32 vector: 157.3 TFLOP/s.  The
 # v_exp_f32 issue rate is 32 lanes per CU per clock (measured by the peaks

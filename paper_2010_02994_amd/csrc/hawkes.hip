@@ -206,20 +206,16 @@ KParams make_kparams(const Layout& Lo, const hawkes_params_t* p) {
   k.sigma_main = -S * std::log(2.0);
   k.flag_floor = Lo.mixed ? kFloorMixed : kFloorFp64;
   // Culling distances, ignoring the spatial parts of the exponents (which
-  // only lower them).  Mixed: both base-2 exponents S - mB dt^2 and S - mW dt
+  // only lower them).  Mixed: the term's base-2 exponent S - mB dt^2 or S - mW dt
   // (dt in units of tau_t) below -160, where exp2 is 0 to any rounding.
-  // Float64: both natural exponents -beta dt^2 and -omega dt below -750,
-  // where exp is 0.
-  k.cull = Lo.cull;
+  // Float64: its natural exponent -beta dt^2 or -omega dt below -750, where exp
+  // is 0.
   k.ru1 = 1;
-  if (Lo.mixed) {
-    const double lim = S + 160.0;
-    k.cull_dtf = (float)std::max(std::sqrt(lim / (double)k.mB), lim / (double)k.mW);
-    k.cull_dt = (double)k.cull_dtf * k.tau_t;
-  } else {
-    k.cull_dt = std::max(std::sqrt(750.0 / k.beta), 750.0 / k.omega);
-    k.cull_dtf = (float)(k.cull_dt / k.tau_t);
-  }
+  const double lim = S + 160.0;
+  k.cull_bgf = (float)std::sqrt(lim / (double)k.mB);
+  k.cull_sef = (float)(lim / (double)k.mW);
+  k.cull_bg = std::sqrt(750.0 / k.beta);
+  k.cull_se = 750.0 / k.omega;
   return k;
 }
 
@@ -390,19 +386,19 @@ static PinnedPool& pinned_pool() {
 // offsets filled in), or, with one != nullptr, a single request whose
 // descriptor the first kernel copies to dev_reqs[0].  Returns HAWKES_EDEVICE if
 // a launch failed.
-int launch_batch(int d, int mixed, int split, const ReqDesc* dev_reqs, int nreq, const BatchGrid& g, bool grad,
+int launch_batch(int d, int mixed, int cull, int split, const ReqDesc* dev_reqs, int nreq, const BatchGrid& g, bool grad,
                  hipStream_t s, const ReqDesc* one) {
   (void)hipGetLastError();
   bool ok = false;
   switch (d) {
-    case 1: ok = launch_d<1>(mixed, split, dev_reqs, nreq, g, grad, s, one); break;
-    case 2: ok = launch_d<2>(mixed, split, dev_reqs, nreq, g, grad, s, one); break;
-    case 3: ok = launch_d<3>(mixed, split, dev_reqs, nreq, g, grad, s, one); break;
-    case 4: ok = launch_d<4>(mixed, split, dev_reqs, nreq, g, grad, s, one); break;
-    case 5: ok = launch_d<5>(mixed, split, dev_reqs, nreq, g, grad, s, one); break;
-    case 6: ok = launch_d<6>(mixed, split, dev_reqs, nreq, g, grad, s, one); break;
-    case 7: ok = launch_d<7>(mixed, split, dev_reqs, nreq, g, grad, s, one); break;
-    case 8: ok = launch_d<8>(mixed, split, dev_reqs, nreq, g, grad, s, one); break;
+    case 1: ok = launch_d<1>(mixed, cull, split, dev_reqs, nreq, g, grad, s, one); break;
+    case 2: ok = launch_d<2>(mixed, cull, split, dev_reqs, nreq, g, grad, s, one); break;
+    case 3: ok = launch_d<3>(mixed, cull, split, dev_reqs, nreq, g, grad, s, one); break;
+    case 4: ok = launch_d<4>(mixed, cull, split, dev_reqs, nreq, g, grad, s, one); break;
+    case 5: ok = launch_d<5>(mixed, cull, split, dev_reqs, nreq, g, grad, s, one); break;
+    case 6: ok = launch_d<6>(mixed, cull, split, dev_reqs, nreq, g, grad, s, one); break;
+    case 7: ok = launch_d<7>(mixed, cull, split, dev_reqs, nreq, g, grad, s, one); break;
+    case 8: ok = launch_d<8>(mixed, cull, split, dev_reqs, nreq, g, grad, s, one); break;
   }
   return ok && hipGetLastError() == hipSuccess ? HAWKES_OK : HAWKES_EDEVICE;
 }
@@ -446,7 +442,7 @@ int run_async(const double* x, const double* t, int64_t n, int d, const hawkes_p
   desc.out_host = grad_x ? out_host : nullptr;   // written by k_reduce2, which only gradient calls run
   const BatchGrid g = assign_blocks(&desc, 1);
   ReqDesc* dev = at<ReqDesc>(ws, Lo.off_desc);
-  return launch_batch(d, Lo.mixed, Lo.split, dev, 1, g, grad_x != nullptr, s, &desc);
+  return launch_batch(d, Lo.mixed, Lo.cull, Lo.split, dev, 1, g, grad_x != nullptr, s, &desc);
 }
 
 int run_sync(const double* x, const double* t, int64_t n, int d, const hawkes_params_t* p, int prec, void* ws,

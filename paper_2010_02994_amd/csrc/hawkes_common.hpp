@@ -120,13 +120,12 @@ struct KParams {
   double inv_tx, inv_tt;      // 1/tau_x, 1/tau_t (packing scales)
   double sigma_main;          // natural log of the scale the main pass sums carry (-S ln 2, or 0)
   double flag_floor;          // a row is recomputed when lambda~ < cmax * 2^flag_floor
-  // exact culling (optional): a column tile whose every pair is further apart
-  // in time than cull_dt (in the records' time units) adds exactly zero
-  int cull;
+  // exact culling (optional): beyond these time distances (records' time
+  // units) the background, or the excitation, term of a pair is exactly zero
   int ru1;                    // the rate pass accumulates the background moments R, U (else the gradient pass
                               // forms their parameter-gradient terms: gradient calls)
-  float cull_dtf;             // mixed records: bandwidth units of tau_t
-  double cull_dt;             // float64 records: time units
+  float cull_bgf, cull_sef;   // mixed records: bandwidth units of tau_t
+  double cull_bg, cull_se;    // float64 records: time units
 };
 
 // One request of a launch: its constants, its inputs and outputs, the pieces

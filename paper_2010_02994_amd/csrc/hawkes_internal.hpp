@@ -33,7 +33,7 @@ ReqDesc make_desc(const Layout& Lo, const KParams& kp, const double* x, const do
                   double* grad_x);
 BatchGrid assign_blocks(ReqDesc* descs, int nreq);
 // split: the step groups of every request's pair passes (Layout::split).
-int launch_batch(int d, int mixed, int split, const ReqDesc* dev_reqs, int nreq, const BatchGrid& g, bool grad,
+int launch_batch(int d, int mixed, int cull, int split, const ReqDesc* dev_reqs, int nreq, const BatchGrid& g, bool grad,
                  hipStream_t s, const ReqDesc* one = nullptr);
 // Enqueue one full evaluation (validation, rate pass, finalize and, when
 // grad_x is not null, the gradient pass) with no host synchronization.
@@ -62,7 +62,7 @@ void fork_give(int dev, Fork* f);
 
 // The phases of a batch for dimension D (launch.hip, one object per D).
 template <int D>
-bool launch_d(int mixed, int split, const ReqDesc* reqs, int nreq, const BatchGrid& g, bool grad, hipStream_t s,
+bool launch_d(int mixed, int cull, int split, const ReqDesc* reqs, int nreq, const BatchGrid& g, bool grad, hipStream_t s,
               const ReqDesc* one);
 // While the stages are being timed (hawkes_grad_timed): records the event
 // before stage `stage` on s.

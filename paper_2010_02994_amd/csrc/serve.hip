@@ -290,7 +290,7 @@ bool admit_and_launch(hawkes_server* S) {
       if (hipMemcpyAsync(b.dev_desc, b.host_desc, sizeof(ReqDesc) * b.nreq, hipMemcpyHostToDevice, b.stream) !=
           hipSuccess)
         st = HAWKES_EDEVICE;
-      if (st == HAWKES_OK) st = launch_batch(cls_d, (cls_p & ~HAWKES_CULL) == HAWKES_MIXED, cls_s, b.dev_desc, b.nreq, g, grad, b.stream);
+      if (st == HAWKES_OK) st = launch_batch(cls_d, (cls_p & ~HAWKES_CULL) == HAWKES_MIXED, (cls_p & HAWKES_CULL) != 0, cls_s, b.dev_desc, b.nreq, g, grad, b.stream);
       if (st == HAWKES_OK &&
           hipMemcpyAsync(b.host_out, b.dev_out, sizeof(double) * 8 * b.nreq, hipMemcpyDeviceToHost, b.stream) !=
               hipSuccess)

@@ -76,3 +76,25 @@ def test_float64_step_groups(seed, n, d, ties):
     check("fp64", got, ref, w.params, label=w.name)
     ll = api.loglik(torch.tensor(w.x, device="cuda:0"), torch.tensor(w.t, device="cuda:0"), w.params, prec="fp64")
     assert abs(ll - ref.ll) <= 1e-10 * abs(ref.ll)
+
+
+@pytest.mark.parametrize("prec", ["mixed", "fp64"])
+@pytest.mark.parametrize("tau,omega", [(0.05, 0.5), (40.0, 300.0), (0.05, 300.0), (2.0, 40.0)])
+@pytest.mark.parametrize("n,d", [(1500, 2), (1100, 6), (6200, 1)])
+def test_culled_terms_are_bitwise_identical(prec, tau, omega, n, d):
+    """Far tiles that keep only the excitation term (short background
+    bandwidth), only the background term (fast decay), neither, and a mixture:
+    every output equals the all-pairs run's bit for bit, with and without the
+    gradient."""
+    import torch
+
+    from paper_2010_02994_amd import api
+    w = W.random_case(41, n, d, ties=3, t_span=400.0)
+    p = w.params.copy()
+    p[2], p[4] = tau, omega
+    say(f"case culled terms n={n} d={d} tau={tau} omega={omega} prec={prec}")
+    a = run_gpu(w.x, w.t, p, prec)
+    b = run_gpu(w.x, w.t, p, prec + "+cull")
+    assert a[0] == b[0] and np.array_equal(a[1], b[1]) and np.array_equal(a[2], b[2])
+    x, t = torch.tensor(w.x, device="cuda:0"), torch.tensor(w.t, device="cuda:0")
+    assert api.loglik(x, t, p, prec=prec) == api.loglik(x, t, p, prec=prec + "+cull")
