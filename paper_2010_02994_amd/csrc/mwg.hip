@@ -14,6 +14,7 @@
 // does not depend on locations.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdint>
 
@@ -26,10 +27,17 @@ namespace mwg {
 
 constexpr int kBlock = 256;
 constexpr double kGuard = 0x1p-16; // incremental update kept only above this share of its terms
-constexpr int kSeg = 32;          // partner segments per exactly recomputed row (workspace per event)
+constexpr int kSeg = 32;          // partner segments (workspace per event) of exactly recomputed rows
 constexpr int kMaxSeg = 512;      // at most, when few rows are listed
-constexpr int kExactGrid = 512;   // workgroups of the exact-row kernel (grid-stride over tasks)
+constexpr int kExactGrid = 512;   // workgroups of the exact-row kernel's listed rows (grid-stride over tasks)
 constexpr int kListThreads = 1024;
+// Steps of fewer than kManyMoved moved events over at most this many events are
+// two launches instead of three: the decision kernel merges the moved rows'
+// chunk sums and recomputes listed rows itself (all of its workgroups, the same
+// rows; a listed row is N / 256 pair terms per thread there, 32 at this size).
+// One moved event at N = 2,925: 9.6 us a step against 10.4 with three launches;
+// with 64, merging in every workgroup cost more than the launch (30 and 22 us).
+constexpr int kFewEvents = 8192;
 
 struct Model {
   double mu0, theta;
@@ -42,7 +50,9 @@ struct Step {
   Model m;
   double* x;            // n x D, moved rows overwritten on accept
   const double* t;
-  int n, nmove, nrb;    // events, moved events, row blocks
+  int n, nmove;         // events, moved events
+  int nrb, rows;        // row blocks and rows per block
+  int nchunk, chunk;    // partner chunks of the moved rows' sums and partners per chunk
   double* terms;        // n x 4 cached state
   const int64_t* idx;   // nmove moved events, strictly increasing
   const double* xnew;   // nmove x D proposed locations
@@ -51,18 +61,20 @@ struct Step {
   // workspace
   double* new_a;        // n each
   double* new_b;
-  double* dlog;         // incremental rows: log-rate change; listed rows: old log-rate
+  double* dlog;         // incremental rows: log-rate change; listed and moved rows: old log-rate
   int* flag;            // 0 incremental, 1 recompute exactly, 2 moved
   double* bpart;        // nrb: per row block, sum of dlog over its incremental rows
   int* bcount;          // nrb: rows of the block needing an exact recompute
-  int* stage;           // nrb x kBlock: those rows in index order
+  int* stage;           // nrb x rows: those rows in index order
   int* list;            // n: all of them in index order
-  double* part;         // n x kSeg x 2: segment sums (a, b) of the listed rows
+  double* part;         // listed rows' segment sums (a, b), n x kSeg x 2 at most
+  double* mpart;        // nchunk x nmove x 2: moved rows' chunk sums (at most n x kSeg x 2)
+  double* mrow;         // nmove x 2: moved rows' sums (three-launch steps)
   int* state;           // [accepted, list length]
 };
 
-// Contributions of event j to row i: background per unit mu0 (excluded at equal
-// times) and self-excitation per unit theta (only from strictly earlier j).
+// Contributions of event j to row i, without the pair weights: background
+// (excluded at equal times) and self-excitation (only from strictly earlier j).
 template <int D>
 __device__ __forceinline__ void pair_ab(const Model& m, const double* xi, double ti, const double* xj, double tj,
                                         double& a, double& b, const double* __restrict__ tab) {
@@ -73,8 +85,8 @@ __device__ __forceinline__ void pair_ab(const Model& m, const double* xi, double
     r2 = fma(dx, dx, r2);
   }
   const double dt = ti - tj;
-  a = dt != 0.0 ? m.cbg_unit * exp_tab(-m.alpha * r2 - m.beta * dt * dt, tab) : 0.0;
-  b = dt > 0.0 ? m.cse_unit * exp_tab(-m.omega * dt - m.gamma * r2, tab) : 0.0;
+  a = dt != 0.0 ? exp_tab(-m.alpha * r2 - m.beta * dt * dt, tab) : 0.0;
+  b = dt > 0.0 ? exp_tab(-m.omega * dt - m.gamma * r2, tab) : 0.0;
 }
 
 // Position of event j in the moved list, or -1 (binary search; the list is
@@ -112,28 +124,30 @@ __device__ __forceinline__ double block_sum(double v, double* sh) {
 // below 2^-16 of the terms it was formed from, so its rounding error could
 // exceed ~2^-37 of it) the row is listed for an exact recompute instead, so
 // float64 cancellation neither decides a move nor corrupts the cached parts.
-// Moved rows are listed too.  A workgroup covers kBlock rows with RL adjacent
-// lanes per row: each lane takes every RL-th moved event, and butterfly steps
-// combine the RL sums in a fixed order (the same on every lane), so a block of
-// many moved events is not one long chain per row.  Few moved events take one
-// lane per row (smaller workgroups start and finish sooner).
+// A workgroup covers kBlock / RL rows with RL adjacent lanes per row: each lane
+// takes every RL-th moved event, and butterfly steps combine the RL sums in a
+// fixed order (the same on every lane), so a block of many moved events is not
+// one long chain per row, and N = 50,000 rows make 782 workgroups of four waves
+// rather than 196 of sixteen, which left a quarter of the chip idle.  Few moved
+// events take one lane per row.
 constexpr int kRowLanesMany = 4;
 constexpr int kManyMoved = 8;   // moved events from which four lanes per row pay
 
 template <int D, int RL>
-__global__ void __launch_bounds__(RL * kBlock) k_mwg_rows(Step s) {
-  __shared__ double s_old[kBlock][D];
-  __shared__ double s_new[kBlock][D];
-  __shared__ double s_t[kBlock];
-  __shared__ int s_j[kBlock];
-  __shared__ double s_dl[kBlock];
-  __shared__ double sh[RL * kBlock];
-  __shared__ int s_wcnt[(RL * kBlock) / 64];
+__device__ __forceinline__ void moved_change(const Step& s, int blk) {
+  constexpr int kRows = kBlock / RL;
+  constexpr int kList = 64;    // moved events staged at a time
+  __shared__ double s_old[kList][D];
+  __shared__ double s_new[kList][D];
+  __shared__ double s_t[kList];
+  __shared__ int s_j[kList];
+  __shared__ double sh[kBlock / 64];
+  __shared__ int s_wcnt[kBlock / 64];
   __shared__ double s_exptab[kExpTab];   // 2^(j/kExpTab) for exp_tab (read after the loop's barrier)
   fill_exp_table(s_exptab);
   const int tid = threadIdx.x;
   const int rl = tid / RL, sub = tid % RL;
-  const int i = blockIdx.x * kBlock + rl;
+  const int i = blk * kRows + rl;
   const bool row = i < s.n;
   double xi[D], ti = 0.0;
 #pragma unroll
@@ -141,8 +155,8 @@ __global__ void __launch_bounds__(RL * kBlock) k_mwg_rows(Step s) {
   if (row) ti = s.t[i];
   double da = 0.0, db = 0.0, oa = 0.0, ob = 0.0;
   int moved = 0;
-  for (int c0 = 0; c0 < s.nmove; c0 += kBlock) {
-    const int cn = min(kBlock, s.nmove - c0);
+  for (int c0 = 0; c0 < s.nmove; c0 += kList) {
+    const int cn = min(kList, s.nmove - c0);
     __syncthreads();
     if (tid < cn) {
       const int64_t j = s.idx[c0 + tid];
@@ -183,6 +197,10 @@ __global__ void __launch_bounds__(RL * kBlock) k_mwg_rows(Step s) {
     ob += __shfl_xor(ob, o);
     moved |= __shfl_xor(moved, o);
   }
+  da *= s.m.cbg_unit;
+  oa *= s.m.cbg_unit;
+  db *= s.m.cse_unit;
+  ob *= s.m.cse_unit;
   int fl = 0;
   double dl = 0.0;
   if (row) {
@@ -206,32 +224,114 @@ __global__ void __launch_bounds__(RL * kBlock) k_mwg_rows(Step s) {
     }
     if (sub == 0) {
       s.flag[i] = fl;
-      // listed rows: their old log-rate, for the exact change formed later
+      // other rows: their old log-rate, for the exact change formed later
       s.dlog[i] = fl == 0 ? dl : s.terms[(int64_t)i * 4 + 2];
     }
   }
-  // block sum of the rows' log-rate changes over the row order (the first
-  // kBlock threads hold the rows, the rest zeros, so the tree is the one of a
-  // kBlock-thread sum)
-  if (sub == 0) s_dl[rl] = dl;
-  __syncthreads();
-  const double bs = block_sum(tid < kBlock ? s_dl[tid] : 0.0, sh);
+  // block sum of the rows' log-rate changes (one lane per row counts)
+  const double bs = block_sum(sub == 0 ? dl : 0.0, sh);
   // stage the rows needing an exact recompute, in index order (one lane per row votes)
-  const bool listed = row && sub == 0 && fl != 0;
+  const bool listed = row && sub == 0 && fl == 1;
   const unsigned long long msk = __ballot(listed);
   const int lane = tid & 63, w = tid >> 6;
   if (lane == 0) s_wcnt[w] = __popcll(msk);
   __syncthreads();
   int before = 0, total = 0;
-  for (int ww = 0; ww < (RL * kBlock) / 64; ++ww) {
+#pragma unroll
+  for (int ww = 0; ww < kBlock / 64; ++ww) {
     if (ww < w) before += s_wcnt[ww];
     total += s_wcnt[ww];
   }
-  if (listed) s.stage[(int64_t)blockIdx.x * kBlock + before + __popcll(msk & ((1ull << lane) - 1ull))] = i;
+  if (listed) s.stage[(int64_t)blk * kRows + before + __popcll(msk & ((1ull << lane) - 1ull))] = i;
   if (tid == 0) {
-    s.bcount[blockIdx.x] = total;
-    s.bpart[blockIdx.x] = bs;
+    s.bcount[blk] = total;
+    s.bpart[blk] = bs;
   }
+}
+
+// Moved rows: their sums over one chunk of partners, every event at its proposed
+// place.  The workgroup's lanes are moved rows (up to 64; with fewer, 64 / P2
+// lanes share a row, P2 the power of two that holds them) and its waves take a
+// quarter each of every kBlock partners staged in LDS, which all lanes of a row
+// read as a broadcast: no sum crosses lanes until the end.  (One moved row at a
+// time, its partners across the lanes, took 33 us for 64 moved events at
+// N = 50,000: a workgroup reduction per six partners and lane.)
+template <int D>
+__device__ __forceinline__ void moved_rows(const Step& s, int blk) {
+  __shared__ double s_p[kBlock][D + 1];
+  __shared__ int64_t s_idx[kBlock];
+  __shared__ double s_ab[kBlock / 64][64][2];
+  __shared__ double s_exptab[kExpTab];
+  fill_exp_table(s_exptab);
+  const int groups = (s.nmove + 63) / 64;
+  const int c = blk / groups, g = blk % groups;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int in_group = min(64, s.nmove - g * 64);
+  int p2 = 1;
+  while (p2 < in_group) p2 <<= 1;
+  const int e = g * 64 + (lane & (p2 - 1)), sub = lane / p2, subs = 64 / p2;
+  const bool staged = s.nmove <= kBlock;   // the moved list fits LDS
+  if (staged && tid < s.nmove) s_idx[tid] = s.idx[tid];
+  int r = -1;
+  double xr[D], tr = 0.0;
+#pragma unroll
+  for (int q = 0; q < D; ++q) xr[q] = 0.0;
+  if (e < s.nmove) {
+    const int64_t j = s.idx[e];
+    if (j >= 0 && j < s.n) {
+      r = (int)j;
+      tr = s.t[r];
+    }
+#pragma unroll
+    for (int q = 0; q < D; ++q) xr[q] = s.xnew[(int64_t)e * D + q];
+  }
+  double a = 0.0, b = 0.0;
+  const int j_end = min(s.n, (c + 1) * s.chunk);
+  for (int j0 = c * s.chunk; j0 < j_end; j0 += kBlock) {
+    __syncthreads();
+    const int j = j0 + tid;
+    if (j < j_end) {
+      const int pos = staged ? find_moved(s_idx, s.nmove, j) : find_moved(s.idx, s.nmove, j);
+      const double* src = pos >= 0 ? s.xnew + (int64_t)pos * D : s.x + (int64_t)j * D;
+#pragma unroll
+      for (int q = 0; q < D; ++q) s_p[tid][q] = src[q];
+      s_p[tid][D] = s.t[j];
+    }
+    __syncthreads();
+    const int k_end = min(64 * w + 64, j_end - j0);
+    if (r >= 0)
+      for (int k = 64 * w + sub; k < k_end; k += subs) {
+        if (j0 + k == r) continue;
+        double pa, pb;
+        pair_ab<D>(s.m, xr, tr, s_p[k], s_p[k][D], pa, pb, s_exptab);
+        a += pa;
+        b += pb;
+      }
+  }
+  for (int o = p2; o < 64; o <<= 1) {
+    a += __shfl_xor(a, o);
+    b += __shfl_xor(b, o);
+  }
+  s_ab[w][lane][0] = a;
+  s_ab[w][lane][1] = b;
+  __syncthreads();
+  if (w == 0 && lane < in_group) {
+#pragma unroll
+    for (int ww = 1; ww < kBlock / 64; ++ww) {
+      a += s_ab[ww][lane][0];
+      b += s_ab[ww][lane][1];
+    }
+    double* mp = s.mpart + ((int64_t)c * s.nmove + e) * 2;
+    mp[0] = a * s.m.cbg_unit;
+    mp[1] = b * s.m.cse_unit;
+  }
+}
+
+// Both in one launch: neither reads what the other writes.
+template <int D, int RL>
+__global__ void __launch_bounds__(kBlock) k_mwg_rows(Step s) {
+  if ((int)blockIdx.x < s.nrb) moved_change<D, RL>(s, blockIdx.x);
+  else moved_rows<D>(s, blockIdx.x - s.nrb);
 }
 
 // Partner segments per listed row: kSeg, or more when few rows are listed so
@@ -244,87 +344,130 @@ __device__ __forceinline__ int segs_for(int cnt, int n) {
   return segs;
 }
 
-// Exact rows, split into (row, partner segment) tasks over a fixed grid: sums
-// of the row's pair terms against one segment of partners, every event at its
-// proposed place; a moved row sits at its proposed location.  The listed rows
-// in index order come from k_mwg_rows' per-block counts and staged rows: every
-// workgroup scans the counts (each thread over a chunk of consecutive blocks)
-// and finds its tasks' rows from the scan; workgroup 0 also writes the list
-// and its length, which the later kernels read.
+// Inclusive scan over the workgroup (kBlock threads): within each wave by
+// shuffles, then the totals of the earlier waves.
+__device__ __forceinline__ int block_scan(int v, int* s_wtot) {
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const int u = __shfl_up(v, off);
+    if (lane >= off) v += u;
+  }
+  if (lane == 63) s_wtot[wv] = v;
+  __syncthreads();
+  for (int w2 = 0; w2 < wv; ++w2) v += s_wtot[w2];
+  return v;
+}
+
+// The listed rows in index order come from k_mwg_rows' per-block counts and
+// staged rows: every workgroup scans the counts (each thread over a chunk of
+// consecutive blocks) and finds any row of the list from the scan.
+struct Listed {
+  int cnt, per;
+  const int* scan;   // LDS, kBlock: rows up to and including each thread's chunk
+};
+__device__ __forceinline__ Listed listed_rows(const Step& s, int* s_scan, int* s_wtot, int& own, int& lo, int& hi) {
+  Listed L;
+  const int tid = threadIdx.x;
+  L.per = (s.nrb + kBlock - 1) / kBlock;
+  lo = min(s.nrb, tid * L.per);
+  hi = min(s.nrb, lo + L.per);
+  own = 0;
+  for (int b = lo; b < hi; ++b) own += s.bcount[b];
+  s_scan[tid] = block_scan(own, s_wtot);
+  __syncthreads();
+  L.cnt = s_scan[kBlock - 1];
+  L.scan = s_scan;
+  return L;
+}
+__device__ __forceinline__ int listed_row(const Step& s, const Listed& L, int e) {
+  // the first chunk whose inclusive count exceeds e, then the block inside it
+  int c0 = 0, c1 = kBlock - 1;
+  while (c0 < c1) {
+    const int mid = (c0 + c1) >> 1;
+    if (L.scan[mid] > e) c1 = mid; else c0 = mid + 1;
+  }
+  int rr = e - (c0 > 0 ? L.scan[c0 - 1] : 0);
+  int rb = c0 * L.per;
+  for (int cb = s.bcount[rb]; rr >= cb; cb = s.bcount[rb]) { rr -= cb; ++rb; }
+  return s.stage[(int64_t)rb * s.rows + rr];
+}
+
+// One listed (unmoved) row's sums over partners [j0, j1), every event at its
+// proposed place; this thread's share.
+template <int D>
+__device__ __forceinline__ void listed_sums(const Step& s, int r, int j0, int j1, const double* tab, double (&ab)[2]) {
+  double xr[D];
+#pragma unroll
+  for (int q = 0; q < D; ++q) xr[q] = s.x[(int64_t)r * D + q];
+  const double tr = s.t[r];
+  double a = 0.0, b = 0.0;
+  for (int j = j0 + threadIdx.x; j < j1; j += kBlock) {
+    if (j == r) continue;
+    // k_mwg_rows flagged the moved rows with 2: only they search the list
+    const int pos = s.flag[j] == 2 ? find_moved(s.idx, s.nmove, j) : -1;
+    double xj[D];
+#pragma unroll
+    for (int q = 0; q < D; ++q) xj[q] = pos >= 0 ? s.xnew[(int64_t)pos * D + q] : s.x[(int64_t)j * D + q];
+    double pa, pb;
+    pair_ab<D>(s.m, xr, tr, xj, s.t[j], pa, pb, tab);
+    a += pa;
+    b += pb;
+  }
+  ab[0] = a * s.m.cbg_unit;
+  ab[1] = b * s.m.cse_unit;
+}
+
+// Three-launch steps: the listed rows, split into (row, partner segment) tasks
+// over a fixed grid, and (after them, one wave per row) the moved rows' chunk
+// sums added in a fixed order.  Workgroup 0 also writes the list and its
+// length, which the decision kernel reads.
+constexpr int kMergeRows = kBlock / 64;
 template <int D>
 __global__ void __launch_bounds__(kBlock) k_mwg_exact(Step s) {
   __shared__ double sh[2 * kBlock];
   __shared__ int s_scan[kBlock];
   __shared__ int s_wtot[kBlock / 64];
   __shared__ double s_exptab[kExpTab];   // 2^(j/kExpTab) for exp_tab (read after the scan's barriers)
-  fill_exp_table(s_exptab);
   const int tid = threadIdx.x;
-  const int per = (s.nrb + kBlock - 1) / kBlock;
-  const int lo = min(s.nrb, tid * per), hi = min(s.nrb, lo + per);
-  int own = 0;
-  for (int b = lo; b < hi; ++b) own += s.bcount[b];
-  // inclusive scan of the counts: within each wave by shuffles, then the
-  // totals of the earlier waves (two barriers instead of sixteen)
-  {
-    const int lane = tid & 63, wv = tid >> 6;
-    int incl = own;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-      const int v = __shfl_up(incl, off);
-      if (lane >= off) incl += v;
+  if ((int)blockIdx.x >= kExactGrid) {
+    const int e = ((int)blockIdx.x - kExactGrid) * kMergeRows + (tid >> 6), lane = tid & 63;
+    if (e >= s.nmove) return;
+    double a = 0.0, b = 0.0;
+    for (int c = lane; c < s.nchunk; c += 64) {
+      a += s.mpart[((int64_t)c * s.nmove + e) * 2 + 0];
+      b += s.mpart[((int64_t)c * s.nmove + e) * 2 + 1];
     }
-    if (lane == 63) s_wtot[wv] = incl;
-    __syncthreads();
-    for (int w2 = 0; w2 < wv; ++w2) incl += s_wtot[w2];
-    s_scan[tid] = incl;
-    __syncthreads();
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      a += __shfl_xor(a, o);
+      b += __shfl_xor(b, o);
+    }
+    if (lane == 0) {
+      s.mrow[(int64_t)e * 2 + 0] = a;
+      s.mrow[(int64_t)e * 2 + 1] = b;
+    }
+    return;
   }
-  const int cnt = s_scan[kBlock - 1];
+  fill_exp_table(s_exptab);
+  int own, lo, hi;
+  const Listed L = listed_rows(s, s_scan, s_wtot, own, lo, hi);
   if (blockIdx.x == 0) {
     int pos = s_scan[tid] - own;
     for (int b = lo; b < hi; ++b) {
       const int c = s.bcount[b];
-      for (int k = 0; k < c; ++k) s.list[pos++] = s.stage[(int64_t)b * kBlock + k];
+      for (int k = 0; k < c; ++k) s.list[pos++] = s.stage[(int64_t)b * s.rows + k];
     }
-    if (tid == 0) s.state[1] = cnt;
+    if (tid == 0) s.state[1] = L.cnt;
   }
-  const int segs = segs_for(cnt, s.n);
+  const int segs = segs_for(L.cnt, s.n);
   const int seg = (s.n + segs - 1) / segs;
-  for (int64_t task = blockIdx.x; task < (int64_t)cnt * segs; task += gridDim.x) {
+  for (int64_t task = blockIdx.x; task < (int64_t)L.cnt * segs; task += kExactGrid) {
     const int e = (int)(task / segs), sg = (int)(task % segs);
-    // listed row e: the first chunk whose inclusive count exceeds e, then the
-    // block inside it
-    int c0 = 0, c1 = kBlock - 1;
-    while (c0 < c1) {
-      const int mid = (c0 + c1) >> 1;
-      if (s_scan[mid] > e) c1 = mid; else c0 = mid + 1;
-    }
-    int rr = e - (c0 > 0 ? s_scan[c0 - 1] : 0);
-    int rb = c0 * per;
-    for (int cb = s.bcount[rb]; rr >= cb; cb = s.bcount[rb]) { rr -= cb; ++rb; }
-    const int r = s.stage[(int64_t)rb * kBlock + rr];
-    const int rpos = s.flag[r] == 2 ? find_moved(s.idx, s.nmove, r) : -1;
-    double xr[D];
-#pragma unroll
-    for (int q = 0; q < D; ++q) xr[q] = rpos >= 0 ? s.xnew[(int64_t)rpos * D + q] : s.x[(int64_t)r * D + q];
-    const double tr = s.t[r];
-    const int j0 = sg * seg, j1 = min(s.n, j0 + seg);
-    double a = 0.0, b = 0.0;
-    for (int j = j0 + threadIdx.x; j < j1; j += kBlock) {
-      if (j == r) continue;
-      // k_mwg_rows flagged the moved rows with 2: only they search the list
-      const int pos = s.flag[j] == 2 ? find_moved(s.idx, s.nmove, j) : -1;
-      double xj[D];
-#pragma unroll
-      for (int q = 0; q < D; ++q) xj[q] = pos >= 0 ? s.xnew[(int64_t)pos * D + q] : s.x[(int64_t)j * D + q];
-      double pa, pb;
-      pair_ab<D>(s.m, xr, tr, xj, s.t[j], pa, pb, s_exptab);
-      a += pa;
-      b += pb;
-    }
-    double ab[2] = {a, b};
+    double ab[2];
+    listed_sums<D>(s, listed_row(s, L, e), sg * seg, min(s.n, sg * seg + seg), s_exptab, ab);
     block_sum_n(ab, sh);
-    if (threadIdx.x == 0) {
+    if (tid == 0) {
       s.part[((int64_t)e * segs + sg) * 2 + 0] = ab[0];
       s.part[((int64_t)e * segs + sg) * 2 + 1] = ab[1];
     }
@@ -332,17 +475,18 @@ __global__ void __launch_bounds__(kBlock) k_mwg_exact(Step s) {
 }
 
 // Decision and update in one launch.  Every workgroup checks the moved block,
-// merges the listed rows' segments and sums the log-rate changes in the same
-// fixed order, so all of them reach the same total and the same decision;
-// each then updates its own rows on accept, and workgroup 0 reports.  The
-// listed rows' old log-rates come from k_mwg_rows' copy (a workgroup updating
-// its rows' cached terms must not change what another one reads).  (A
-// device-wide fence in every workgroup of the exact kernel, to decide in its
-// last workgroup instead, would write back the L2 of each die, which costs
-// more than a launch.)
-template <int D>
+// takes the moved and the listed rows' sums and adds the log-rate changes in
+// the same fixed order, so all of them reach the same total and the same
+// decision; each then updates its own rows on accept, and workgroup 0 reports.
+// The moved and listed rows' old log-rates come from k_mwg_rows' copy (a
+// workgroup updating its rows' cached terms must not change what another one
+// reads).  FEW: two-launch steps, which merge the moved rows' chunk sums and
+// recompute the listed rows here.  (A device-wide fence in every workgroup of
+// the exact kernel, to decide in its last workgroup instead, would write back
+// the L2 of each die, which costs more than a launch.)
+template <int D, bool FEW>
 __global__ void __launch_bounds__(kBlock) k_mwg_settle(Step s) {
-  __shared__ double sh[kBlock];
+  __shared__ double sh[2 * kBlock];
   __shared__ double s_na[kBlock], s_nb[kBlock], s_dl[kBlock];
   __shared__ int s_own[kBlock];
   __shared__ int s_bad;
@@ -351,42 +495,82 @@ __global__ void __launch_bounds__(kBlock) k_mwg_settle(Step s) {
   s_own[tid] = 0;
   if (tid == 0) s_bad = 0;
   __syncthreads();
-  for (int k = tid; k < s.nmove; k += kBlock) {
-    const int64_t j = s.idx[k];
-    bool bad = j < 0 || j >= s.n || (k > 0 && s.idx[k - 1] >= j);
-#pragma unroll
-    for (int q = 0; q < D; ++q) bad = bad || !isfinite(s.xnew[(int64_t)k * D + q]);
-    if (bad) atomicOr(&s_bad, 1);
-  }
-  const int cnt = s.state[1];
-  const int segs = segs_for(cnt, s.n);
-  // G lanes per listed row (segs / 4, at most a wave): they add strided
-  // segments, a butterfly within the group combines them (the same fixed
-  // order every time), and the group's first lane keeps the row's log-rate
-  // change in its running sum.  Many listed rows (G small) run side by side.
-  const int G = min(64, segs / 4);
-  const int grp = tid / G, gl = tid % G;
-  double acc = 0.0;
-  for (int e = grp; e < cnt; e += kBlock / G) {
+  double acc = 0.0;   // this thread's part of the sum of log-rate changes
+  auto settle_row = [&](int r, double a, double b) {
+    const double dl = log(s.m.mu0 * a + s.m.theta * b) - s.dlog[r];
+    acc += dl;
+    if (r >= base && r < base + kBlock) {
+      s_na[r - base] = a;
+      s_nb[r - base] = b;
+      s_dl[r - base] = dl;
+      s_own[r - base] = 1;
+    }
+  };
+  // the moved rows: LM lanes per row add strided chunk sums (FEW), a butterfly
+  // combines them
+  constexpr int LM = FEW ? 16 : 1;
+  for (int k0 = 0; k0 < s.nmove; k0 += kBlock / LM) {
+    const int k = k0 + tid / LM, gl = tid % LM;
+    const bool in = k < s.nmove;
     double a = 0.0, b = 0.0;
-    for (int sg = gl; sg < segs; sg += G) {
-      a += s.part[((int64_t)e * segs + sg) * 2 + 0];
-      b += s.part[((int64_t)e * segs + sg) * 2 + 1];
-    }
-    for (int o = G / 2; o > 0; o >>= 1) {
-      a += __shfl_xor(a, o);
-      b += __shfl_xor(b, o);
-    }
-    if (gl == 0) {
-      const int r = s.list[e];
-      const double dl = log(s.m.mu0 * a + s.m.theta * b) - s.dlog[r];
-      acc += dl;
-      if (r >= base && r < base + kBlock) {
-        s_na[r - base] = a;
-        s_nb[r - base] = b;
-        s_dl[r - base] = dl;
-        s_own[r - base] = 1;
+    if (FEW) {
+      for (int c = gl; in && c < s.nchunk; c += LM) {
+        a += s.mpart[((int64_t)c * s.nmove + k) * 2 + 0];
+        b += s.mpart[((int64_t)c * s.nmove + k) * 2 + 1];
       }
+      for (int o = LM / 2; o > 0; o >>= 1) {
+        a += __shfl_xor(a, o);
+        b += __shfl_xor(b, o);
+      }
+    } else if (in) {
+      a = s.mrow[(int64_t)k * 2 + 0];
+      b = s.mrow[(int64_t)k * 2 + 1];
+    }
+    if (in && gl == 0) {
+      const int64_t j = s.idx[k];
+      bool bad = j < 0 || j >= s.n || (k > 0 && s.idx[k - 1] >= j);
+#pragma unroll
+      for (int q = 0; q < D; ++q) bad = bad || !isfinite(s.xnew[(int64_t)k * D + q]);
+      if (bad) atomicOr(&s_bad, 1);
+      else settle_row((int)j, a, b);
+    }
+  }
+  if constexpr (FEW) {
+    __shared__ int s_scan[kBlock];
+    __shared__ int s_wtot[kBlock / 64];
+    __shared__ double s_exptab[kExpTab];
+    int own, lo, hi;
+    const Listed L = listed_rows(s, s_scan, s_wtot, own, lo, hi);
+    if (L.cnt > 0) {
+      fill_exp_table(s_exptab);
+      __syncthreads();
+      for (int e = 0; e < L.cnt; ++e) {
+        const int r = listed_row(s, L, e);
+        double ab[2];
+        listed_sums<D>(s, r, 0, s.n, s_exptab, ab);
+        block_sum_n(ab, sh);
+        if (tid == 0) settle_row(r, ab[0], ab[1]);
+      }
+    }
+  } else {
+    const int cnt = s.state[1];
+    const int segs = segs_for(cnt, s.n);
+    // G lanes per listed row (segs / 4, at most a wave): they add strided
+    // segments, a butterfly within the group combines them (the same fixed
+    // order every time).  Many listed rows (G small) run side by side.
+    const int G = min(64, segs / 4);
+    const int grp = tid / G, gl = tid % G;
+    for (int e = grp; e < cnt; e += kBlock / G) {
+      double a = 0.0, b = 0.0;
+      for (int sg = gl; sg < segs; sg += G) {
+        a += s.part[((int64_t)e * segs + sg) * 2 + 0];
+        b += s.part[((int64_t)e * segs + sg) * 2 + 1];
+      }
+      for (int o = G / 2; o > 0; o >>= 1) {
+        a += __shfl_xor(a, o);
+        b += __shfl_xor(b, o);
+      }
+      if (gl == 0) settle_row(s.list[e], a, b);
     }
   }
   for (int b = tid; b < s.nrb; b += kBlock) acc += s.bpart[b];
@@ -462,10 +646,10 @@ static size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
 
 // Workspace pieces for n events, in order.
 struct Pieces {
-  size_t new_a, new_b, dlog, flag, bpart, bcount, stage, list, part, state, total;
+  size_t new_a, new_b, dlog, flag, bpart, bcount, stage, list, part, mpart, mrow, state, total;
 };
 static Pieces pieces(int64_t n) {
-  const size_t nrb = (size_t)((n + kBlock - 1) / kBlock);
+  const size_t nrb = (size_t)((n + kBlock / kRowLanesMany - 1) / (kBlock / kRowLanesMany));
   Pieces p;
   size_t o = 0;
   auto take = [&](size_t bytes) { const size_t at = o; o = align256(o + bytes); return at; };
@@ -475,9 +659,11 @@ static Pieces pieces(int64_t n) {
   p.flag = take(sizeof(int) * (size_t)n);
   p.bpart = take(sizeof(double) * nrb);
   p.bcount = take(sizeof(int) * nrb);
-  p.stage = take(sizeof(int) * nrb * kBlock);
+  p.stage = take(sizeof(int) * (size_t)(n + kBlock));
   p.list = take(sizeof(int) * (size_t)n);
   p.part = take(sizeof(double) * 2 * kSeg * (size_t)n);
+  p.mpart = take(sizeof(double) * 2 * kSeg * (size_t)n);
+  p.mrow = take(sizeof(double) * 2 * (size_t)n);
   p.state = take(sizeof(int) * 16);
   p.total = o;
   return p;
@@ -485,12 +671,16 @@ static Pieces pieces(int64_t n) {
 
 template <int D>
 static void launch(const Step& s, hipStream_t st) {
-  if (s.nmove >= kManyMoved)
-    k_mwg_rows<D, kRowLanesMany><<<s.nrb, kRowLanesMany * kBlock, 0, st>>>(s);
-  else
-    k_mwg_rows<D, 1><<<s.nrb, kBlock, 0, st>>>(s);
-  k_mwg_exact<D><<<kExactGrid, kBlock, 0, st>>>(s);
-  k_mwg_settle<D><<<s.nrb, kBlock, 0, st>>>(s);
+  const int grid = s.nrb + s.nchunk * ((s.nmove + 63) / 64);
+  const int nset = (s.n + kBlock - 1) / kBlock;
+  if (s.nmove >= kManyMoved) k_mwg_rows<D, kRowLanesMany><<<grid, kBlock, 0, st>>>(s);
+  else k_mwg_rows<D, 1><<<grid, kBlock, 0, st>>>(s);
+  if (s.n <= kFewEvents && s.nmove < kManyMoved) {
+    k_mwg_settle<D, true><<<nset, kBlock, 0, st>>>(s);
+  } else {
+    k_mwg_exact<D><<<kExactGrid + (s.nmove + kMergeRows - 1) / kMergeRows, kBlock, 0, st>>>(s);
+    k_mwg_settle<D, false><<<nset, kBlock, 0, st>>>(s);
+  }
 }
 
 }  // namespace mwg
@@ -520,7 +710,13 @@ int hawkes_mwg_step(double* x, const double* t, int64_t n, int d, const hawkes_p
   s.t = t;
   s.n = (int)n;
   s.nmove = (int)nmove;
-  s.nrb = (int)((n + kBlock - 1) / kBlock);
+  s.rows = kBlock / (nmove >= kManyMoved ? kRowLanesMany : 1);
+  s.nrb = (int)((n + s.rows - 1) / s.rows);
+  // kBlock partners per chunk, or as many more as keep the chunk sums of all
+  // moved rows within the workspace (n x kSeg)
+  const int64_t most = std::max<int64_t>(1, (int64_t)kSeg * n / nmove);
+  s.chunk = kBlock * (int)((n + kBlock * most - 1) / (kBlock * most));
+  s.nchunk = (int)((n + s.chunk - 1) / s.chunk);
   s.terms = terms;
   s.idx = idx;
   s.xnew = x_new;
@@ -535,6 +731,8 @@ int hawkes_mwg_step(double* x, const double* t, int64_t n, int d, const hawkes_p
   s.stage = reinterpret_cast<int*>(w + pc.stage);
   s.list = reinterpret_cast<int*>(w + pc.list);
   s.part = reinterpret_cast<double*>(w + pc.part);
+  s.mpart = reinterpret_cast<double*>(w + pc.mpart);
+  s.mrow = reinterpret_cast<double*>(w + pc.mrow);
   s.state = reinterpret_cast<int*>(w + pc.state);
   hipStream_t st = static_cast<hipStream_t>(stream);
   (void)hipGetLastError();

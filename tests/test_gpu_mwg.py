@@ -274,3 +274,31 @@ def test_mwg_large_blocks_match_oracle(n, block):
     assert out.cpu().numpy()[1] == 1
     assert np.array_equal(xd.cpu().numpy(), x1)
     _check_terms(terms.cpu().numpy(), oracle.event_terms(x1, w.t, w.params), "fp64", w.params, "large block")
+
+
+@pytest.mark.parametrize("n,d,nmove", [(300, 2, 7), (300, 3, 8), (8192, 1, 7), (8193, 1, 7), (700, 6, 63), (700, 6, 65),
+                                       (900, 2, 256), (900, 2, 257), (2600, 2, 2600)])
+def test_mwg_block_sizes(n, d, nmove):
+    """Two-launch and three-launch steps, one and several groups of 64 moved
+    rows, the moved list in LDS and in device memory, partner chunks of several
+    LDS batches (every event moved): Delta ell and the terms afterwards."""
+    import torch
+    from paper_2010_02994_amd import api
+    w = W.random_case(95, n, d, ties=4, t_span=n / 50)
+    rng = np.random.default_rng(95)
+    idx = np.sort(rng.choice(n, size=nmove, replace=False)).astype(np.int64)
+    x_new = w.x[idx] + 0.3 * rng.standard_normal((nmove, d))
+    xd, td, terms = _state(w)
+    say(f"case mwg block sizes n={n} d={d} nmove={nmove}")
+    out = api.mwg_step(xd, td, w.params, terms, _dev(idx), _dev(x_new), _dev(np.array([-np.inf])))
+    x1 = w.x.copy()
+    x1[idx] = x_new
+    _, ll0, _, _ = oracle.loglik_grad(w.x, w.t, w.params, threads=True, want_grad_x=False)
+    _, ll1, _, _ = oracle.loglik_grad(x1, w.t, w.params, threads=True, want_grad_x=False)
+    torch.cuda.synchronize()
+    got = out.cpu().numpy()
+    assert got[1] == 1.0 and got[2] == 0.0
+    # the two log-likelihoods round to ~1e-13 of their size each
+    assert abs(got[0] - (ll1 - ll0)) <= 1e-10 * max(abs(ll0), abs(ll1))
+    assert np.array_equal(xd.cpu().numpy(), x1)
+    _check_terms(terms.cpu().numpy(), oracle.event_terms(x1, w.t, w.params), "fp64", w.params, f"nmove{nmove}")
