@@ -13,8 +13,9 @@
 // Tiles: row band I (rows [64 I, 64 I + 64)) meets column chunks
 // J = 0 .. floor(I / 4) of 256 columns.  The lanes of a wave read consecutive
 // delta entries of a row (coalesced row segments), column sums stay in the
-// lanes, and a row's sum is formed over each 16-lane row of the wave by DPP row
-// shifts, the partials being added in a fixed order.  Two schedules:
+// lanes, and a row's sum is formed over the wave by matrix instructions (float64
+// tiles) or over each 16-lane row of it by DPP row shifts (strips), the partials
+// being added in a fixed order.  Two schedules:
 //  - few tiles (under 4,096): a workgroup of four waves per tile, one column
 //    per lane, rows loaded eight at a time;
 //  - many tiles: vertical strips, one wave per chunk and segment of bands,
@@ -74,24 +75,91 @@ struct Args {
   int accumulate; // 1: grad_x += the gradient (0: grad_x = the gradient)
 };
 
-// DPP reads of a lane in the same row of 16 (row shifts); lanes without a
-// source read 0.
-template <int CTRL, int ROWS>
-__device__ __forceinline__ float dpp_f(float v) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, ROWS, 0xf, true));
+// Row sums: a row's gradient sum adds D values over the wave's lanes.
+//
+// Strips, by DPP: row shifts 1, 2, 4, 8 (each 16 lanes' total in their lane 15, four
+// partials a row), one step at a time across the D values so no DPP read waits on the
+// add just before it.
+template <int CTRL>
+__device__ __forceinline__ float dpp_shr(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
 }
-template <int CTRL, int ROWS>
-__device__ __forceinline__ double dpp_d(double v) {
+template <int CTRL>
+__device__ __forceinline__ double dpp_shr(double v) {
   const unsigned long long u = (unsigned long long)__double_as_longlong(v);
-  const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(u & 0xffffffffull), CTRL, ROWS, 0xf, true);
-  const int hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(u >> 32), CTRL, ROWS, 0xf, true);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(u & 0xffffffffull), CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(u >> 32), CTRL, 0xf, 0xf, true);
   return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
 }
-template <int CTRL, int ROWS, typename R>
-__device__ __forceinline__ R dpp_step(R v) {
-  if constexpr (std::is_same<R, float>::value) return dpp_f<CTRL, ROWS>(v);
-  else return dpp_d<CTRL, ROWS>(v);
+template <int D, typename R>
+__device__ __forceinline__ void row_sum_dpp(R (&g)[D], R (*s_row)[4][D], int r) {
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int q = 0; q < D; ++q) g[q] += dpp_shr<0x111>(g[q]);
+#pragma unroll
+  for (int q = 0; q < D; ++q) g[q] += dpp_shr<0x112>(g[q]);
+#pragma unroll
+  for (int q = 0; q < D; ++q) g[q] += dpp_shr<0x114>(g[q]);
+#pragma unroll
+  for (int q = 0; q < D; ++q) g[q] += dpp_shr<0x118>(g[q]);
+  if ((lane & 15) == 15)
+#pragma unroll
+    for (int q = 0; q < D; ++q) s_row[r][lane >> 4][q] = g[q];
 }
+
+// Float64 tiles, on the matrix cores.  A wave that holds one column per lane has one
+// pair per lane and row, and its row sums by DPP (two moves and an add a step) were
+// more than half as many vector instructions as the pairs.  Instead each value is the
+// A operand of a 4x4x4 matrix instruction (four blocks) whose B operand is one-hot in
+// the row's place among kGroup rows: it adds the values of four lanes (16 apart) to
+// that row's column of an accumulator, exactly, and zero to the others, beside the
+// vector units.  Every kGroup rows two DPP steps add the blocks.
+//   A lane l = (i = l % 4, block = l / 4 % 4, k = l / 16);
+//   D lane l = (j = l % 4, block, i = l / 16).
+// A value that is not finite times zero would reach the group's other rows.  It also
+// stays in its column's sum, so a wave whose column sums are not all finite does its
+// tile again with rows kept apart: multiplied by ones and selected.
+//
+// Measured, with the kernel's launch bounds: N = 4,733, D = 6 115 -> 81 us a call,
+// N = 8,000, D = 6 322 -> 248 (201 with the near tail's fits below).  The 16x16x4 form
+// takes four times the cycles for the same sums; a test of each row's values instead of
+// the column sums cost 8 of those 34 us.  In the strips, whose lanes hold several
+// columns, the accumulators cost a wave per SIMD: N = 20,000, D = 6, float64 pairs
+// 1,403 -> 1,862 us, float32 pairs 438 -> 486.
+template <int D>
+struct MfmaRowSums {
+  static constexpr int kGroup = 4;   // rows between stores
+  double acc[D] = {};
+  __device__ __forceinline__ void add(double (&g)[D], double (*s_row)[D], int r, bool apart) {
+    const int lane = threadIdx.x & 63;
+    const bool mine = (lane & 3) == (r & 3);
+    if (!apart) {
+      const double hot = mine ? 1.0 : 0.0;
+#pragma unroll
+      for (int q = 0; q < D; ++q) acc[q] = __builtin_amdgcn_mfma_f64_4x4x4f64(g[q], hot, acc[q], 0, 0, 0);
+    } else {
+#pragma unroll
+      for (int q = 0; q < D; ++q) {
+        const double t = __builtin_amdgcn_mfma_f64_4x4x4f64(g[q], 1.0, 0.0, 0, 0, 0);
+        if (mine) acc[q] = t;
+      }
+    }
+    if (r % kGroup != kGroup - 1) return;
+    // over the lanes 16 apart (the accumulator read as a B operand of the same lane
+    // layout, k = i, times ones), then over the blocks: lanes 12 to 15 hold the sums
+#pragma unroll
+    for (int q = 0; q < D; ++q) acc[q] = __builtin_amdgcn_mfma_f64_4x4x4f64(1.0, acc[q], 0.0, 0, 0, 0);
+#pragma unroll
+    for (int q = 0; q < D; ++q) acc[q] += dpp_shr<0x114>(acc[q]);
+#pragma unroll
+    for (int q = 0; q < D; ++q) acc[q] += dpp_shr<0x118>(acc[q]);
+    if ((lane >> 2) == 3)
+#pragma unroll
+      for (int q = 0; q < D; ++q) s_row[r - (kGroup - 1) + (lane & 3)][q] = acc[q];
+#pragma unroll
+    for (int q = 0; q < D; ++q) acc[q] = 0.0;
+  }
+};
 
 // erfc(w) for w >= 0 in float32: the Chebyshev-fitted form
 // t exp(-w^2 + P(t)), t = 1/(1 + w/2), of Press et al., Numerical Recipes
@@ -160,12 +228,93 @@ __device__ __forceinline__ double rsqrt_f64(double r2) {
   return r2 > 0.0 ? 1.0 / sqrt(r2) : 0.0;
 }
 
+// 1/v in float64 for a normal v well inside the range: the hardware reciprocal
+// refined by two Newton-Raphson steps.
+__device__ __forceinline__ double rcp_f64(double v) {
+  double y = __builtin_amdgcn_rcp(v);
+  y = __builtin_fma(y, __builtin_fma(-v, y, 1.0), y);
+  return __builtin_fma(y, __builtin_fma(-v, y, 1.0), y);
+}
+
+// n/d for a normal d: one refinement of the reciprocal, one of the quotient.
+__device__ __forceinline__ double div_f64(double n, double d) {
+  double y = __builtin_amdgcn_rcp(d);
+  y = __builtin_fma(y, __builtin_fma(-d, y, 1.0), y);
+  const double v = n * y;
+  return __builtin_fma(__builtin_fma(-d, v, n), y, v);
+}
+
+// A constant that is put into scalar registers where it is used: left to itself the
+// compiler keeps the fits' constants in vector registers across the row loop.
+__device__ __forceinline__ double in_place(double v) {
+  asm volatile("" : "+s"(v));
+  return v;
+}
+
+// log Phi(z) and phi(z)/(sigma Phi(z)) of a float64 pair whose tail is not small, from
+// z, e = exp(-z^2/2) and pdf_s = phi(z)/sigma.  With the Mills ratio M(z) = q(z)/phi(z),
+// (z + 3) M(z) is smooth in u = z/(z + 3): a polynomial of degree 20 (its coefficients
+// over sqrt(2 pi), so that e times it over z + 3 is q) that interpolates the exact
+// function (50-digit values) in the Chebyshev nodes of z in [0, 7]; being in u, its small
+// terms and their roundings vanish with z.  (A wave's lanes beyond 7 reach it beside
+// nearer ones: off by 4e-13 at z = 9, where q is 1e-19.)  log(1 - q) = -2 atanh(s),
+// s = q/(2 - q), by a polynomial in s^2 of degree 10 fitted the same way (s <= 1/3; 1e-16).
+//
+// Against 40-digit values over z in [0.02, 4]: log Phi 2.4e-16 relative, rms (8.5e-16
+// with the library's erfc and log1p, since the rounding of erfc's argument z/sqrt 2
+// grows by z^2), phi/Phi 1.5e-16 absolute, rms (1.5e-16).  The library's functions took
+// several times the instructions and 60 to 70 more registers, a wave or two per SIMD.
+// Measured with this form and the wider launch bounds it allows: N = 20,000, D = 2,
+// where most waves hold a near pair, 2,066 -> 941 us a call; D = 6 1,390 -> 1,083;
+// N = 11,000, D = 3 700 -> 324.
+__device__ __forceinline__ void near_tail(double z, double e, double pdf_s, double& lphi, double& rho_s) {
+  const double d = z + 3.0, r = rcp_f64(d), u = z * r;
+  double p = in_place(-0.010904292822729063);
+  p = __builtin_fma(p, u, in_place(0.061637281884370176));
+  p = __builtin_fma(p, u, in_place(-0.15435331051904394));
+  p = __builtin_fma(p, u, in_place(0.2345076322663165));
+  p = __builtin_fma(p, u, in_place(-0.24966511846030615));
+  p = __builtin_fma(p, u, in_place(0.19385982851905348));
+  p = __builtin_fma(p, u, in_place(-0.11110767054411723));
+  p = __builtin_fma(p, u, in_place(0.055289565653312264));
+  p = __builtin_fma(p, u, in_place(-0.016822569077253376));
+  p = __builtin_fma(p, u, in_place(-0.0009458103503858226));
+  p = __builtin_fma(p, u, in_place(-0.015614625827786695));
+  p = __builtin_fma(p, u, in_place(-0.011181711029268428));
+  p = __builtin_fma(p, u, in_place(0.017453950679225196));
+  p = __builtin_fma(p, u, in_place(0.058748817072442866));
+  p = __builtin_fma(p, u, in_place(0.04046632499959328));
+  p = __builtin_fma(p, u, in_place(-0.11791314663852558));
+  p = __builtin_fma(p, u, in_place(-0.26018837803937195));
+  p = __builtin_fma(p, u, in_place(0.20711685832709964));
+  p = __builtin_fma(p, u, in_place(1.0690389527741675));
+  p = __builtin_fma(p, u, in_place(-2.090480523612894));
+  p = __builtin_fma(p, u, in_place(1.5));
+  p *= e;
+  double q = p * r;
+  q = __builtin_fma(__builtin_fma(-d, q, p), r, q);
+  rho_s = div_f64(pdf_s, 1.0 - q);
+  const double s = div_f64(q, 2.0 - q), s2 = s * s;
+  double a = in_place(0.17056574502947028);
+  a = __builtin_fma(a, s2, in_place(0.08317620940429153));
+  a = __builtin_fma(a, s2, in_place(0.12111792015820001));
+  a = __builtin_fma(a, s2, in_place(0.13300162200565394));
+  a = __builtin_fma(a, s2, in_place(0.15386630743249172));
+  a = __builtin_fma(a, s2, in_place(0.18181740017812253));
+  a = __builtin_fma(a, s2, in_place(0.22222224104933036));
+  a = __builtin_fma(a, s2, in_place(0.2857142854504191));
+  a = __builtin_fma(a, s2, in_place(0.4000000000018931));
+  a = __builtin_fma(a, s2, in_place(0.6666666666666614));
+  lphi = -__builtin_fma(s * s2, a, 2.0 * s);
+}
+
 // log Phi(z) and rho/sigma = phi(z)/(sigma Phi(z)) of one observed pair at
 // distance dist = r2 rs (rs = 1/dist, 0 for a coincident pair); z = dist/sigma.
 // The upper tail is formed directly, so log Phi keeps small tails.  Beyond
 // z = 3 (float32) or z = 4 (float64) on every lane of the wave (the usual
 // case for well separated points) the tail comes from the Mills-ratio
-// polynomial and no erfc, log or reciprocal is evaluated; otherwise from erfc.
+// polynomial and no erfc, log or reciprocal is evaluated; otherwise from erfc
+// (float32) or near_tail (float64).
 template <typename R>
 __device__ __forceinline__ void pair_phi(R r2, R dist, R rs, const Args& a, const double* __restrict__ tab, R& lphi,
                                          R& rho_s) {
@@ -184,7 +333,8 @@ __device__ __forceinline__ void pair_phi(R r2, R dist, R rs, const Args& a, cons
       rho_s = pdf_s * __builtin_amdgcn_rcpf(phi);
     }
   } else {
-    const double pdf_s = a.pdf_k64 * exp_tab(a.pdf_c64 * r2, tab);
+    const double e = exp_tab(a.pdf_c64 * r2, tab);   // exp(-z^2/2)
+    const double pdf_s = a.pdf_k64 * e;
     if (__all(r2 > a.r2_mid)) {
       const double iz = a.sigma * rs;
       const double q = pdf_s * mills_s64(iz * iz) * (a.sigma * iz);
@@ -192,9 +342,7 @@ __device__ __forceinline__ void pair_phi(R r2, R dist, R rs, const Args& a, cons
       lphi = q * __builtin_fma(q, __builtin_fma(q, -1.0 / 3.0, -0.5), -1.0);
       rho_s = __builtin_fma(pdf_s * q, __builtin_fma(q, __builtin_fma(q, 1.0, 1.0), 1.0), pdf_s);
     } else {
-      const double q = 0.5 * erfc(dist * a.inv_sigma * 0.70710678118654752440);
-      lphi = log1p(-q);
-      rho_s = pdf_s / (1.0 - q);
+      near_tail(dist * a.inv_sigma, e, pdf_s, lphi, rho_s);
     }
   }
 }
@@ -207,19 +355,18 @@ struct TileShape {
   static constexpr int kLanes = kTC / C;   // workgroup size
   static constexpr int kWavesT = kLanes / 64;
   static constexpr int kPre = kPrefetch;   // rows loaded ahead
-  // partial row sums per wave: one column per lane reduces over the whole
-  // wave (row broadcasts 15 and 31 after the row shifts); wider lanes stop at
-  // the four 16-lane rows
-  static constexpr int kParts = C == 1 ? 1 : 4;
 };
 
+// (Waves per SIMD: as many as the registers allow without spills.)
 template <int D, bool MIX, int C>
-__global__ void __launch_bounds__(TileShape<C>::kLanes) k_bmds_tiles(Args a) {
+__global__ void __launch_bounds__(TileShape<C>::kLanes, D <= 4 ? 4 : 3) k_bmds_tiles(Args a) {
   using R = typename std::conditional<MIX, float, double>::type;
   using TS = TileShape<C>;
-  constexpr int NL = TS::kLanes, NW = TS::kWavesT, PRE = TS::kPre, NP = TS::kParts;
+  constexpr int NL = TS::kLanes, NW = TS::kWavesT, PRE = TS::kPre;
+  using Sums = MfmaRowSums<D>;
+  static_assert(PRE % Sums::kGroup == 0, "row groups end with the prefetched rows");
   __shared__ R s_x[kTR][D];
-  __shared__ R s_row[NW][kTR][NP][D];   // partial row sums
+  __shared__ R s_row[NW][kTR][D];   // the waves' row sums
   __shared__ double sh[4 * NL];
   __shared__ double s_exptab[MIX ? 1 : kExpTab];   // float64 pairs: 2^(j/kExpTab) for exp_tab
   if constexpr (!MIX) fill_exp_table(s_exptab);
@@ -252,22 +399,29 @@ __global__ void __launch_bounds__(TileShape<C>::kLanes) k_bmds_tiles(Args a) {
     s_x[r][q] = (R)xv;
   }
   R xj[C][D], g[C][D];
+  const int bad_x = bad;
   // sums over this lane's pairs of (delta - d)^2, log Phi(z) and rho d/sigma:
   // float32 micro-partials over the pairs of each group of prefetched rows
   // (at most PRE x C terms), folded into float64
-  double a_res2 = 0.0, a_lphi = 0.0, a_rz = 0.0;
-  int miss = 0;
+  double a_res2, a_lphi, a_rz;
+  int miss;
 #pragma unroll
-  for (int c = 0; c < C; ++c) {
+  for (int c = 0; c < C; ++c)
 #pragma unroll
-    for (int q = 0; q < D; ++q) {
-      xj[c][q] = jc[c] < a.n ? (R)a.x[(int64_t)jc[c] * D + q] : R(0);
-      g[c][q] = R(0);
-    }
-  }
+    for (int q = 0; q < D; ++q) xj[c][q] = jc[c] < a.n ? (R)a.x[(int64_t)jc[c] * D + q] : R(0);
   const R inv_s2 = (R)a.inv_s2;
   __syncthreads();
   const int rows = min(kTR, a.n - i0);
+  Sums sums;
+  bool apart = false;   // rows of a group kept apart
+again:
+  a_res2 = a_lphi = a_rz = 0.0;
+  miss = 0;
+  bad = bad_x;
+#pragma unroll
+  for (int c = 0; c < C; ++c)
+#pragma unroll
+    for (int q = 0; q < D; ++q) g[c][q] = R(0);
   for (int r0 = 0; r0 < rows; r0 += PRE) {
     // the next rows' entries first, so PRE x C loads are in flight at once;
     // every load is issued (its address clamped into the matrix) and the
@@ -283,15 +437,14 @@ __global__ void __launch_bounds__(TileShape<C>::kLanes) k_bmds_tiles(Args a) {
     R m_res2 = R(0), m_lphi = R(0), m_rz = R(0);
 #pragma unroll
     for (int u = 0; u < PRE; ++u) {
-      const int r = r0 + u;
-      if (r >= rows) break;
+      const int r = r0 + u;   // rows past the last add nothing (no column is below them)
       R xi[D], gi[D];
 #pragma unroll
       for (int q = 0; q < D; ++q) { xi[q] = s_x[r][q]; gi[q] = R(0); }
 #pragma unroll
       for (int c = 0; c < C; ++c) {
         const double dv = v[u][c];
-        if (jc[c] < i0 + r) {
+        if (jc[c] < i0 + r && r < rows) {
           if (isnan(dv)) {
             miss += 1;
           } else if (dv < 0.0 || isinf(dv)) {
@@ -326,46 +479,27 @@ __global__ void __launch_bounds__(TileShape<C>::kLanes) k_bmds_tiles(Args a) {
           }
         }
       }
-      // 16-lane row sums (row shifts 1, 2, 4, 8 leave each row's total in
-      // its lane 15), one step at a time across the D values so no DPP read
-      // waits on the add just before it
-#pragma unroll
-      for (int q = 0; q < D; ++q) gi[q] += dpp_step<0x111, 0xf>(gi[q]);
-#pragma unroll
-      for (int q = 0; q < D; ++q) gi[q] += dpp_step<0x112, 0xf>(gi[q]);
-#pragma unroll
-      for (int q = 0; q < D; ++q) gi[q] += dpp_step<0x114, 0xf>(gi[q]);
-#pragma unroll
-      for (int q = 0; q < D; ++q) gi[q] += dpp_step<0x118, 0xf>(gi[q]);
-      if constexpr (NP == 1) {
-        // lane 63 gains lane 47 (row 2's total), then lane 31 (by then rows
-        // 0 and 1's total); rows 0 and 1 may pick up other values, which no
-        // one reads
-#pragma unroll
-        for (int q = 0; q < D; ++q) gi[q] += dpp_step<0x142, 0xf>(gi[q]);   // row_bcast:15
-#pragma unroll
-        for (int q = 0; q < D; ++q) gi[q] += dpp_step<0x143, 0xf>(gi[q]);   // row_bcast:31
-        if (lane == 63)
-#pragma unroll
-          for (int q = 0; q < D; ++q) s_row[w][r][0][q] = gi[q];
-      } else {
-        if ((lane & 15) == 15)
-#pragma unroll
-          for (int q = 0; q < D; ++q) s_row[w][r][lane >> 4][q] = gi[q];
-      }
+      sums.add(gi, s_row[w], r, apart);
     }
     a_res2 += (double)m_res2;
     a_lphi += (double)m_lphi;
     a_rz += (double)m_rz;
+  }
+  bool finite = true;
+#pragma unroll
+  for (int c = 0; c < C; ++c)
+#pragma unroll
+    for (int q = 0; q < D; ++q) finite = finite && fabs((double)g[c][q]) < HUGE_VAL;
+  if (!apart && !__all(finite)) {
+    apart = true;
+    goto again;
   }
   __syncthreads();
   for (int e = threadIdx.x; e < rows * D; e += NL) {
     const int r = e / D, q = e % D;
     double sum = 0.0;
 #pragma unroll
-    for (int ww = 0; ww < NW; ++ww)
-#pragma unroll
-      for (int k = 0; k < NP; ++k) sum += (double)s_row[ww][r][k][q];
+    for (int ww = 0; ww < NW; ++ww) sum += (double)s_row[ww][r][q];
     static_cast<double*>(a.prow)[(tile * kTR + r) * D + q] = sum;
   }
 #pragma unroll
@@ -538,7 +672,7 @@ __device__ __forceinline__ void strip_band(const Args& a, const double* __restri
                                            double (&v)[P][C], R (&g)[C][D], R (&s_row)[NW][kTR][4][D],
                                            double& a_res2, double& a_lphi, double& a_rz, int& miss, int& bad) {
   const int n = a.n;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int w = threadIdx.x >> 6;
   for (int r = 0; r < nr; r += P) {
     // float32 micro-partials over the ring's P x C pairs, folded into float64
     R m_res2 = R(0), m_lphi = R(0), m_rz = R(0);
@@ -553,18 +687,7 @@ __device__ __forceinline__ void strip_band(const Args& a, const double* __restri
           gi[q] = R(0);
         }
         strip_row<D, MIX, C>(a, tab, below ? INT_MAX : i, xi, xj, v[u], jc, g, gi, m_res2, m_lphi, m_rz, miss, bad);
-        // 16-lane row sums (row shifts 1, 2, 4, 8: each row's total in its lane 15)
-#pragma unroll
-        for (int q = 0; q < D; ++q) gi[q] += dpp_step<0x111, 0xf>(gi[q]);
-#pragma unroll
-        for (int q = 0; q < D; ++q) gi[q] += dpp_step<0x112, 0xf>(gi[q]);
-#pragma unroll
-        for (int q = 0; q < D; ++q) gi[q] += dpp_step<0x114, 0xf>(gi[q]);
-#pragma unroll
-        for (int q = 0; q < D; ++q) gi[q] += dpp_step<0x118, 0xf>(gi[q]);
-        if ((lane & 15) == 15)
-#pragma unroll
-          for (int q = 0; q < D; ++q) s_row[w][r + u][lane >> 4][q] = gi[q];
+        row_sum_dpp<D>(gi, s_row[w], r + u);
       }
       const int64_t ni = min(i + P, rend - 1);   // refill this ring slot with row i + P
 #pragma unroll
@@ -577,7 +700,7 @@ __device__ __forceinline__ void strip_band(const Args& a, const double* __restri
 }
 
 template <int D, bool MIX, int C, int NW, int P>
-__global__ void __launch_bounds__(64 * NW) k_bmds_strips(Args a,
+__global__ void __launch_bounds__(64 * NW, MIX ? 1 : D <= 3 ? 4 : D <= 6 ? 3 : 1) k_bmds_strips(Args a,
                                                          const typename std::conditional<MIX, float, double>::type*
                                                              __restrict__ xs,
                                                          const double* __restrict__ delta) {

@@ -116,3 +116,58 @@ def test_bmds_tile_count_boundary(prec, n):
     pairs, single-band strips of one column per lane for float32 pairs), and
     N = 11,457 the smallest with more (the wide strips)."""
     _check_device_case(("edge", n), 30 + n % 7, n, 3, prec)
+
+
+@pytest.mark.parametrize("spread", [0.1, 0.6, 2.0])
+@pytest.mark.parametrize("n,d", [(2, 1), (3, 2), (66, 5), (67, 4), (255, 8), (259, 2)])
+def test_bmds_near_pairs_and_row_groups(n, d, spread):
+    """Float64 pairs at small z (the tail's fitted forms, coincident events,
+    waves that hold near and far pairs) at counts that end a row band within a
+    group of rows.  Each pair's terms carry some tens of roundings and a sum
+    over a row up to N more, so the errors stay below 1e-13 of the sums of the
+    terms' magnitudes."""
+    rng = np.random.default_rng(n + d)
+    sigma = 0.8
+    x = rng.normal(size=(n, d)) * spread * sigma
+    if n > 4:
+        x[4] = x[1]
+        x[n // 2:] *= 4.0
+    dist = np.sqrt(((x[:, None] - x[None]) ** 2).sum(-1))
+    delta = np.abs(dist + sigma * rng.normal(size=(n, n)))
+    say(f"case bmds near pairs n={n} d={d} spread={spread}")
+    st, ll, ds, M, gx_ref = oracle.bmds(x, delta, sigma)
+    assert st == 0
+    o, gx = _gpu(_Case(x, delta, sigma), "fp64")
+    low = np.tril(np.ones((n, n), bool), -1)
+    size = (delta + dist) / sigma ** 2 + 1.0 / sigma   # bounds |delta - d|/sigma^2 + rho/sigma (rho <= 0.8)
+    size = np.where(low, size, 0.0)
+    row = size.sum(1) + size.sum(0)
+    s_ll = np.where(low, (delta - dist) ** 2 / (2 * sigma ** 2) + abs(np.log(sigma)) + 0.7, 0.0).sum()
+    s_ds = np.where(low, (delta - dist) ** 2 / sigma ** 3 + (delta + dist) * dist / sigma ** 3 + 2.0 / sigma, 0.0).sum()
+    assert o[3] == 0 and o[2] == M
+    assert abs(o[0] - ll) <= 1e-13 * s_ll
+    assert abs(o[1] - ds) <= 1e-13 * s_ds
+    assert np.all(np.abs(gx - gx_ref) <= 1e-13 * row[:, None])
+
+
+class _Case:
+    def __init__(self, x, delta, sigma):
+        self.x, self.delta, self.sigma = x, delta, sigma
+
+
+@pytest.mark.parametrize("far,near", [(37, 5), (66, 64), (1, 0)])
+def test_bmds_overflowing_pair_stays_in_its_rows(far, near):
+    """One event so far away that its distance overflows, observed from one
+    other event only: those two events' gradients are not finite, and every
+    other event's is what it is without that pair."""
+    c = W.bmds_case(9, 70, 3)
+    c.x[far] = 1e200
+    c.delta[far, :] = c.delta[:, far] = np.nan
+    say(f"case bmds overflow far={far} near={near}")
+    o0, g0 = _gpu(c, "fp64")
+    assert o0[3] == 0 and np.all(np.isfinite(g0))
+    c.delta[far, near] = c.delta[near, far] = 1.0
+    o, g = _gpu(c, "fp64")
+    rest = np.setdiff1d(np.arange(70), [far, near])
+    assert not np.isfinite(o[0]) and not np.any(np.isfinite(g[[far, near]]))
+    assert np.all(np.abs(g[rest] - g0[rest]) <= 1e-14 * np.abs(g0).max())
