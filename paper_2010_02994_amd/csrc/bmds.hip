@@ -26,6 +26,7 @@
 // Per-tile (or per-segment) partials are reduced per event in a fixed order.
 #include <hip/hip_runtime.h>
 
+#include <cfloat>
 #include <climits>
 #include <cmath>
 #include <cstdint>
@@ -525,13 +526,16 @@ again:
 // The rows' entries stream through a ring of P rows in registers: the loads
 // of row i + P are issued as soon as row i is done, so P rows stay in flight
 // while the wave computes, also across band boundaries (the band's row-sum
-// barrier waits for LDS only).  The row's own coordinates come by scalar loads
-// from a packed copy of x (kXs values per event).
+// barrier waits for LDS only).  The row's own coordinates come from a packed copy of x
+// (kXs values per event): for float64 pairs by scalar loads, for float32 pairs through
+// LDS, a band at a time, since a float32 operation with a scalar operand issues at half
+// rate.  Float32 pairs take the workgroups in the order of the matrix' rows, so those in
+// flight read neighbouring memory (1 to 2 % at N = 20,000 against chunk by chunk).
+// Measured, float32 pairs, with the totals formed beside the reduction: N = 1,000,
+// D = 6 48.5 -> 35.4 us a call; 4,733 54.8 -> 49.4; 8,000 110 -> 98; 20,000 421 -> 409
+// (D = 2 364 -> 351, 4.7 TB/s; two columns a lane 438, four rows in the ring 426).
 constexpr int kXs = 8;
 constexpr int kPackThreads = 256;
-#ifndef HK_BMDS_STRIP_K_MIXED
-#define HK_BMDS_STRIP_K_MIXED 1
-#endif
 #ifndef HK_BMDS_STRIP_K_FP64
 #define HK_BMDS_STRIP_K_FP64 2
 #endif
@@ -552,9 +556,9 @@ constexpr int kPackThreads = 256;
 // 17 more registers, one wave per SIMD fewer, 5 % slower) and four for
 // float64 pairs.
 constexpr bool valid_strip_k(int k) { return k == 1 || k == 2 || (k >= 4 && k % 4 == 0); }
-constexpr int kStripKMixed = HK_BMDS_STRIP_K_MIXED;
+constexpr int kStripKMixed = 1;   // (the strips' order of workgroups relies on it)
 constexpr int kStripKFp64 = HK_BMDS_STRIP_K_FP64;
-static_assert(valid_strip_k(kStripKMixed) && valid_strip_k(kStripKFp64), "segment length");
+static_assert(kStripKMixed == 1 && valid_strip_k(kStripKFp64), "segment length");
 constexpr int kRingMixed = HK_BMDS_RING_MIXED;
 constexpr int kRingFp64 = HK_BMDS_RING_FP64;
 constexpr int kStripColsMixed = 4;                        // one wave per chunk
@@ -635,7 +639,7 @@ __device__ __forceinline__ void strip_row(const Args& a, const double* __restric
         }
         R rs, dist;
         if constexpr (MIX) {
-          rs = r2 > 0.0f ? __builtin_amdgcn_rsqf(r2) : 0.0f;
+          rs = __builtin_amdgcn_rsqf(fmaxf(r2, FLT_MIN));   // a coincident pair: finite, times differences of 0
           dist = r2 * rs;
         } else {
           rs = rsqrt_f64(r2);
@@ -651,7 +655,7 @@ __device__ __forceinline__ void strip_row(const Args& a, const double* __restric
 #pragma unroll
         for (int q = 0; q < D; ++q) {
           gi[q] = coef * diff[q] + gi[q];
-          g[c][q] = -coef * diff[q] + g[c][q];
+          g[c][q] = coef * diff[q] + g[c][q];
         }
       } else if (isnan(dv)) {
         miss += 1;
@@ -670,9 +674,16 @@ __device__ __forceinline__ void strip_band(const Args& a, const double* __restri
                                            const double* __restrict__ delta, int i0, int nr, int rend, bool below,
                                            const int (&jc)[C], const int (&off)[C], const R (&xj)[C][D],
                                            double (&v)[P][C], R (&g)[C][D], R (&s_row)[NW][kTR][4][D],
-                                           double& a_res2, double& a_lphi, double& a_rz, int& miss, int& bad) {
+                                           R (&s_xi)[MIX ? kTR : 1][kXs], double& a_res2, double& a_lphi, double& a_rz, int& miss, int& bad) {
   const int n = a.n;
   const int w = threadIdx.x >> 6;
+  if constexpr (MIX) {
+    for (int e = threadIdx.x; e < kTR * kXs / 4; e += 64 * NW) {
+      const int64_t i = min(i0 + e / (kXs / 4), n - 1);
+      reinterpret_cast<float4*>(s_xi)[e] = reinterpret_cast<const float4*>(xs)[i * (kXs / 4) + e % (kXs / 4)];
+    }
+    lds_barrier();
+  }
   for (int r = 0; r < nr; r += P) {
     // float32 micro-partials over the ring's P x C pairs, folded into float64
     R m_res2 = R(0), m_lphi = R(0), m_rz = R(0);
@@ -683,7 +694,7 @@ __device__ __forceinline__ void strip_band(const Args& a, const double* __restri
         R xi[D], gi[D];
 #pragma unroll
         for (int q = 0; q < D; ++q) {
-          xi[q] = xs[(int64_t)i * kXs + q];
+          xi[q] = MIX ? s_xi[MIX ? r + u : 0][q] : xs[(int64_t)i * kXs + q];
           gi[q] = R(0);
         }
         strip_row<D, MIX, C>(a, tab, below ? INT_MAX : i, xi, xj, v[u], jc, g, gi, m_res2, m_lphi, m_rz, miss, bad);
@@ -708,6 +719,7 @@ __global__ void __launch_bounds__(64 * NW, MIX ? 1 : D <= 3 ? 4 : D <= 6 ? 3 : 1
   static_assert(64 * C * NW == kTC, "the waves of a workgroup cover one chunk");
   static_assert(kTR % P == 0, "the ring restarts at each band");
   __shared__ R s_row[NW][kTR][4][D];   // 16-lane partial row sums
+  __shared__ __attribute__((aligned(16))) R s_xi[MIX ? kTR : 1][kXs];   // float32 pairs: the band's rows
   __shared__ double sh[4 * 64 * NW];
   __shared__ double s_exptab[MIX ? 1 : kExpTab];
   if constexpr (!MIX) {
@@ -715,15 +727,28 @@ __global__ void __launch_bounds__(64 * NW, MIX ? 1 : D <= 3 ? 4 : D <= 6 ? 3 : 1
     __syncthreads();
   }
   const int K = a.seg_k, M = a.seg_m, n = a.n;
-  const int64_t b = blockIdx.x;
-  int lo = 0, hi = a.ncb - 1;   // chunk: largest J with seg_base(J) <= b
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (seg_base(mid, K, M) <= b) lo = mid;
-    else hi = mid - 1;
+  int64_t b = blockIdx.x;
+  int J, m;
+  if constexpr (MIX) {   // one band a segment: workgroups in the order of the matrix' rows
+    int lo = 0, hi = a.nb - 1;   // band: largest m with band_offset(m) <= b
+    while (lo < hi) {
+      const int mid = (lo + hi + 1) >> 1;
+      if (band_offset(mid) <= b) lo = mid;
+      else hi = mid - 1;
+    }
+    m = lo;
+    J = (int)(b - band_offset(m));
+    b = seg_base(J, K, M) + m - seg_m0(J, K);
+  } else {
+    int lo = 0, hi = a.ncb - 1;   // chunk: largest J with seg_base(J) <= b
+    while (lo < hi) {
+      const int mid = (lo + hi + 1) >> 1;
+      if (seg_base(mid, K, M) <= b) lo = mid;
+      else hi = mid - 1;
+    }
+    J = lo;
+    m = seg_m0(J, K) + (int)(b - seg_base(J, K, M));
   }
-  const int J = lo;
-  const int m = seg_m0(J, K) + (int)(b - seg_base(J, K, M));
   const int rbeg = max(4 * J, m * K) * kTR, rend = min(n, min(a.nb, m * K + K) * kTR);
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   int jc[C], off[C];
@@ -760,7 +785,7 @@ __global__ void __launch_bounds__(64 * NW, MIX ? 1 : D <= 3 ? 4 : D <= 6 ? 3 : 1
     // skip the diagonal test; one code path serves both (a second copy of
     // the loop would cost more registers than the test costs issue slots)
     const bool below = J * kTC + kTC <= i0;
-    strip_band<D, MIX, C, NW, P>(a, s_exptab, xs, delta, i0, nr, rend, below, jc, off, xj, v, g, s_row, a_res2,
+    strip_band<D, MIX, C, NW, P>(a, s_exptab, xs, delta, i0, nr, rend, below, jc, off, xj, v, g, s_row, s_xi, a_res2,
                                  a_lphi, a_rz, miss, bad);
     // the band's row sums over the NW x 4 partials, in a fixed order, stored
     // as R (a float32 row sum over the chunk's columns for float32 pairs; the
@@ -782,20 +807,21 @@ __global__ void __launch_bounds__(64 * NW, MIX ? 1 : D <= 3 ? 4 : D <= 6 ? 3 : 1
 #pragma unroll
   for (int c = 0; c < C; ++c)
 #pragma unroll
-    for (int q = 0; q < D; ++q) static_cast<R*>(a.pcol)[(b * kTC + (w * C + c) * 64 + lane) * D + q] = g[c][q];
+    for (int q = 0; q < D; ++q) static_cast<R*>(a.pcol)[(b * kTC + (w * C + c) * 64 + lane) * D + q] = -g[c][q];
   double tot[4] = {-0.5 * a.inv_s2 * a_res2 - a_lphi, a.inv_sigma * (a.inv_s2 * a_res2 + a_rz), (double)miss,
                    (double)bad};
   block_sum_n(tot, sh);
-  if (threadIdx.x == 0)
+  if (threadIdx.x == 0) {
     for (int k = 0; k < 4; ++k) a.ptile[b * 4 + k] = tot[k];
+    if (tot[3] > 0.0) a.pbad[b % a.npack] = 1.0;   // (every writer stores the same; see k_bmds_reduce)
+  }
 }
 
 // One workgroup: the tile (or segment) totals in order, the -M/2 log sigma^2
 // and -M/sigma terms (M: the pairs of the triangle less the missing ones), and
 // the data checks (invalid deltas, and non-finite x counted by the tiles or by
 // the packing kernel).
-__global__ void __launch_bounds__(kFinalThreads) k_bmds_final(Args a) {
-  __shared__ double sh[4 * kFinalThreads];
+__device__ __forceinline__ void final_block(const Args& a, double* sh) {   // sh: 4 kFinalThreads values
   double v[4] = {0, 0, 0, 0};   // the four totals
   for (int64_t t = threadIdx.x; t < a.nparts; t += kFinalThreads)
     for (int k = 0; k < 4; ++k) v[k] += a.ptile[t * 4 + k];
@@ -810,6 +836,10 @@ __global__ void __launch_bounds__(kFinalThreads) k_bmds_final(Args a) {
     a.out4[3] = bad ? (double)HAWKES_EDATA : 0.0;
   }
 }
+__global__ void __launch_bounds__(kFinalThreads) k_bmds_final(Args a) {
+  __shared__ double sh[4 * kFinalThreads];
+  final_block(a, sh);
+}
 
 // Per event: its row partials over the chunks of its band, then its column
 // partials over the bands (tiles) or segments (strips) that reach its chunk.
@@ -817,18 +847,37 @@ __global__ void __launch_bounds__(kFinalThreads) k_bmds_final(Args a) {
 // one event per lane, so each partial is read by a wave as one contiguous run;
 // its kRedWavesB waves take every kRedWavesB-th chunk and band or segment, in
 // order, and the waves' sums are added in wave order.
+//
+// FIN (strips, one call): the launch's first workgroup forms the totals as
+// k_bmds_final does, beside the others instead of before them (one workgroup reads
+// 400 KB of segment totals at N = 20,000, 11 us of a call's 410), and the others take
+// the data checks from the packing blocks' counts, which a strip that meets an invalid
+// delta also sets.
 constexpr int kRedWavesB = 16;
 
-template <int D, typename PT>
+template <int D, typename PT, bool FIN>
 __global__ void __launch_bounds__(64 * kRedWavesB) k_bmds_reduce(Args a) {
-  __shared__ double s_part[kRedWavesB][D][64];
+  static_assert(64 * kRedWavesB == kFinalThreads, "the totals take a workgroup of the same size");
+  __shared__ double s_mem[FIN && D < 4 ? 4 : D][kFinalThreads];
+  double (*s_part)[D][64] = reinterpret_cast<double (*)[D][64]>(s_mem);
+  if (FIN && blockIdx.x == 0) {
+    final_block(a, &s_mem[0][0]);
+    return;
+  }
   const PT* prow = static_cast<const PT*>(a.prow);
   const PT* pcol = static_cast<const PT*>(a.pcol);
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int n0 = blockIdx.x * 64;   // a multiple of kTR: the band's first row
+  const int n0 = (blockIdx.x - FIN) * 64;   // a multiple of kTR: the band's first row
   const int n = n0 + lane;
   const bool live = n < a.n;
-  const bool bad = a.out4[3] != 0.0;
+  bool bad;
+  if constexpr (FIN) {
+    bool any = false;
+    for (int t = lane; t < a.npack; t += 64) any = any || a.pbad[t] > 0.0;
+    bad = __any(any);
+  } else {
+    bad = a.out4[3] != 0.0;
+  }
   double g[D];
 #pragma unroll
   for (int q = 0; q < D; ++q) g[q] = 0.0;
@@ -907,13 +956,17 @@ static void launch(const Args& a, int prec, hipStream_t s, int phase) {
     } else {   // float64 pairs, few tiles
       k_bmds_tiles<D, false, 1><<<nt, TileShape<1>::kLanes, 0, s>>>(a);
     }
-    k_bmds_final<<<1, kFinalThreads, 0, s>>>(a);
+    if (phase == 1 || !a.grad_x || a.seg_k == 0) k_bmds_final<<<1, kFinalThreads, 0, s>>>(a);
   }
   if (phase != 1 && a.grad_x) {
     const unsigned nred = (unsigned)((a.n + 63) / 64);
+    constexpr int nt = 64 * kRedWavesB;
     // the strips store float32 partials for float32 pairs
-    if (a.seg_k > 0 && prec == HAWKES_MIXED) k_bmds_reduce<D, float><<<nred, 64 * kRedWavesB, 0, s>>>(a);
-    else k_bmds_reduce<D, double><<<nred, 64 * kRedWavesB, 0, s>>>(a);
+    if (a.seg_k == 0) k_bmds_reduce<D, double, false><<<nred, nt, 0, s>>>(a);
+    else if (phase == 2 && prec == HAWKES_MIXED) k_bmds_reduce<D, float, false><<<nred, nt, 0, s>>>(a);
+    else if (phase == 2) k_bmds_reduce<D, double, false><<<nred, nt, 0, s>>>(a);
+    else if (prec == HAWKES_MIXED) k_bmds_reduce<D, float, true><<<nred + 1, nt, 0, s>>>(a);
+    else k_bmds_reduce<D, double, true><<<nred + 1, nt, 0, s>>>(a);
   }
 }
 

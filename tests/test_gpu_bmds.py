@@ -171,3 +171,19 @@ def test_bmds_overflowing_pair_stays_in_its_rows(far, near):
     rest = np.setdiff1d(np.arange(70), [far, near])
     assert not np.isfinite(o[0]) and not np.any(np.isfinite(g[[far, near]]))
     assert np.all(np.abs(g[rest] - g0[rest]) <= 1e-14 * np.abs(g0).max())
+
+
+@pytest.mark.parametrize("value", [-1.0, np.inf])
+@pytest.mark.parametrize("row,col", [(1, 0), (64, 63), (299, 298), (299, 0)])
+def test_bmds_strips_report_an_invalid_delta(row, col, value):
+    """Float32 pairs (strips): an invalid dissimilarity in the first and last
+    rows and in the corners of a band reaches the totals and every gradient
+    row, and the next call with valid data does not see it."""
+    c = W.bmds_case(7, 300, 2)
+    keep = c.delta[row, col]
+    c.delta[row, col] = value
+    say(f"case bmds strips invalid delta row={row} col={col}")
+    o, gx = _gpu(c, "mixed")
+    assert o[3] == -3 and np.isnan(o[0]) and np.isnan(o[1]) and np.all(np.isnan(gx))
+    c.delta[row, col] = keep
+    _check(c, "mixed", c.name)
