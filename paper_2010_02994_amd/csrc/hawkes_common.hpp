@@ -49,9 +49,12 @@ constexpr int kRedThreads = 64 * kRedWaves;
 // Waves per SIMD the mixed passes are compiled for: the register budget
 // (512 / waves per lane) must hold the rows' state, which grows with D, or
 // the kernel spills to scratch.  The set values apply at D <= 2; wider
-// records take fewer waves.
+// records take fewer waves.  Gradient pass, one wave fewer without spills
+// against one more with them (N = 50,000, whole call): D = 3 1,437 -> 1,385 us,
+// D = 4 1,582 -> 1,567, D = 6 1,934 -> 1,927 (N = 4,733 81.4 -> 78.6); at D = 5
+// four waves with 20 spills stay (three: 1,734 -> 1,741).
 constexpr int rate_waves(int d, bool ru) { return ru && d >= 2 ? 4 : HK_RATE_WAVES_PER_EU; }
-constexpr int grad_waves(int d) { return d <= 2 ? HK_GRAD_WAVES_PER_EU : d <= 4 ? 5 : d <= 6 ? 4 : 3; }
+constexpr int grad_waves(int d) { return d <= 2 ? HK_GRAD_WAVES_PER_EU : d <= 5 ? 4 : 3; }
 // Step groups of the float64 passes (see PassLds): dimensions above
 // kMaxSplitD have no split form.
 constexpr int kMaxSplitD = 4;
