@@ -153,7 +153,7 @@ int hawkes_diagnostics(const void* ws /* device */, size_t ws_bytes, int64_t n, 
  * its own copy until the process ends), so the call allocates nothing and
  * creates no stream; the scalars come back through a
  * pooled pinned buffer only if one already exists (else by a copy).  Limit: hawkes_workspace_bytes(n, d,
- * prec) <= HAWKES_NOALLOC_SCRATCH_BYTES (about n <= 18,000 at d = 2), else
+ * prec) <= HAWKES_NOALLOC_SCRATCH_BYTES (n <= 17,920 at d = 2, 17,658 at d = 6), else
  * HAWKES_ENOMEM and nothing runs.  Every call on one GPU shares its array,
  * which keeps the last call's contents (each call writes every part it
  * reads), so calls that overlap on one GPU -- from two threads, or on two
@@ -310,7 +310,9 @@ int hawkes_leapfrog_bmds(double* x /* device, n*d */, double* p /* device, n*d *
  * (d, precision) form a batch that runs as one kernel launch per phase on one
  * of several HIP streams, so batches overlap on the device and requests that
  * arrive meanwhile are admitted as slots and memory free up.  A request's
- * result is bitwise identical whether it runs alone or in any batch.
+ * result is bitwise identical whether it runs alone or in any batch (and that
+ * of the direct call, unless only a workspace of larger work items, whose
+ * float64 partial sums are grouped otherwise, fits in the arena).
  *
  * Threading: every call may come from any host thread.  x and grad_x stay
  * owned by the client and must stay alive until the request completes.

@@ -87,17 +87,14 @@ static int split_for(int64_t n, int nb, int d, bool mixed) {
   return !mixed && d <= kMaxSplitD && tiles <= 700 ? 2 : 1;
 }
 
-bool make_layout(int64_t n, int d, int prec, Layout& Lo) {
-  const int base = prec & ~HAWKES_CULL;
-  if (n < 2 || n > (int64_t(1) << 30) || d < 1 || d > kMaxD || (base != HAWKES_FP64 && base != HAWKES_MIXED))
-    return false;
+static void layout_with(int64_t n, int d, int base, bool cull, int L, Layout& Lo) {
   Lo.n = n;
   Lo.d = d;
   Lo.mixed = base == HAWKES_MIXED;
-  Lo.cull = (prec & HAWKES_CULL) != 0;
+  Lo.cull = cull;
   Lo.nb = (int)((n + kBandRows - 1) / kBandRows);
   Lo.n_pad = Lo.nb * kBandRows;
-  Lo.L = tiles_per_item(n);
+  Lo.L = L;
   Lo.b_fine = fine_bands(n, Lo.nb, Lo.L);
   Lo.split = split_for(n, Lo.nb, d, Lo.mixed);
   Lo.items = 0;
@@ -133,6 +130,26 @@ bool make_layout(int64_t n, int d, int prec, Layout& Lo) {
   Lo.off_fixpart = take(sizeof(double) * kFixStride * (size_t)n);
   Lo.off_mompart = take(sizeof(double) * 2 * (size_t)Lo.items);
   Lo.total = o;
+}
+
+// Small items cost row partials (N = 10,000, D = 2: 49 MB of workspace with one tile
+// per item, 28 with four), so a workspace that would pass `room` takes larger items,
+// up to four tiles, if it then fits.  Every call of up to kScratchEvents events has the
+// static scratch of hawkes_grad_noalloc for room, so that it serves the sizes that four
+// tiles per item allow (all N <= 17,920 up to D = 3, 15,872 at D = 6) with the results of
+// hawkes_grad.  Beyond, the items stay as measured best (N = 20,000, D = 2 would fit
+// with four tiles per item at 300 us against 284).
+constexpr int64_t kScratchEvents = 17920;
+bool make_layout(int64_t n, int d, int prec, Layout& Lo, size_t room) {
+  const int base = prec & ~HAWKES_CULL;
+  const bool cull = (prec & HAWKES_CULL) != 0;
+  if (n < 2 || n > (int64_t(1) << 30) || d < 1 || d > kMaxD || (base != HAWKES_FP64 && base != HAWKES_MIXED))
+    return false;
+  if (room == 0) room = n <= kScratchEvents ? (size_t)HAWKES_NOALLOC_SCRATCH_BYTES : SIZE_MAX;
+  const int L = tiles_per_item(n);
+  layout_with(n, d, base, cull, L, Lo);
+  for (int k = L + 1; Lo.total > room && k <= 4; ++k) layout_with(n, d, base, cull, k, Lo);
+  if (Lo.total > room && Lo.L != L) layout_with(n, d, base, cull, L, Lo);
   return true;
 }
 

@@ -26,7 +26,8 @@ struct BatchGrid {
   int red_blocks;  // blocks of a reduction launch
 };
 
-bool make_layout(int64_t n, int d, int prec, Layout& Lo);
+// room: bytes the workspace should fit (0: the library's rule).
+bool make_layout(int64_t n, int d, int prec, Layout& Lo, size_t room = 0);
 bool valid_params(const hawkes_params_t* p);
 KParams make_kparams(const Layout& Lo, const hawkes_params_t* p);
 ReqDesc make_desc(const Layout& Lo, const KParams& kp, const double* x, const double* t, void* ws, double* out8,

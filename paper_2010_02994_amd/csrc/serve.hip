@@ -165,9 +165,15 @@ void dev_free(hawkes_server* S, void* p) {
   else (void)hipFree(p);
 }
 
-size_t footprint(int64_t n, int d, int prec) {
-  const size_t ws = hawkes_workspace_bytes(n, d, prec);
-  return ws ? (ws + 4095) & ~size_t(4095) : 0;
+size_t whole_pages(size_t bytes) { return (bytes + 4095) & ~size_t(4095); }
+size_t footprint(int64_t n, int d, int prec) { return whole_pages(hawkes_workspace_bytes(n, d, prec)); }
+
+// A request's layout: the direct calls' unless the arena cannot hold that, then the
+// larger work items that it can hold, if any (a request that fits neither is refused).
+bool request_layout(hawkes_server* S, const Dataset& ds, int prec, Layout& Lo) {
+  const size_t cap = S->arena.capacity() & ~size_t(4095);
+  if (!make_layout(ds.n, ds.d, prec, Lo)) return false;
+  return Lo.total <= cap || make_layout(ds.n, ds.d, prec, Lo, cap);
 }
 
 void finish(hawkes_server* S, Request* r, int status, const double* out8) {
@@ -280,7 +286,7 @@ bool admit_and_launch(hawkes_server* S) {
         Request* r = take[k];
         const Dataset& ds = S->datasets[r->ds];
         Layout Lo;
-        make_layout(ds.n, ds.d, r->prec, Lo);
+        request_layout(S, ds, r->prec, Lo);
         const KParams kp = make_kparams(Lo, &r->p);
         b.host_desc[k] = make_desc(Lo, kp, r->x, ds.t, S->arena_base + r->off, b.dev_out + 8 * k, r->grad_x);
         grad = grad || r->grad_x != nullptr;
@@ -436,8 +442,9 @@ int hawkes_serve_submit(hawkes_server_t* S, int32_t dataset_id, const double* x,
   if (S->stop) return HAWKES_ESTATE;
   if (dataset_id < 0 || dataset_id >= (int32_t)S->datasets.size()) return HAWKES_ESTATE;
   const Dataset& ds = S->datasets[dataset_id];
-  const size_t foot = footprint(ds.n, ds.d, prec);
-  if (foot == 0) return HAWKES_EINVAL;
+  Layout Lo;
+  if (!request_layout(S, ds, prec, Lo)) return HAWKES_EINVAL;
+  const size_t foot = whole_pages(Lo.total);
   if (foot > S->arena.capacity()) return HAWKES_ENOMEM;
   auto* r = new Request;
   r->ticket = S->next_ticket++;
@@ -447,8 +454,6 @@ int hawkes_serve_submit(hawkes_server_t* S, int32_t dataset_id, const double* x,
   r->prec = prec;
   r->grad_x = grad_x;
   r->foot = foot;
-  hawkes::Layout Lo;
-  hawkes::make_layout(ds.n, ds.d, prec, Lo);   // foot > 0: the sizes are valid
   r->split = Lo.split;
   r->res.status = HAWKES_EPENDING;
   r->res.t_submit_ns = now_ns();
