@@ -89,6 +89,24 @@ __device__ __forceinline__ void pair_ab(const Model& m, const double* xi, double
   b = dt > 0.0 ? exp_tab(-m.omega * dt - m.gamma * r2, tab) : 0.0;
 }
 
+// The same without a branch: both exps are computed, and dropped where they do not
+// count.
+template <int D>
+__device__ __forceinline__ void pair_ab_both(const Model& m, const double* xi, double ti, const double* xj, double tj,
+                                             double& a, double& b, const double* __restrict__ tab) {
+  double r2 = 0.0;
+#pragma unroll
+  for (int q = 0; q < D; ++q) {
+    const double dx = xi[q] - xj[q];
+    r2 = fma(dx, dx, r2);
+  }
+  const double dt = ti - tj;
+  const double ea = exp_tab(-m.alpha * r2 - m.beta * dt * dt, tab);
+  const double eb = exp_tab(-m.omega * fmax(dt, 0.0) - m.gamma * r2, tab);
+  a = dt != 0.0 ? ea : 0.0;
+  b = dt > 0.0 ? eb : 0.0;
+}
+
 // Position of event j in the moved list, or -1 (binary search; the list is
 // read within its bounds whatever it holds).
 __device__ __forceinline__ int find_moved(const int64_t* idx, int nmove, int j) {
@@ -256,6 +274,14 @@ __device__ __forceinline__ void moved_change(const Step& s, int blk) {
 // read as a broadcast: no sum crosses lanes until the end.  (One moved row at a
 // time, its partners across the lanes, took 33 us for 64 moved events at
 // N = 50,000: a workgroup reduction per six partners and lane.)
+//
+// Launches of few such workgroups leave most SIMDs with one wave of them, bound by the
+// latency of the chain through a pair: up to kFewSums they take two partners at a time
+// without branches, so four exps are in flight.  N = 20,000 (79 workgroups), 20 moved
+// events 19.4 -> 17.1 us a step, 64 moved 27.5 -> 24.7; with 196 workgroups (N = 50,000,
+// 64 moved), whose waves hide it for each other, the exps this computes for later
+// partners cost more: 30.1 -> 32.1.
+constexpr int kFewSums = 128;
 template <int D>
 __device__ __forceinline__ void moved_rows(const Step& s, int blk) {
   __shared__ double s_p[kBlock][D + 1];
@@ -265,6 +291,7 @@ __device__ __forceinline__ void moved_rows(const Step& s, int blk) {
   fill_exp_table(s_exptab);
   const int groups = (s.nmove + 63) / 64;
   const int c = blk / groups, g = blk % groups;
+  const bool few = s.nchunk * groups <= kFewSums;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int in_group = min(64, s.nmove - g * 64);
   int p2 = 1;
@@ -299,14 +326,33 @@ __device__ __forceinline__ void moved_rows(const Step& s, int blk) {
     }
     __syncthreads();
     const int k_end = min(64 * w + 64, j_end - j0);
-    if (r >= 0)
-      for (int k = 64 * w + sub; k < k_end; k += subs) {
-        if (j0 + k == r) continue;
-        double pa, pb;
-        pair_ab<D>(s.m, xr, tr, s_p[k], s_p[k][D], pa, pb, s_exptab);
-        a += pa;
-        b += pb;
+    if (r >= 0) {
+      if (few) {
+        for (int k = 64 * w + sub; k < k_end; k += 2 * subs) {
+          // two partners at a time: their exps are independent chains
+          const int k1 = min(k + subs, k_end - 1);
+          double pa, pb, qa, qb;
+          pair_ab_both<D>(s.m, xr, tr, s_p[k], s_p[k][D], pa, pb, s_exptab);
+          pair_ab_both<D>(s.m, xr, tr, s_p[k1], s_p[k1][D], qa, qb, s_exptab);
+          if (j0 + k != r) {
+            a += pa;
+            b += pb;
+          }
+          if (k + subs < k_end && j0 + k1 != r) {
+            a += qa;
+            b += qb;
+          }
+        }
+      } else {
+        for (int k = 64 * w + sub; k < k_end; k += subs) {
+          if (j0 + k == r) continue;
+          double pa, pb;
+          pair_ab<D>(s.m, xr, tr, s_p[k], s_p[k][D], pa, pb, s_exptab);
+          a += pa;
+          b += pb;
+        }
       }
+    }
   }
   for (int o = p2; o < 64; o <<= 1) {
     a += __shfl_xor(a, o);
@@ -327,11 +373,18 @@ __device__ __forceinline__ void moved_rows(const Step& s, int blk) {
   }
 }
 
-// Both in one launch: neither reads what the other writes.
+// Both in one launch: neither reads what the other writes.  The longer workgroups go
+// first: a moved rows' sum is 64 partners a wave whatever the block, a row block's change
+// three to four exps for every (four lanes: every fourth) moved event.  N = 50,000: 64
+// moved events 35.1 -> 30.2 us a step with the sums first, 300 moved 81.9 -> 92.4.
+constexpr int kSumsFirst = 128;
 template <int D, int RL>
 __global__ void __launch_bounds__(kBlock) k_mwg_rows(Step s) {
-  if ((int)blockIdx.x < s.nrb) moved_change<D, RL>(s, blockIdx.x);
-  else moved_rows<D>(s, blockIdx.x - s.nrb);
+  const int sums = (int)gridDim.x - s.nrb;   // workgroups of the moved rows' sums
+  const bool sums_first = s.nmove <= kSumsFirst;
+  const int b = (int)blockIdx.x - (sums_first ? sums : 0);
+  if (b >= 0 && b < s.nrb) moved_change<D, RL>(s, b);
+  else moved_rows<D>(s, sums_first ? blockIdx.x : blockIdx.x - s.nrb);
 }
 
 // Partner segments per listed row: kSeg, or more when few rows are listed so

@@ -302,3 +302,11 @@ def test_mwg_block_sizes(n, d, nmove):
     assert abs(got[0] - (ll1 - ll0)) <= 1e-10 * max(abs(ll0), abs(ll1))
     assert np.array_equal(xd.cpu().numpy(), x1)
     _check_terms(terms.cpu().numpy(), oracle.event_terms(x1, w.t, w.params), "fp64", w.params, f"nmove{nmove}")
+
+
+@pytest.mark.parametrize("n,nmove", [(8200, 128), (8200, 129), (8200, 192), (8200, 193), (8449, 1), (513, 33)])
+def test_mwg_moved_row_sums(n, nmove):
+    """The moved rows' sums before and after the unmoved rows' workgroups, two
+    partners at a time and one (99 and 132 workgroups), and last partner chunks
+    of 8 and of 1, whose second partner is missing."""
+    test_mwg_block_sizes(n, 2, nmove)
