@@ -280,9 +280,10 @@ __device__ __forceinline__ void moved_change(const Step& s, int blk) {
 // without branches, so four exps are in flight.  N = 20,000 (79 workgroups), 20 moved
 // events 19.4 -> 17.1 us a step, 64 moved 27.5 -> 24.7; with 196 workgroups (N = 50,000,
 // 64 moved), whose waves hide it for each other, the exps this computes for later
-// partners cost more: 30.1 -> 32.1.
+// partners cost more: 30.1 -> 32.1.  (PAIRS: not in the kernel of few moved events, whose
+// lanes have a few partners each; one event at N = 2,925 9.4 against 9.5 us a step.)
 constexpr int kFewSums = 128;
-template <int D>
+template <int D, bool PAIRS>
 __device__ __forceinline__ void moved_rows(const Step& s, int blk) {
   __shared__ double s_p[kBlock][D + 1];
   __shared__ int64_t s_idx[kBlock];
@@ -291,12 +292,12 @@ __device__ __forceinline__ void moved_rows(const Step& s, int blk) {
   fill_exp_table(s_exptab);
   const int groups = (s.nmove + 63) / 64;
   const int c = blk / groups, g = blk % groups;
-  const bool few = s.nchunk * groups <= kFewSums;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int in_group = min(64, s.nmove - g * 64);
   int p2 = 1;
   while (p2 < in_group) p2 <<= 1;
   const int e = g * 64 + (lane & (p2 - 1)), sub = lane / p2, subs = 64 / p2;
+  const bool few = PAIRS && s.nchunk * groups <= kFewSums;
   const bool staged = s.nmove <= kBlock;   // the moved list fits LDS
   if (staged && tid < s.nmove) s_idx[tid] = s.idx[tid];
   int r = -1;
@@ -381,10 +382,10 @@ constexpr int kSumsFirst = 128;
 template <int D, int RL>
 __global__ void __launch_bounds__(kBlock) k_mwg_rows(Step s) {
   const int sums = (int)gridDim.x - s.nrb;   // workgroups of the moved rows' sums
-  const bool sums_first = s.nmove <= kSumsFirst;
+  const bool sums_first = RL > 1 && s.nmove <= kSumsFirst;
   const int b = (int)blockIdx.x - (sums_first ? sums : 0);
   if (b >= 0 && b < s.nrb) moved_change<D, RL>(s, b);
-  else moved_rows<D>(s, sums_first ? blockIdx.x : blockIdx.x - s.nrb);
+  else moved_rows<D, (RL > 1)>(s, sums_first ? blockIdx.x : blockIdx.x - s.nrb);
 }
 
 // Partner segments per listed row: kSeg, or more when few rows are listed so
