@@ -639,7 +639,11 @@ __device__ __forceinline__ void strip_row(const Args& a, const double* __restric
         }
         R rs, dist;
         if constexpr (MIX) {
-          rs = __builtin_amdgcn_rsqf(fmaxf(r2, FLT_MIN));   // a coincident pair: finite, times differences of 0
+          // a coincident pair adds no direction, nor does one whose squared distance is
+          // subnormal, which the reciprocal root takes for 0 (a finite stand-in for 1/d would
+          // not do: times (delta - d)/sigma^2 it can pass the float32 range, and inf times the
+          // zero differences is NaN)
+          rs = r2 >= FLT_MIN ? __builtin_amdgcn_rsqf(r2) : 0.0f;
           dist = r2 * rs;
         } else {
           rs = rsqrt_f64(r2);

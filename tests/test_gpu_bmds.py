@@ -187,3 +187,27 @@ def test_bmds_strips_report_an_invalid_delta(row, col, value):
     assert o[3] == -3 and np.isnan(o[0]) and np.isnan(o[1]) and np.all(np.isnan(gx))
     c.delta[row, col] = keep
     _check(c, "mixed", c.name)
+
+
+@pytest.mark.parametrize("sigma", [1.0, 1e-6, 1e-10, 1e-15])
+@pytest.mark.parametrize("n,d,apart", [(2, 3, 0.0), (2, 1, 1e-20), (70, 2, 0.0), (11457, 2, 0.0)])
+def test_bmds_coincident_float32_pairs_add_no_direction(n, d, apart, sigma):
+    """Float32 pairs (narrow strips, and the wide ones from 11,457 events on) of
+    events at one place, whose residuals over sigma^2 reach 1e30: their
+    distances are exactly zero (or so small that their squares are subnormal),
+    so every gradient entry is zero.  The scalars follow
+    from d = 0: each pair adds delta^2/(2 sigma^2) + log Phi(0), and
+    delta^2/sigma^3 (float32 terms: 1e-5)."""
+    import torch
+    from paper_2010_02994_amd import api
+    x = torch.zeros((n, d), dtype=torch.float64, device="cuda:0")
+    x[1:] += apart
+    dl = torch.ones((n, n), dtype=torch.float64, device="cuda:0")
+    say(f"case bmds coincident n={n} d={d} apart={apart} sigma={sigma}")
+    out4, gx = api.bmds(x, dl, sigma, prec="mixed")
+    o = out4.cpu().numpy()
+    m = n * (n - 1) // 2
+    assert o[3] == 0 and o[2] == m
+    assert not torch.any(gx).item()   # all zero (a NaN would count as nonzero)
+    assert o[0] == pytest.approx(-m * (np.log(sigma) + 0.5 / sigma**2 + np.log(0.5)), rel=1e-5)
+    assert o[1] == pytest.approx(m * (1.0 / sigma**3 - 1.0 / sigma), rel=1e-5, abs=1e-5 * m / sigma)
