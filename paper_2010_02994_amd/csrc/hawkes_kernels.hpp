@@ -996,7 +996,11 @@ __global__ void __launch_bounds__(SP* kThreads) __attribute__((amdgpu_waves_per_
 // folded into their float64 accumulators every kRowFold = 32 steps.
 // Everything stored outside the wave is float64.
 constexpr int kColSteps = 32 / kRowsPerLane;
-constexpr float kNoPair = -INFINITY;                          // exponent of a pair that does not interact
+// Exponent of a pair that does not interact, selected after the exponents are formed: the
+// scales mG and mW may be infinite in float32 (tau_x/h beyond 2e19, omega tau_t beyond
+// 2e38), and infinity times the zero distance or time difference of an event with itself
+// would make an exponent that starts at -infinity NaN.
+constexpr float kNoPair = -INFINITY;
 constexpr float kHalfLog2e = (float)(0.5 * 1.4426950408889634074);   // mA = mB
 
 // A constant of the pair loop in a vector register.  A float32 operation with
@@ -1054,12 +1058,11 @@ __device__ __forceinline__ void pass1_tile_mixed(Pass1Rows<D, true>& S, const ty
           const float dt = S.t[r] - col.v[D];
           r2v[s][r] = r2;
           dtv[s][r] = dt;
-          // an inactive pair's exponents start at -inf, so both exps are 0
-          // (|dt|, so that -inf meets no +inf; active pairs have dt > 0): one
-          // select for the two terms, and none on their sums
-          const float z0 = !MASK || (tile_base + ((lane + k0 + s) & 63)) < S.first[r] ? sh : kNoPair;
-          ebv[s][r] = __builtin_fmaf(-kHalfLog2e, dt * dt, __builtin_fmaf(-kHalfLog2e, r2, z0));
-          esv[s][r] = __builtin_fmaf(-mW, MASK ? __builtin_fabsf(dt) : dt, __builtin_fmaf(-mG, r2, z0));
+          const bool act = !MASK || (tile_base + ((lane + k0 + s) & 63)) < S.first[r];
+          const float zb = __builtin_fmaf(-kHalfLog2e, dt * dt, __builtin_fmaf(-kHalfLog2e, r2, sh));
+          const float zs = __builtin_fmaf(-mW, dt, __builtin_fmaf(-mG, r2, sh));
+          ebv[s][r] = act ? zb : kNoPair;
+          esv[s][r] = act ? zs : kNoPair;
         }
       }
 #pragma unroll
@@ -1252,9 +1255,11 @@ __device__ __forceinline__ void pass2_tile_mixed(Pass2Rows<D, true>& S, const ty
             r2[s][r] = q == 0 ? dx[s][r][q] * dx[s][r][q] : dx[s][r][q] * dx[s][r][q] + r2[s][r];
           }
           dt[s][r] = S.t[r] - col.v[D];
-          const float z0 = !MASK || (tile_base + ((lane + k0 + s) & 63)) < S.first[r] ? sh : kNoPair;
-          eb[s][r] = __builtin_fmaf(-kHalfLog2e, dt[s][r] * dt[s][r], __builtin_fmaf(-kHalfLog2e, r2[s][r], z0));
-          es[s][r] = __builtin_fmaf(-mW, MASK ? __builtin_fabsf(dt[s][r]) : dt[s][r], __builtin_fmaf(-mG, r2[s][r], z0));
+          const bool act = !MASK || (tile_base + ((lane + k0 + s) & 63)) < S.first[r];
+          const float zb = __builtin_fmaf(-kHalfLog2e, dt[s][r] * dt[s][r], __builtin_fmaf(-kHalfLog2e, r2[s][r], sh));
+          const float zs = __builtin_fmaf(-mW, dt[s][r], __builtin_fmaf(-mG, r2[s][r], sh));
+          eb[s][r] = act ? zb : kNoPair;
+          es[s][r] = act ? zs : kNoPair;
         }
       }
 #pragma unroll

@@ -98,3 +98,26 @@ def test_culled_terms_are_bitwise_identical(prec, tau, omega, n, d):
     assert a[0] == b[0] and np.array_equal(a[1], b[1]) and np.array_equal(a[2], b[2])
     x, t = torch.tensor(w.x, device="cuda:0"), torch.tensor(w.t, device="cuda:0")
     assert api.loglik(x, t, p, prec=prec) == api.loglik(x, t, p, prec=prec + "+cull")
+
+
+@pytest.mark.parametrize("params,scale", [((0.5, 1.0, 1e20, 0.0, 1e20, 1.0), 1.0), ((0.5, 1.0, 1e20, 0.3, 1e20, 1.0), 1.0),
+                                          ((0.5, 1.0, 1.0, 0.0, 1.0, 1e-20), 1.0)])
+@pytest.mark.parametrize("n,d", [(70, 1), (700, 2), (700, 6)])
+@pytest.mark.parametrize("cull", ["", "+cull"])
+def test_mixed_scales_beyond_float32(params, scale, n, d, cull):
+    """omega tau_t, or (tau_x / h)^2, beyond float32's range: the excitation of
+    every pair is zero in float32 and next to nothing in fact (its weight is
+    zero, or its exponent below -1e17), the background as usual, and pairs
+    that do not interact (an event with itself among them) add nothing."""
+    rng = np.random.default_rng(n + d)
+    x = scale * rng.normal(size=(n, d))
+    t = np.sort(rng.uniform(0.0, 10.0, n))
+    p = np.array(params)
+    say(f"case scales n={n} d={d} params={params} cull={cull}")
+    got = run_gpu(x, t, p, "mixed" + cull)
+    ref = oracle_ref(x, t, p)
+    ll, gx, gp = got
+    assert abs(ll - ref.ll) <= 1e-5 * abs(ref.ll)
+    assert np.all(np.isfinite(gp))
+    d_row = np.linalg.norm(gx - ref.gx, axis=1)
+    assert np.all(d_row <= 3e-4 * ref.row_scale)
