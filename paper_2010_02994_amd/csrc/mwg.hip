@@ -31,13 +31,6 @@ constexpr int kSeg = 32;          // partner segments (workspace per event) of e
 constexpr int kMaxSeg = 512;      // at most, when few rows are listed
 constexpr int kExactGrid = 512;   // workgroups of the exact-row kernel's listed rows (grid-stride over tasks)
 constexpr int kListThreads = 1024;
-// Steps of fewer than kManyMoved moved events over at most this many events are
-// two launches instead of three: the decision kernel merges the moved rows'
-// chunk sums and recomputes listed rows itself (all of its workgroups, the same
-// rows; a listed row is N / 256 pair terms per thread there, 32 at this size).
-// One moved event at N = 2,925: 9.6 us a step against 10.4 with three launches;
-// with 64, merging in every workgroup cost more than the launch (30 and 22 us).
-constexpr int kFewEvents = 8192;
 
 struct Model {
   double mu0, theta;
@@ -69,7 +62,7 @@ struct Step {
   int* list;            // n: all of them in index order
   double* part;         // listed rows' segment sums (a, b), n x kSeg x 2 at most
   double* mpart;        // nchunk x nmove x 2: moved rows' chunk sums (at most n x kSeg x 2)
-  double* mrow;         // nmove x 2: moved rows' sums (three-launch steps)
+  double* mrow;         // nmove x 2: moved rows' sums
   int* state;           // [accepted, list length]
 };
 
@@ -472,17 +465,21 @@ __device__ __forceinline__ void listed_sums(const Step& s, int r, int j0, int j1
   ab[1] = b * s.m.cse_unit;
 }
 
-// Three-launch steps: the listed rows, split into (row, partner segment) tasks
-// over a fixed grid, and (after them, one wave per row) the moved rows' chunk
-// sums added in a fixed order.  Workgroup 0 also writes the list and its
-// length, which the decision kernel reads.
+// The listed rows, split into (row, partner segment) tasks over a fixed grid, and
+// (after them, one wave per row) the moved rows' chunk sums added in a fixed order.
+// Workgroup 0 also writes the list and its length, which the decision kernel reads.
+// (Small steps without this launch, whose decision kernel merged the moved rows' sums and
+// recomputed the listed rows in every one of its workgroups, saved about 1 us where no row
+// was listed, one event at N = 2,925, and had no bound where some were: a first event moved
+// away from 300 events of the next day 2.0 ms instead of 0.1, from 8,191 at N = 8,192 104 ms
+// instead of 1.8; 7 moved events at N = 8,000, D = 6 92 us instead of 20.)
 constexpr int kMergeRows = kBlock / 64;
 template <int D>
 __global__ void __launch_bounds__(kBlock) k_mwg_exact(Step s) {
   __shared__ double sh[2 * kBlock];
   __shared__ int s_scan[kBlock];
   __shared__ int s_wtot[kBlock / 64];
-  __shared__ double s_exptab[kExpTab];   // 2^(j/kExpTab) for exp_tab (read after the scan's barriers)
+  __shared__ double s_exptab[kExpTab];   // 2^(j/kExpTab) for exp_tab
   const int tid = threadIdx.x;
   if ((int)blockIdx.x >= kExactGrid) {
     const int e = ((int)blockIdx.x - kExactGrid) * kMergeRows + (tid >> 6), lane = tid & 63;
@@ -503,7 +500,6 @@ __global__ void __launch_bounds__(kBlock) k_mwg_exact(Step s) {
     }
     return;
   }
-  fill_exp_table(s_exptab);
   int own, lo, hi;
   const Listed L = listed_rows(s, s_scan, s_wtot, own, lo, hi);
   if (blockIdx.x == 0) {
@@ -514,6 +510,9 @@ __global__ void __launch_bounds__(kBlock) k_mwg_exact(Step s) {
     }
     if (tid == 0) s.state[1] = L.cnt;
   }
+  if (L.cnt == 0) return;
+  fill_exp_table(s_exptab);
+  __syncthreads();
   const int segs = segs_for(L.cnt, s.n);
   const int seg = (s.n + segs - 1) / segs;
   for (int64_t task = blockIdx.x; task < (int64_t)L.cnt * segs; task += kExactGrid) {
@@ -534,11 +533,10 @@ __global__ void __launch_bounds__(kBlock) k_mwg_exact(Step s) {
 // decision; each then updates its own rows on accept, and workgroup 0 reports.
 // The moved and listed rows' old log-rates come from k_mwg_rows' copy (a
 // workgroup updating its rows' cached terms must not change what another one
-// reads).  FEW: two-launch steps, which merge the moved rows' chunk sums and
-// recompute the listed rows here.  (A device-wide fence in every workgroup of
+// reads).  (A device-wide fence in every workgroup of
 // the exact kernel, to decide in its last workgroup instead, would write back
 // the L2 of each die, which costs more than a launch.)
-template <int D, bool FEW>
+template <int D>
 __global__ void __launch_bounds__(kBlock) k_mwg_settle(Step s) {
   __shared__ double sh[2 * kBlock];
   __shared__ double s_na[kBlock], s_nb[kBlock], s_dl[kBlock];
@@ -560,72 +558,32 @@ __global__ void __launch_bounds__(kBlock) k_mwg_settle(Step s) {
       s_own[r - base] = 1;
     }
   };
-  // the moved rows: LM lanes per row add strided chunk sums (FEW), a butterfly
-  // combines them
-  constexpr int LM = FEW ? 16 : 1;
-  for (int k0 = 0; k0 < s.nmove; k0 += kBlock / LM) {
-    const int k = k0 + tid / LM, gl = tid % LM;
-    const bool in = k < s.nmove;
-    double a = 0.0, b = 0.0;
-    if (FEW) {
-      for (int c = gl; in && c < s.nchunk; c += LM) {
-        a += s.mpart[((int64_t)c * s.nmove + k) * 2 + 0];
-        b += s.mpart[((int64_t)c * s.nmove + k) * 2 + 1];
-      }
-      for (int o = LM / 2; o > 0; o >>= 1) {
-        a += __shfl_xor(a, o);
-        b += __shfl_xor(b, o);
-      }
-    } else if (in) {
-      a = s.mrow[(int64_t)k * 2 + 0];
-      b = s.mrow[(int64_t)k * 2 + 1];
-    }
-    if (in && gl == 0) {
-      const int64_t j = s.idx[k];
-      bool bad = j < 0 || j >= s.n || (k > 0 && s.idx[k - 1] >= j);
+  for (int k = tid; k < s.nmove; k += kBlock) {
+    const int64_t j = s.idx[k];
+    bool bad = j < 0 || j >= s.n || (k > 0 && s.idx[k - 1] >= j);
 #pragma unroll
-      for (int q = 0; q < D; ++q) bad = bad || !isfinite(s.xnew[(int64_t)k * D + q]);
-      if (bad) atomicOr(&s_bad, 1);
-      else settle_row((int)j, a, b);
-    }
+    for (int q = 0; q < D; ++q) bad = bad || !isfinite(s.xnew[(int64_t)k * D + q]);
+    if (bad) atomicOr(&s_bad, 1);
+    else settle_row((int)j, s.mrow[(int64_t)k * 2 + 0], s.mrow[(int64_t)k * 2 + 1]);
   }
-  if constexpr (FEW) {
-    __shared__ int s_scan[kBlock];
-    __shared__ int s_wtot[kBlock / 64];
-    __shared__ double s_exptab[kExpTab];
-    int own, lo, hi;
-    const Listed L = listed_rows(s, s_scan, s_wtot, own, lo, hi);
-    if (L.cnt > 0) {
-      fill_exp_table(s_exptab);
-      __syncthreads();
-      for (int e = 0; e < L.cnt; ++e) {
-        const int r = listed_row(s, L, e);
-        double ab[2];
-        listed_sums<D>(s, r, 0, s.n, s_exptab, ab);
-        block_sum_n(ab, sh);
-        if (tid == 0) settle_row(r, ab[0], ab[1]);
-      }
+  const int cnt = s.state[1];
+  const int segs = segs_for(cnt, s.n);
+  // G lanes per listed row (segs / 4, at most a wave): they add strided
+  // segments, a butterfly within the group combines them (the same fixed
+  // order every time).  Many listed rows (G small) run side by side.
+  const int G = min(64, segs / 4);
+  const int grp = tid / G, gl = tid % G;
+  for (int e = grp; e < cnt; e += kBlock / G) {
+    double a = 0.0, b = 0.0;
+    for (int sg = gl; sg < segs; sg += G) {
+      a += s.part[((int64_t)e * segs + sg) * 2 + 0];
+      b += s.part[((int64_t)e * segs + sg) * 2 + 1];
     }
-  } else {
-    const int cnt = s.state[1];
-    const int segs = segs_for(cnt, s.n);
-    // G lanes per listed row (segs / 4, at most a wave): they add strided
-    // segments, a butterfly within the group combines them (the same fixed
-    // order every time).  Many listed rows (G small) run side by side.
-    const int G = min(64, segs / 4);
-    const int grp = tid / G, gl = tid % G;
-    for (int e = grp; e < cnt; e += kBlock / G) {
-      double a = 0.0, b = 0.0;
-      for (int sg = gl; sg < segs; sg += G) {
-        a += s.part[((int64_t)e * segs + sg) * 2 + 0];
-        b += s.part[((int64_t)e * segs + sg) * 2 + 1];
-      }
-      for (int o = G / 2; o > 0; o >>= 1) {
-        a += __shfl_xor(a, o);
-        b += __shfl_xor(b, o);
-      }
-      if (gl == 0) settle_row(s.list[e], a, b);
+    for (int o = G / 2; o > 0; o >>= 1) {
+      a += __shfl_xor(a, o);
+      b += __shfl_xor(b, o);
     }
+    if (gl == 0) settle_row(s.list[e], a, b);
   }
   for (int b = tid; b < s.nrb; b += kBlock) acc += s.bpart[b];
   const double tot = block_sum(acc, sh);   // also orders the LDS writes above
@@ -729,12 +687,8 @@ static void launch(const Step& s, hipStream_t st) {
   const int nset = (s.n + kBlock - 1) / kBlock;
   if (s.nmove >= kManyMoved) k_mwg_rows<D, kRowLanesMany><<<grid, kBlock, 0, st>>>(s);
   else k_mwg_rows<D, 1><<<grid, kBlock, 0, st>>>(s);
-  if (s.n <= kFewEvents && s.nmove < kManyMoved) {
-    k_mwg_settle<D, true><<<nset, kBlock, 0, st>>>(s);
-  } else {
-    k_mwg_exact<D><<<kExactGrid + (s.nmove + kMergeRows - 1) / kMergeRows, kBlock, 0, st>>>(s);
-    k_mwg_settle<D, false><<<nset, kBlock, 0, st>>>(s);
-  }
+  k_mwg_exact<D><<<kExactGrid + (s.nmove + kMergeRows - 1) / kMergeRows, kBlock, 0, st>>>(s);
+  k_mwg_settle<D><<<nset, kBlock, 0, st>>>(s);
 }
 
 }  // namespace mwg

@@ -310,3 +310,49 @@ def test_mwg_moved_row_sums(n, nmove):
     partners at a time and one (99 and 132 workgroups), and last partner chunks
     of 8 and of 1, whose second partner is missing."""
     test_mwg_block_sizes(n, 2, nmove)
+
+
+@pytest.mark.parametrize("n,next_day", [(2925, 3), (2925, 300), (8192, 8191)])
+def test_mwg_many_rows_that_lose_their_one_source(n, next_day):
+    """Whole-day times: the first event, alone on its day, excites the
+    `next_day` events of the next one, which excite each other no more than
+    equal times allow.  It moves away, so all of their rows are recomputed
+    exactly.  Delta ell and the terms after 1, 7 and 8 moved events, and the
+    steps of few moved events cost what those of eight do (the same rows to
+    recompute: within a factor of 3, where every workgroup recomputing all of
+    them took 20 to 60)."""
+    import torch
+    from paper_2010_02994_amd import api
+    rng = np.random.default_rng(n + next_day)
+    x = 0.5 * rng.standard_normal((n, 2))
+    t = np.concatenate([[0.0], np.full(next_day, 1.0), 2.0 + np.sort(np.floor(rng.uniform(0, 300, n - 1 - next_day)))])
+    p = np.array([0.5, 1.0, 5.0, 0.4, 0.2, 1.0])
+    _, ll0, _, _ = oracle.loglik_grad(x, t, p, threads=True, want_grad_x=False)
+    us = {}
+    for nmove in (1, 7, 8):
+        idx = np.concatenate([[0], np.arange(n - nmove + 1, n)]).astype(np.int64)
+        x1 = x.copy()
+        x1[0] += 5.0   # excitation and background there: e^-25 of those at its old place
+        xd, td = _dev(x), _dev(t)
+        terms, _ = api.event_terms(xd, td, p, prec="fp64")
+        i_, x_, never = _dev(idx), _dev(x1[idx]), _dev(np.array([np.inf]))
+        say(f"case mwg listed rows n={n} next_day={next_day} nmove={nmove}")
+        times = []
+        for _ in range(5):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            for _ in range(4):
+                api.mwg_step(xd, td, p, terms, i_, x_, never)
+            b.record()
+            b.synchronize()
+            times.append(a.elapsed_time(b) * 250.0)
+        us[nmove] = min(times)
+        out = api.mwg_step(xd, td, p, terms, i_, x_, _dev(np.array([-np.inf]))).cpu().numpy()
+        _, ll1, _, _ = oracle.loglik_grad(x1, t, p, threads=True, want_grad_x=False)
+        assert out[1] == 1.0 and out[2] == 0.0
+        # the two log-likelihoods round to ~1e-13 of their size each
+        assert abs(out[0] - (ll1 - ll0)) <= 1e-10 * max(abs(ll0), abs(ll1))
+        assert np.array_equal(xd.cpu().numpy(), x1)
+        _check_terms(terms.cpu().numpy(), oracle.event_terms(x1, t, p), "fp64", p, f"listed nmove{nmove}")
+    say(f"  us a step: {us}")
+    assert us[1] <= 3.0 * us[8] and us[7] <= 3.0 * us[8]
