@@ -77,7 +77,14 @@ typedef enum {
 } hawkes_status_t;
 
 /* Device workspace needed by hawkes_loglik / hawkes_grad for (n, d, prec).
- * Returns 0 for invalid (n, d, prec).  Layout is private to the library. */
+ * Returns 0 for invalid (n, d, prec).  Layout is private to the library.  The
+ * size is not monotone in n (the work items, whose partial sums are most of it,
+ * change with n): a program that keeps one buffer for several n takes the
+ * largest of their sizes, or relies on this: a call whose workspace is smaller
+ * takes larger work items where these fit, so a buffer for some n serves every
+ * smaller n.  Such a call's float64 partial sums are grouped otherwise (its
+ * results differ in the last digits), and hawkes_diagnostics on it takes the
+ * call's own ws_bytes. */
 size_t hawkes_workspace_bytes(int64_t n, int d, int prec);
 
 /* Log-likelihood only (rate pass, finalize).  loglik is a host pointer.

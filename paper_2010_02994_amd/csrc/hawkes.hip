@@ -133,23 +133,29 @@ static void layout_with(int64_t n, int d, int base, bool cull, int L, Layout& Lo
 }
 
 // Small items cost row partials (N = 10,000, D = 2: 49 MB of workspace with one tile
-// per item, 28 with four), so a workspace that would pass `room` takes larger items,
-// up to four tiles, if it then fits.  Every call of up to kScratchEvents events has the
-// static scratch of hawkes_grad_noalloc for room, so that it serves the sizes that four
-// tiles per item allow (all N <= 17,920 up to D = 3, 15,872 at D = 6) with the results of
-// hawkes_grad.  Beyond, the items stay as measured best (N = 20,000, D = 2 would fit
-// with four tiles per item at 300 us against 284).
+// per item, 28 with four), so a workspace of `room` bytes that the items of tiles_per_item
+// do not fit takes larger ones, if these fit (up to four tiles, or one more than usual): a
+// buffer that the caller sized for other calls, or a server's arena.  Every call of up to kScratchEvents events
+// also has the static scratch of hawkes_grad_noalloc for room, so that it serves the sizes
+// that four tiles per item allow with the results of hawkes_grad.
 constexpr int64_t kScratchEvents = 17920;
+constexpr int kMaxSmallItem = 4;
 bool make_layout(int64_t n, int d, int prec, Layout& Lo, size_t room) {
   const int base = prec & ~HAWKES_CULL;
   const bool cull = (prec & HAWKES_CULL) != 0;
   if (n < 2 || n > (int64_t(1) << 30) || d < 1 || d > kMaxD || (base != HAWKES_FP64 && base != HAWKES_MIXED))
     return false;
-  if (room == 0) room = n <= kScratchEvents ? (size_t)HAWKES_NOALLOC_SCRATCH_BYTES : SIZE_MAX;
-  const int L = tiles_per_item(n);
-  layout_with(n, d, base, cull, L, Lo);
-  for (int k = L + 1; Lo.total > room && k <= 4; ++k) layout_with(n, d, base, cull, k, Lo);
-  if (Lo.total > room && Lo.L != L) layout_with(n, d, base, cull, L, Lo);
+  const int usual = tiles_per_item(n), most = std::max(kMaxSmallItem, usual + 1);
+  layout_with(n, d, base, cull, usual, Lo);
+  const auto fit = [&](size_t bytes) {
+    Layout larger;
+    for (int k = Lo.L + 1; Lo.total > bytes && k <= most; ++k) {
+      layout_with(n, d, base, cull, k, larger);
+      if (larger.total <= bytes) Lo = larger;
+    }
+  };
+  if (n <= kScratchEvents) fit(HAWKES_NOALLOC_SCRATCH_BYTES);
+  fit(room);
   return true;
 }
 
@@ -440,7 +446,7 @@ BatchGrid assign_blocks(ReqDesc* descs, int nreq) {
 static int check_args(const double* x, const double* t, int64_t n, int d, const hawkes_params_t* p, int prec,
                       void* ws, size_t ws_bytes, Layout& Lo) {
   if (!x || !t || !p || !ws) return HAWKES_EINVAL;
-  if (!make_layout(n, d, prec, Lo)) return HAWKES_EINVAL;
+  if (!make_layout(n, d, prec, Lo, ws_bytes)) return HAWKES_EINVAL;
   if (ws_bytes < Lo.total) return HAWKES_EINVAL;
   if (!valid_params(p)) return HAWKES_EPARAM;
   return HAWKES_OK;
@@ -465,7 +471,7 @@ int run_async(const double* x, const double* t, int64_t n, int d, const hawkes_p
 int run_sync(const double* x, const double* t, int64_t n, int d, const hawkes_params_t* p, int prec, void* ws,
              size_t ws_bytes, void* stream, double* loglik, double* grad_x, double* grad_params, double* terms) {
   Layout Lo;
-  if (!ws || !make_layout(n, d, prec, Lo)) return HAWKES_EINVAL;
+  if (!ws || !make_layout(n, d, prec, Lo, ws_bytes)) return HAWKES_EINVAL;
   double* out8 = at<double>(ws, Lo.off_out8);
   // gradient calls take the scalars from a pinned buffer that their last
   // kernel writes (none is created while allocation is barred)
@@ -551,7 +557,8 @@ const char* hawkes_version(void) { return "0.1.0"; }
 int hawkes_diagnostics(const void* ws, size_t ws_bytes, int64_t n, int d, int prec, const hawkes_params_t* p,
                        void* stream, int32_t* flags, hawkes_diag_t* out) {
   hawkes::Layout Lo;
-  if (!ws || !p || !out || !hawkes::make_layout(n, d, prec, Lo) || ws_bytes < Lo.total) return HAWKES_EINVAL;
+  if (!ws || !p || !out || !hawkes::make_layout(n, d, prec, Lo, ws_bytes) || ws_bytes < Lo.total)
+    return HAWKES_EINVAL;
   if (!hawkes::valid_params(p)) return HAWKES_EPARAM;
   const hawkes::KParams kp = hawkes::make_kparams(Lo, p);
   hipStream_t s = static_cast<hipStream_t>(stream);

@@ -26,8 +26,10 @@ struct BatchGrid {
   int red_blocks;  // blocks of a reduction launch
 };
 
-// room: bytes the workspace should fit (0: the library's rule).
-bool make_layout(int64_t n, int d, int prec, Layout& Lo, size_t room = 0);
+// The layout of a call whose workspace has `room` bytes: by default the one that
+// hawkes_workspace_bytes describes, or, where that does not fit, one of larger work items
+// that does, if any (else Lo.total > room).
+bool make_layout(int64_t n, int d, int prec, Layout& Lo, size_t room = SIZE_MAX);
 bool valid_params(const hawkes_params_t* p);
 KParams make_kparams(const Layout& Lo, const hawkes_params_t* p);
 ReqDesc make_desc(const Layout& Lo, const KParams& kp, const double* x, const double* t, void* ws, double* out8,

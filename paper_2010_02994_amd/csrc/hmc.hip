@@ -222,8 +222,8 @@ static int leapfrog(double* x, double* p, const double* t, int64_t n, int d, con
   if (steps < 1 || !std::isfinite(eps) || !(eps > 0.0)) return HAWKES_EINVAL;
   if (bound != HAWKES_BOUND_NONE && bound != HAWKES_BOUND_BOX && bound != HAWKES_BOUND_DISC) return HAWKES_EINVAL;
   if (bound != HAWKES_BOUND_NONE && (!b0 || !b1)) return HAWKES_EINVAL;
-  const size_t need = hawkes_workspace_bytes(n, d, prec);
-  if (need == 0 || ws_bytes < need) return HAWKES_EINVAL;
+  Layout Lo;
+  if (!make_layout(n, d, prec, Lo, ws_bytes) || ws_bytes < Lo.total) return HAWKES_EINVAL;
   if (!valid_params(prm)) return HAWKES_EPARAM;
   if (mds) {
     if (!mds->delta || !mds->ws || !mds->out4) return HAWKES_EINVAL;

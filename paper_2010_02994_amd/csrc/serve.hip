@@ -171,9 +171,7 @@ size_t footprint(int64_t n, int d, int prec) { return whole_pages(hawkes_workspa
 // A request's layout: the direct calls' unless the arena cannot hold that, then the
 // larger work items that it can hold, if any (a request that fits neither is refused).
 bool request_layout(hawkes_server* S, const Dataset& ds, int prec, Layout& Lo) {
-  const size_t cap = S->arena.capacity() & ~size_t(4095);
-  if (!make_layout(ds.n, ds.d, prec, Lo)) return false;
-  return Lo.total <= cap || make_layout(ds.n, ds.d, prec, Lo, cap);
+  return make_layout(ds.n, ds.d, prec, Lo, S->arena.capacity() & ~size_t(4095));
 }
 
 void finish(hawkes_server* S, Request* r, int status, const double* out8) {

@@ -62,3 +62,81 @@ def test_larger_items_give_the_same_results(n, d, prec):
     tol = 16 * n * 2.0 ** -53
     assert abs(r["loglik"] - ll) <= tol * max(abs(ll), n)
     assert float((g3 - gx).abs().max()) <= tol * float(gx.abs().max())
+
+
+def _accepts(n, d, prec, ws_bytes):
+    """Whether calls take a workspace of ws_bytes: parameters outside their
+    domain are refused after the workspace's size and before any pointer is
+    used, so nothing runs."""
+    L = _lib.lib()
+    bad = _lib.HawkesParams(-1.0, 1.0, 1.0, 0.3, 1.0, 0.5)
+    p8 = ctypes.c_void_p(8)
+    st = {L.hawkes_grad_async(p8, p8, n, d, ctypes.byref(bad), PREC[prec], p8, ws_bytes, None, p8, p8),
+          L.hawkes_leapfrog(p8, p8, p8, n, d, ctypes.byref(bad), PREC[prec], 0.1, 1, 0, None, None, p8, ws_bytes, None, p8, 0,
+                            p8)}
+    assert st <= {_lib.EPARAM, _lib.EINVAL} and len(st) == 1
+    return st == {_lib.EPARAM}
+
+
+@pytest.mark.parametrize("prec", ["fp64", "mixed"])
+@pytest.mark.parametrize("n,d,ws_bytes", [(4733, 6, 12_000_000), (8000, 2, 19_200_000), (10000, 2, 27_000_000),
+                                          (11700, 2, 33_800_000), (20000, 2, 83_300_000)])
+def test_small_workspaces_are_accepted(n, d, ws_bytes, prec):
+    """Buffers of the size that four tiles per work item take, smaller than the
+    usual items' workspace; and one too small for any items is refused."""
+    assert _lib.lib().hawkes_workspace_bytes(n, d, PREC[prec]) > ws_bytes
+    assert _accepts(n, d, prec, ws_bytes)
+    assert not _accepts(n, d, prec, ws_bytes // 2)
+
+
+@pytest.mark.parametrize("prec", ["fp64", "mixed"])
+def test_a_workspace_serves_every_smaller_call(prec):
+    rng = np.random.default_rng(7)
+    for d in (1, 2, 6):
+        ns = np.unique((10.0 ** rng.uniform(0.5, 5.2, 60)).astype(int))
+        for k in range(1, len(ns)):
+            n = int(ns[k])
+            room = _lib.lib().hawkes_workspace_bytes(n, d, PREC[prec])
+            for m in {int(ns[k - 1]), int(ns[rng.integers(0, k)]), n - 1}:
+                assert _accepts(m, d, prec, room), (m, n, d)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("prec", ["fp64", "mixed"])
+def test_a_larger_calls_workspace_is_reused(prec):
+    """A buffer sized for n = 13,000 at n = 11,700, whose usual workspace is
+    larger: gradient, per-event terms, diagnostics and a trajectory, against
+    the same calls with the usual workspace (tolerance as above)."""
+    import torch
+    from paper_2010_02994_amd import api
+    n, d = 11700, 2
+    w = W.random_case(93, n, d, ties=2, t_span=60.0)
+    w.x[5] += 60.0   # its rate lies below both precisions' windows
+    x, t = torch.tensor(w.x, device="cuda:0"), torch.tensor(w.t, device="cuda:0")
+    L, ps, p = _lib.lib(), api.params_struct(w.params), api._prec(prec)
+    say(f"case reused workspace prec={prec}")
+    res = []
+    for size in (L.hawkes_workspace_bytes(13000, d, p), L.hawkes_workspace_bytes(n, d, p)):
+        ws = torch.empty(size, dtype=torch.uint8, device="cuda:0")
+        st = api._stream_ptr(x.device)
+        gx, terms, ll, gp = torch.empty_like(x), torch.empty((n, 4), dtype=x.dtype, device=x.device), ctypes.c_double(), (ctypes.c_double * 6)()
+        assert L.hawkes_grad(x.data_ptr(), t.data_ptr(), n, d, ctypes.byref(ps), p, ws.data_ptr(), size, st,
+                             ctypes.byref(ll), gx.data_ptr(), gp) == _lib.OK
+        diag, flags = _lib.HawkesDiag(), torch.zeros(n, dtype=torch.int32, device="cuda:0")
+        assert L.hawkes_diagnostics(ws.data_ptr(), size, n, d, p, ctypes.byref(ps), st, flags.data_ptr(),
+                                    ctypes.byref(diag)) == _lib.OK
+        assert L.hawkes_event_terms(x.data_ptr(), t.data_ptr(), n, d, ctypes.byref(ps), p, ws.data_ptr(), size, st,
+                                    terms.data_ptr(), None) == _lib.OK
+        xt, mom, g2, out8 = x.clone(), torch.zeros_like(x), torch.empty_like(x), torch.empty(8, dtype=x.dtype, device=x.device)
+        assert L.hawkes_leapfrog(xt.data_ptr(), mom.data_ptr(), t.data_ptr(), n, d, ctypes.byref(ps), p, 1e-3, 1, 0, None,
+                                 None, ws.data_ptr(), size, st, g2.data_ptr(), 0, out8.data_ptr()) == _lib.OK
+        torch.cuda.synchronize()
+        res.append((ll.value, gx, np.array(gp[:]), diag.flagged_rows, flags, terms, out8[0].item(), g2))
+    a, b = res
+    assert L.hawkes_workspace_bytes(13000, d, p) < L.hawkes_workspace_bytes(n, d, p)
+    tol = 16 * n * 2.0 ** -53
+    assert abs(a[0] - b[0]) <= tol * max(abs(b[0]), n) and abs(a[6] - b[6]) <= tol * max(abs(b[6]), n)
+    for q in (1, 5, 7):
+        assert float((a[q] - b[q]).abs().max()) <= tol * float(b[q].abs().max())
+    assert np.allclose(a[2], b[2], rtol=1e-9)
+    assert a[3] == b[3] == 1 and torch.equal(a[4], b[4])
