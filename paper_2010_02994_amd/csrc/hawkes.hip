@@ -51,11 +51,13 @@ static int fine_bands(int64_t n, int nb, int L) {
   return b;
 }
 
+// HAWKES_TILES_PER_ITEM: tiles per item as given, whatever room there is (0: unset).
+static int tiles_per_item_env() {
+  const char* e = std::getenv("HAWKES_TILES_PER_ITEM");
+  return e ? std::max(0, std::atoi(e)) : 0;
+}
+
 static int tiles_per_item(int64_t n) {
-  if (const char* e = std::getenv("HAWKES_TILES_PER_ITEM")) {
-    const int v = std::atoi(e);
-    if (v > 0) return v;
-  }
   const int nb = (int)((n + kBandRows - 1) / kBandRows);
   int64_t tiles = 0;
   for (int b = 0; b < nb; ++b) tiles += (std::min<int64_t>(n, (int64_t)(b + 1) * kBandRows) + kTile - 1) / kTile;
@@ -145,6 +147,10 @@ bool make_layout(int64_t n, int d, int prec, Layout& Lo, size_t room) {
   const bool cull = (prec & HAWKES_CULL) != 0;
   if (n < 2 || n > (int64_t(1) << 30) || d < 1 || d > kMaxD || (base != HAWKES_FP64 && base != HAWKES_MIXED))
     return false;
+  if (const int given = tiles_per_item_env()) {
+    layout_with(n, d, base, cull, given, Lo);
+    return true;
+  }
   const int usual = tiles_per_item(n), most = std::max(kMaxSmallItem, usual + 1);
   layout_with(n, d, base, cull, usual, Lo);
   const auto fit = [&](size_t bytes) {

@@ -140,3 +140,18 @@ def test_a_larger_calls_workspace_is_reused(prec):
         assert float((a[q] - b[q]).abs().max()) <= tol * float(b[q].abs().max())
     assert np.allclose(a[2], b[2], rtol=1e-9)
     assert a[3] == b[3] == 1 and torch.equal(a[4], b[4])
+
+
+def test_given_items_are_kept(monkeypatch):
+    """HAWKES_TILES_PER_ITEM fixes the items, also where they pass the static
+    scratch or the workspace at hand."""
+    size = _lib.lib().hawkes_workspace_bytes
+    usual = size(15000, 2, _lib.MIXED)
+    monkeypatch.setenv("HAWKES_TILES_PER_ITEM", "1")
+    one = size(15000, 2, _lib.MIXED)
+    assert one > 64 << 20 > usual
+    assert _accepts(15000, 2, "mixed", one) and not _accepts(15000, 2, "mixed", usual)
+    monkeypatch.setenv("HAWKES_TILES_PER_ITEM", "2")
+    assert size(15000, 2, _lib.MIXED) == usual
+    monkeypatch.setenv("HAWKES_TILES_PER_ITEM", "0")
+    assert size(15000, 2, _lib.MIXED) == usual
