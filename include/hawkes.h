@@ -318,8 +318,8 @@ int hawkes_leapfrog_bmds(double* x /* device, n*d */, double* p /* device, n*d *
  * of several HIP streams, so batches overlap on the device and requests that
  * arrive meanwhile are admitted as slots and memory free up.  A request's
  * result is bitwise identical whether it runs alone or in any batch (and that
- * of the direct call, unless only a workspace of larger work items, whose
- * float64 partial sums are grouped otherwise, fits in the arena).
+ * of the direct call, unless the arena holds fewer than two such requests and
+ * takes larger work items, whose float64 partial sums are grouped otherwise).
  *
  * Threading: every call may come from any host thread.  x and grad_x stay
  * owned by the client and must stay alive until the request completes.
@@ -346,7 +346,8 @@ typedef struct {
  * after a virtual delay with loglik 0), for testing admission and queueing. */
 #define HAWKES_SERVE_SIMULATE 0x100
 
-/* Device bytes one admitted request of (n, d, prec) holds (0 if invalid). */
+/* Device bytes one admitted request of (n, d, prec) holds (0 if invalid), or
+ * fewer in an arena of less than twice that size (larger work items). */
 size_t hawkes_serve_footprint(int64_t n, int d, int prec);
 
 /* Create a server (allocates the arena, streams and pinned staging).

@@ -141,7 +141,6 @@ static void layout_with(int64_t n, int d, int base, bool cull, int L, Layout& Lo
 // also has the static scratch of hawkes_grad_noalloc for room, so that it serves the sizes
 // that four tiles per item allow with the results of hawkes_grad.
 constexpr int64_t kScratchEvents = 17920;
-constexpr int kMaxSmallItem = 4;
 bool make_layout(int64_t n, int d, int prec, Layout& Lo, size_t room) {
   const int base = prec & ~HAWKES_CULL;
   const bool cull = (prec & HAWKES_CULL) != 0;

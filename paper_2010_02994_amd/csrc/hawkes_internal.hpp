@@ -26,6 +26,8 @@ struct BatchGrid {
   int red_blocks;  // blocks of a reduction launch
 };
 
+// Tiles that the work items of small calls are enlarged to where the workspace is short.
+constexpr int kMaxSmallItem = 4;
 // The layout of a call whose workspace has `room` bytes: by default the one that
 // hawkes_workspace_bytes describes, or, where that does not fit, one of larger work items
 // that does, if any (else Lo.total > room).

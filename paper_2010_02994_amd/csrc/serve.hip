@@ -99,7 +99,7 @@ struct Request {
   int prec = 0;
   double* grad_x = nullptr;
   size_t foot = 0, off = 0;
-  int split = 1;         // step groups of its pair passes (Layout::split)
+  Layout lo;             // of its workspace
   bool admitted = false, done = false;
   hawkes_result_t res{};
 };
@@ -168,10 +168,25 @@ void dev_free(hawkes_server* S, void* p) {
 size_t whole_pages(size_t bytes) { return (bytes + 4095) & ~size_t(4095); }
 size_t footprint(int64_t n, int d, int prec) { return whole_pages(hawkes_workspace_bytes(n, d, prec)); }
 
-// A request's layout: the direct calls' unless the arena cannot hold that, then the
-// larger work items that it can hold, if any (a request that fits neither is refused).
-bool request_layout(hawkes_server* S, const Dataset& ds, int prec, Layout& Lo) {
-  return make_layout(ds.n, ds.d, prec, Lo, S->arena.capacity() & ~size_t(4095));
+// A request's layout: the direct calls', or, in an arena that cannot hold two such requests,
+// the one of larger work items (up to four tiles) of which it holds most: an arena of 60 MB
+// holds one request of N = 10,000, D = 2 with the usual items (49 MB) and two with four
+// tiles per item (25 MB).  A request that fits in neither form is refused.  The choice
+// depends on the server and the request's size and precision only, never on the load, so
+// neither do a request's results.
+bool request_layout(const hawkes_server* S, const Dataset& ds, int prec, Layout& Lo) {
+  const size_t cap = S->arena.capacity() & ~size_t(4095);
+  if (!make_layout(ds.n, ds.d, prec, Lo)) return false;
+  if (cap / whole_pages(Lo.total) >= 2) return true;
+  make_layout(ds.n, ds.d, prec, Lo, cap);
+  for (size_t held = cap / whole_pages(Lo.total) + 1; held <= (size_t)S->max_slots; ++held) {
+    const size_t room = (cap / held) & ~size_t(4095);
+    Layout larger;
+    make_layout(ds.n, ds.d, prec, larger, room);
+    if (larger.L > kMaxSmallItem || larger.total > room) break;
+    Lo = larger;
+  }
+  return true;
 }
 
 void finish(hawkes_server* S, Request* r, int status, const double* out8) {
@@ -228,8 +243,8 @@ int size_band(int64_t n) {
 
 // Admit from the FIFO into free batch slots and launch.  The head request
 // decides the batch's class (D, precision, with or without a location
-// gradient, size band); later requests of another class wait for a later
-// batch.  D, precision and the gradient flag fix which kernels run, so a
+// gradient, size band, step groups); later requests of another class wait for a
+// later batch.  All but the size band fix which kernels run, so a
 // request's arithmetic is the same alone, in any batch and through the direct
 // calls.  A head request that does not fit in memory blocks admission until
 // memory frees up (no overtaking by smaller requests of its class), which
@@ -245,9 +260,9 @@ bool admit_and_launch(hawkes_server* S) {
       Request* r = *it;
       const Dataset& ds = S->datasets[r->ds];
       if (S->active >= S->max_slots) break;
-      if (cls_d < 0) { cls_d = ds.d; cls_p = r->prec; cls_g = r->grad_x != nullptr; cls_b = size_band(ds.n); cls_s = r->split; }
+      if (cls_d < 0) { cls_d = ds.d; cls_p = r->prec; cls_g = r->grad_x != nullptr; cls_b = size_band(ds.n); cls_s = r->lo.split; }
       if (ds.d != cls_d || r->prec != cls_p || (r->grad_x != nullptr) != cls_g || size_band(ds.n) != cls_b ||
-          r->split != cls_s) {
+          r->lo.split != cls_s) {
         ++it;
         continue;
       }
@@ -283,10 +298,8 @@ bool admit_and_launch(hawkes_server* S) {
       for (int k = 0; k < b.nreq; ++k) {
         Request* r = take[k];
         const Dataset& ds = S->datasets[r->ds];
-        Layout Lo;
-        request_layout(S, ds, r->prec, Lo);
-        const KParams kp = make_kparams(Lo, &r->p);
-        b.host_desc[k] = make_desc(Lo, kp, r->x, ds.t, S->arena_base + r->off, b.dev_out + 8 * k, r->grad_x);
+        const KParams kp = make_kparams(r->lo, &r->p);
+        b.host_desc[k] = make_desc(r->lo, kp, r->x, ds.t, S->arena_base + r->off, b.dev_out + 8 * k, r->grad_x);
         grad = grad || r->grad_x != nullptr;
       }
       const BatchGrid g = assign_blocks(b.host_desc, b.nreq);
@@ -452,7 +465,7 @@ int hawkes_serve_submit(hawkes_server_t* S, int32_t dataset_id, const double* x,
   r->prec = prec;
   r->grad_x = grad_x;
   r->foot = foot;
-  r->split = Lo.split;
+  r->lo = Lo;
   r->res.status = HAWKES_EPENDING;
   r->res.t_submit_ns = now_ns();
   S->pending.push_back(r);

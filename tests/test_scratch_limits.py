@@ -155,3 +155,18 @@ def test_given_items_are_kept(monkeypatch):
     assert size(15000, 2, _lib.MIXED) == usual
     monkeypatch.setenv("HAWKES_TILES_PER_ITEM", "0")
     assert size(15000, 2, _lib.MIXED) == usual
+
+
+@pytest.mark.parametrize("n,d,arena,together", [(10000, 2, 54 << 20, 2), (8000, 2, 57 << 20, 3), (11700, 2, 97 << 20, 3)])
+def test_small_arena_holds_several_requests(n, d, arena, together):
+    """Requests whose larger items fit the arena beside each other run beside
+    each other (each takes 60 us or more of virtual time; with room for one, no
+    request is admitted before the one before it is done)."""
+    assert arena // Server.footprint(n, d, "mixed") < together
+    with Server(hbm_budget_bytes=arena, max_slots=8, streams=4, simulate=True) as s:
+        ds = s.register(1, d, n=n)
+        res = [s.wait(tk, 10) for tk in [s.submit(ds, 1, P) for _ in range(24)]]
+        assert all(r["status"] == 0 for r in res)
+        assert s.stats()["arena_free_bytes"] == s.stats()["arena_bytes"]
+    ev = sorted([(r["t_admit_ns"], 1) for r in res] + [(r["t_done_ns"], -1) for r in res])
+    assert max(np.cumsum([k for _, k in ev])) >= together
