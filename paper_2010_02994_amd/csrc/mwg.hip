@@ -46,6 +46,7 @@ struct Step {
   int n, nmove;         // events, moved events
   int nrb, rows;        // row blocks and rows per block
   int nchunk, chunk;    // partner chunks of the moved rows' sums and partners per chunk
+  int64_t npart;        // segment sums that part holds
   double* terms;        // n x 4 cached state
   const int64_t* idx;   // nmove moved events, strictly increasing
   const double* xnew;   // nmove x D proposed locations
@@ -60,9 +61,10 @@ struct Step {
   int* bcount;          // nrb: rows of the block needing an exact recompute
   int* stage;           // nrb x rows: those rows in index order
   int* list;            // n: all of them in index order
-  double* part;         // listed rows' segment sums (a, b), n x kSeg x 2 at most
-  double* mpart;        // nchunk x nmove x 2: moved rows' chunk sums (at most n x kSeg x 2)
-  double* mrow;         // nmove x 2: moved rows' sums
+  // one buffer of shared_pairs(n) pairs (a, b), about n x kSeg:
+  double* mrow;         // nmove: moved rows' sums
+  double* mpart;        // nchunk x nmove: their chunk sums (at most n x kSeg / 2)
+  double* part;         // npart: listed rows' segment sums
   int* state;           // [accepted, list length]
 };
 
@@ -382,12 +384,13 @@ __global__ void __launch_bounds__(kBlock) k_mwg_rows(Step s) {
 }
 
 // Partner segments per listed row: kSeg, or more when few rows are listed so
-// that the tasks still spread over the grid (never more partials than the
-// workspace holds: kSeg per event).
-__device__ __forceinline__ int segs_for(int cnt, int n) {
+// that the tasks still spread over the grid, or fewer when most rows are listed
+// and a large block's chunk sums take their part of the workspace (listed and
+// moved rows are n at most together, so eight segments always fit).
+__device__ __forceinline__ int segs_for(int cnt, const Step& s) {
   int segs = kSeg;
-  while (segs < kMaxSeg && (int64_t)cnt * segs * 2 <= kExactGrid && (int64_t)cnt * segs * 2 <= (int64_t)n * kSeg)
-    segs *= 2;
+  while (segs > 8 && (int64_t)cnt * segs > s.npart) segs /= 2;
+  while (segs < kMaxSeg && (int64_t)cnt * segs * 2 <= kExactGrid && (int64_t)cnt * segs * 2 <= s.npart) segs *= 2;
   return segs;
 }
 
@@ -513,7 +516,7 @@ __global__ void __launch_bounds__(kBlock) k_mwg_exact(Step s) {
   if (L.cnt == 0) return;
   fill_exp_table(s_exptab);
   __syncthreads();
-  const int segs = segs_for(L.cnt, s.n);
+  const int segs = segs_for(L.cnt, s);
   const int seg = (s.n + segs - 1) / segs;
   for (int64_t task = blockIdx.x; task < (int64_t)L.cnt * segs; task += kExactGrid) {
     const int e = (int)(task / segs), sg = (int)(task % segs);
@@ -567,7 +570,7 @@ __global__ void __launch_bounds__(kBlock) k_mwg_settle(Step s) {
     else settle_row((int)j, s.mrow[(int64_t)k * 2 + 0], s.mrow[(int64_t)k * 2 + 1]);
   }
   const int cnt = s.state[1];
-  const int segs = segs_for(cnt, s.n);
+  const int segs = segs_for(cnt, s);
   // G lanes per listed row (segs / 4, at most a wave): they add strided
   // segments, a butterfly within the group combines them (the same fixed
   // order every time).  Many listed rows (G small) run side by side.
@@ -656,9 +659,14 @@ static Model make_model(const hawkes_params_t* p, int d) {
 
 static size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
 
+// Pairs of the buffer that moved and listed rows share.  (Less n / 32 where the counts of
+// 64-row blocks take more than those of 256-row blocks: the workspace's size stays below
+// 32 segments a row and 256-row blocks.)
+static int64_t shared_pairs(int64_t n) { return kSeg * n - (n > 2048 ? n / 32 : 0); }
+
 // Workspace pieces for n events, in order.
 struct Pieces {
-  size_t new_a, new_b, dlog, flag, bpart, bcount, stage, list, part, mpart, mrow, state, total;
+  size_t new_a, new_b, dlog, flag, bpart, bcount, stage, list, part, state, total;
 };
 static Pieces pieces(int64_t n) {
   const size_t nrb = (size_t)((n + kBlock / kRowLanesMany - 1) / (kBlock / kRowLanesMany));
@@ -671,11 +679,9 @@ static Pieces pieces(int64_t n) {
   p.flag = take(sizeof(int) * (size_t)n);
   p.bpart = take(sizeof(double) * nrb);
   p.bcount = take(sizeof(int) * nrb);
-  p.stage = take(sizeof(int) * (size_t)(n + kBlock));
+  p.stage = take(sizeof(int) * (size_t)((n + kBlock - 1) / kBlock * kBlock));
   p.list = take(sizeof(int) * (size_t)n);
-  p.part = take(sizeof(double) * 2 * kSeg * (size_t)n);
-  p.mpart = take(sizeof(double) * 2 * kSeg * (size_t)n);
-  p.mrow = take(sizeof(double) * 2 * (size_t)n);
+  p.part = take(sizeof(double) * 2 * (size_t)shared_pairs(n));
   p.state = take(sizeof(int) * 16);
   p.total = o;
   return p;
@@ -721,8 +727,8 @@ int hawkes_mwg_step(double* x, const double* t, int64_t n, int d, const hawkes_p
   s.rows = kBlock / (nmove >= kManyMoved ? kRowLanesMany : 1);
   s.nrb = (int)((n + s.rows - 1) / s.rows);
   // kBlock partners per chunk, or as many more as keep the chunk sums of all
-  // moved rows within the workspace (n x kSeg)
-  const int64_t most = std::max<int64_t>(1, (int64_t)kSeg * n / nmove);
+  // moved rows within half of the shared buffer
+  const int64_t most = std::max<int64_t>(1, (int64_t)(kSeg / 2) * n / nmove);
   s.chunk = kBlock * (int)((n + kBlock * most - 1) / (kBlock * most));
   s.nchunk = (int)((n + s.chunk - 1) / s.chunk);
   s.terms = terms;
@@ -738,9 +744,10 @@ int hawkes_mwg_step(double* x, const double* t, int64_t n, int d, const hawkes_p
   s.bcount = reinterpret_cast<int*>(w + pc.bcount);
   s.stage = reinterpret_cast<int*>(w + pc.stage);
   s.list = reinterpret_cast<int*>(w + pc.list);
-  s.part = reinterpret_cast<double*>(w + pc.part);
-  s.mpart = reinterpret_cast<double*>(w + pc.mpart);
-  s.mrow = reinterpret_cast<double*>(w + pc.mrow);
+  s.mrow = reinterpret_cast<double*>(w + pc.part);
+  s.mpart = s.mrow + 2 * nmove;
+  s.part = s.mpart + 2 * nmove * s.nchunk;
+  s.npart = shared_pairs(n) - nmove * (s.nchunk + 1);
   s.state = reinterpret_cast<int*>(w + pc.state);
   hipStream_t st = static_cast<hipStream_t>(stream);
   (void)hipGetLastError();

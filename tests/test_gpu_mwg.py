@@ -356,3 +356,42 @@ def test_mwg_many_rows_that_lose_their_one_source(n, next_day):
         _check_terms(terms.cpu().numpy(), oracle.event_terms(x1, t, p), "fp64", p, f"listed nmove{nmove}")
     say(f"  us a step: {us}")
     assert us[1] <= 3.0 * us[8] and us[7] <= 3.0 * us[8]
+
+
+@pytest.mark.parametrize("n,nmove", [(700, 8), (1200, 300), (1200, 600), (1200, 1000), (1200, 1199), (12000, 2000)])
+def test_mwg_moved_and_listed_rows_share_the_workspace(n, nmove):
+    """Blocks that take every source of the remaining rows away, so that these
+    are all listed beside many moved rows' chunk sums (8 to 32 segments a row),
+    in a workspace between guard words: Delta ell, terms, and the guards.
+    (12,000 events, 2,000 moved: 16 segments a row.)"""
+    import ctypes
+
+    import torch
+    from paper_2010_02994_amd import _lib, api
+    rng = np.random.default_rng(n + nmove)
+    x = 0.5 * rng.standard_normal((n, 2))
+    t = np.concatenate([np.sort(rng.uniform(0.0, 1.0, nmove)), np.full(n - nmove, 2.0)])
+    p = np.array([0.5, 1.0, 5.0, 0.4, 0.2, 1.0])
+    idx = np.arange(nmove).astype(np.int64)
+    x1 = x.copy()
+    x1[:nmove] += 8.0
+    xd, td = _dev(x), _dev(t)
+    terms, _ = api.event_terms(xd, td, p, prec="fp64")
+    size, guard = _lib.lib().hawkes_mwg_workspace_bytes(n), 1 << 16
+    ws = torch.full((size + 2 * guard,), 0x5a, dtype=torch.uint8, device="cuda:0")
+    out, i_, x_, th = _dev(np.zeros(3)), _dev(idx), _dev(x1[:nmove]), _dev(np.array([-np.inf]))
+    ps = api.params_struct(p)
+    say(f"case mwg shared workspace n={n} nmove={nmove}")
+    st = _lib.lib().hawkes_mwg_step(xd.data_ptr(), td.data_ptr(), n, 2, ctypes.byref(ps), terms.data_ptr(), i_.data_ptr(),
+                                    x_.data_ptr(), nmove, th.data_ptr(), ws.data_ptr() + guard, size,
+                                    api._stream_ptr(xd.device), out.data_ptr())
+    assert st == _lib.OK
+    torch.cuda.synchronize()
+    _, ll0, _, _ = oracle.loglik_grad(x, t, p, threads=True, want_grad_x=False)
+    _, ll1, _, _ = oracle.loglik_grad(x1, t, p, threads=True, want_grad_x=False)
+    got = out.cpu().numpy()
+    assert got[1] == 1.0 and got[2] == 0.0
+    assert abs(got[0] - (ll1 - ll0)) <= 1e-10 * max(abs(ll0), abs(ll1))
+    assert np.array_equal(xd.cpu().numpy(), x1)
+    _check_terms(terms.cpu().numpy(), oracle.event_terms(x1, t, p), "fp64", p, f"shared nmove{nmove}")
+    assert torch.all(ws[:guard] == 0x5a).item() and torch.all(ws[guard + size:] == 0x5a).item()

@@ -170,3 +170,13 @@ def test_small_arena_holds_several_requests(n, d, arena, together):
         assert s.stats()["arena_free_bytes"] == s.stats()["arena_bytes"]
     ev = sorted([(r["t_admit_ns"], 1) for r in res] + [(r["t_done_ns"], -1) for r in res])
     assert max(np.cumsum([k for _, k in ev])) >= together
+
+
+@pytest.mark.parametrize("n", [2, 65, 2048, 2049, 2925, 50000, 1 << 20])
+def test_mwg_workspace_size(n):
+    """At most 32 segment pairs, three doubles, three integers and the row
+    blocks' sums for every event."""
+    up = lambda b: (b + 255) // 256 * 256
+    nrb = (n + 255) // 256
+    most = 3 * up(8 * n) + 2 * up(4 * n) + up(8 * nrb) + up(4 * nrb) + up(4 * nrb * 256) + up(512 * n) + up(64)
+    assert 0 < _lib.lib().hawkes_mwg_workspace_bytes(n) <= most
