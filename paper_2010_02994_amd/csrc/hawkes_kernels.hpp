@@ -578,23 +578,50 @@ __device__ __forceinline__ void group_sum(double (&v)[NV], double* sh) {
   __syncthreads();
 }
 
+// Calls without a gradient, whose flagged rows have the chip to themselves: workgroups for a
+// request of nblk event blocks (up to four a CU), and partner segments per flagged row, as
+// many as keep kFixPartners partners a segment (with one a thread, 119 rows at N = 3,000
+// took 7 us more than whole rows) and the tasks within four rounds.  (By the request's
+// own size, not the launch's: a request's sums are the same in any batch.)
+__host__ __device__ inline int fix_grid(int nblk) {
+  return 4 * nblk < kFixGrid ? kFixGrid : 4 * nblk > 8 * kFixGrid ? 8 * kFixGrid : 4 * nblk;
+}
+constexpr int kFixSeg = 16;        // at most
+constexpr int kFixPartners = 2048;
+constexpr int kFixSegStride = 8;   // doubles per segment: fixpart holds three a row whatever the count
+__device__ __forceinline__ int fix_segs(int cnt, const KParams& kp) {
+  const int64_t most = min((int64_t)4 * fix_grid(kp.nblk), (int64_t)3 * kp.n);
+  int segs = 1;
+  while (segs < kFixSeg && 2 * segs * kFixPartners <= kp.n && (int64_t)cnt * 2 * segs <= most) segs *= 2;
+  return segs;
+}
+
 // Exact float64 recomputation of each flagged row i: the six row sums and (in
 // gradient calls) the row's own side of the location gradient,
-//   sum_j [mu_ij/tau_x^2 + (t_j < t_i) xi_ij/h^2] (x_j - x_i) / lambda_i,
-// one workgroup per row.  It finds the row's largest log pair term m and sums
-// terms times exp(-m), so no term that matters can underflow.  What the last
-// reduction reads of row f of the list, fixpart[f * kFixStride + q]:
-// q < 6 the unweighted sums times exp(-m), 6: m, 7: log lambda_i, 8: t_i,
-// 9 ..: x_i, 17 ..: the gradient vector.  (Rows split over 16 partner segments,
-// merged by every workgroup of the last reduction, cost it 14 us at N = 50,000
-// with about 40 flagged rows; whole rows cost nothing there, and hide behind
-// the gradient pass here: about 25 us a row and workgroup at that size.)
+//   sum_j [mu_ij/tau_x^2 + (t_j < t_i) xi_ij/h^2] (x_j - x_i) / lambda_i.
+// A task finds the largest log pair term m among its partners and sums terms
+// times exp(-m), so no term that matters can underflow.
+//
+// Gradient calls: one workgroup per row.  What the last reduction reads of row f of
+// the list, fixpart[f * kFixStride + q]: q < 6 the unweighted sums times exp(-m), 6: m,
+// 7: log lambda_i, 8: t_i, 9 ..: x_i, 17 ..: the gradient vector.  (Rows split
+// over 16 partner segments, merged by every workgroup of the last reduction, cost it
+// 14 us at N = 50,000 with about 40 flagged rows; whole rows cost nothing there, and
+// their 160 us a row and workgroup at that size hide behind the gradient pass.)
+//
+// Calls without a gradient have no pass to hide behind: fix_segs segments of the partners
+// a row, each a task of its own, fixpart[(f * segs + g) * 8 + q]: q < 6 the segment's sums,
+// 6: its m (-infinity: no partner).  final_block merges them.  Log-likelihoods of
+// N = 50,000 events with whole rows on 128 workgroups and with segments, us: one flagged
+// row (float64) 1,904 and 1,769 (none: 1,746), 22 (mixed) 973 and 853, 2,500 (mixed) 3,010
+// and 1,410, 49,000 (mixed) 41,000 and 12,000.
+//
 // The ordered list of flagged rows comes from k_reduce1's per-block counts
 // and staged rows: every workgroup scans the counts (each thread over a chunk
 // of consecutive blocks) and finds its tasks' rows from the scan; workgroup 0
 // of each request also writes the list, each row's list position and the
 // count, which the next kernel reads.
-template <int D>
+template <int D, bool GRAD>
 __device__ __forceinline__ void fix_rows(const ReqDesc& rq, int bx, int nbx, double* pool) {
   if (uni(glb(rq.status)[kStData]) != 0) return;
   const KParams& kp = rq.kp;
@@ -629,7 +656,9 @@ __device__ __forceinline__ void fix_rows(const ReqDesc& rq, int bx, int nbx, dou
   const auto x = glb(rq.x);
   const auto t = glb(rq.t);
   const double wb = kp.cbg * kp.itx2, ws = kp.cse * kp.ih2;
-  for (int f = bx; f < cnt; f += nbx) {
+  const int segs = GRAD ? 1 : fix_segs(cnt, kp), seg = (kp.n + segs - 1) / segs;
+  for (int task = bx; task < cnt * segs; task += nbx) {
+    const int f = task / segs, j0 = task % segs * seg, j1 = min(kp.n, j0 + seg);
     // row f of the list: the first chunk whose inclusive count exceeds f,
     // then the block inside it
     int c0 = 0, c1 = nt - 1;
@@ -646,7 +675,7 @@ __device__ __forceinline__ void fix_rows(const ReqDesc& rq, int bx, int nbx, dou
     for (int q = 0; q < D; ++q) xi[q] = x[(int64_t)i * D + q];
     const double ti = t[i];
     double m = -INFINITY;
-    for (int j = tid; j < kp.n; j += nt) {
+    for (int j = j0 + tid; j < j1; j += nt) {
       if (j == i) continue;
       double r2 = 0;
 #pragma unroll
@@ -662,10 +691,11 @@ __device__ __forceinline__ void fix_rows(const ReqDesc& rq, int bx, int nbx, dou
     for (int w = 0; w < (nt >> 6); ++w) m = fmax(m, sh[w]);
     __syncthreads();
     const double msub = m > -INFINITY ? m : 0.0;
-    double a[6 + D];
+    constexpr int NA = GRAD ? 6 + D : 6;
+    double a[NA];
 #pragma unroll
-    for (int q = 0; q < 6 + D; ++q) a[q] = 0.0;
-    for (int j = tid; j < kp.n; j += nt) {
+    for (int q = 0; q < NA; ++q) a[q] = 0.0;
+    for (int j = j0 + tid; j < j1; j += nt) {
       if (j == i) continue;
       double dx[D], r2 = 0;
 #pragma unroll
@@ -682,22 +712,25 @@ __device__ __forceinline__ void fix_rows(const ReqDesc& rq, int bx, int nbx, dou
         a[3] += e; a[4] += e * r2; a[5] += e * dt;
         c += ws * e;
       }
+      if constexpr (GRAD)
 #pragma unroll
-      for (int q = 0; q < D; ++q) a[6 + q] += c * dx[q];
+        for (int q = 0; q < D; ++q) a[6 + q] += c * dx[q];
     }
     group_sum(a, sh);
     if (tid == 0) {
-      const auto fp = glb(rq.fixpart) + (int64_t)f * kFixStride;
-      const double lt = kp.cbg * a[0] + kp.cse * a[3];
+      const auto fp = glb(rq.fixpart) + (int64_t)task * (GRAD ? kFixStride : kFixSegStride);
 #pragma unroll
       for (int q = 0; q < 6; ++q) fp[q] = a[q];
-      fp[6] = msub;
-      fp[7] = log(lt) + msub;   // -inf: the rate is zero
-      fp[8] = ti;
+      fp[6] = GRAD ? msub : m;
+      if constexpr (GRAD) {
+        const double lt = kp.cbg * a[0] + kp.cse * a[3];
+        fp[7] = log(lt) + msub;   // -inf: the rate is zero
+        fp[8] = ti;
 #pragma unroll
-      for (int q = 0; q < D; ++q) {
-        fp[9 + q] = xi[q];
-        fp[17 + q] = a[6 + q] / lt;
+        for (int q = 0; q < D; ++q) {
+          fp[9 + q] = xi[q];
+          fp[17 + q] = a[6 + q] / lt;
+        }
       }
     }
   }
@@ -771,11 +804,12 @@ __device__ __forceinline__ void final_events(const ReqDesc& rq, int lb, double* 
     for (int q = 0; q < 8; ++q) glb(rq.bpart)[(int64_t)lb * 8 + q] = v[q];
 }
 
-// Blocks of a launch that take the fix-ups and the finalize terms.
+// Blocks of a gradient pass that take the fix-ups and the finalize terms.
 __host__ __device__ inline int side_blocks(int nreq, int ev_blocks) { return nreq * kFixGrid + ev_blocks; }
 
-template <int D, bool MIX>
-__device__ __forceinline__ void side_block(const ReqDesc* __restrict__ reqs, int nreq, int ev_blocks, double* pool) {
+template <int D, bool GRAD>
+__device__ __forceinline__ void side_block(const ReqDesc* __restrict__ reqs, int nreq, int ev_blocks, int fix_blocks,
+                                           double* pool) {
   int b = blockIdx.x;
   if (b < ev_blocks) {
     const ReqDesc& rq = reqs[find_req(reqs, nreq, b, 1)];
@@ -783,14 +817,14 @@ __device__ __forceinline__ void side_block(const ReqDesc* __restrict__ reqs, int
     return;
   }
   b -= ev_blocks;
-  fix_rows<D>(reqs[b / kFixGrid], b % kFixGrid, kFixGrid, pool);
+  fix_rows<D, GRAD>(reqs[b / fix_blocks], b % fix_blocks, fix_blocks, pool);
 }
 
 // The same blocks alone (calls without a gradient).
-template <int D, bool MIX>
+template <int D>
 __global__ void __launch_bounds__(kEvBlock) k_side(const ReqDesc* __restrict__ reqs, int nreq, int ev_blocks) {
   __shared__ double s_pool[kEvBlock + (kEvBlock / 64) * (8 + D)];
-  side_block<D, MIX>(reqs, nreq, ev_blocks, s_pool);
+  side_block<D, false>(reqs, nreq, ev_blocks, fix_grid(ev_blocks / nreq), s_pool);
 }
 
 // Pass 2: location gradient.  For the pair (i later, j earlier)
@@ -882,7 +916,7 @@ __global__ void __launch_bounds__(SP* kThreads) __attribute__((amdgpu_waves_per_
   // next kernel only); nothing in the pair pass depends on them
   const int blk = (int)blockIdx.x - side_blocks(nreq, ev_blocks);
   if (blk < 0) {
-    side_block<D, false>(reqs, nreq, ev_blocks, s_acc);
+    side_block<D, true>(reqs, nreq, ev_blocks, kFixGrid, s_acc);
     return;
   }
   const int rid = find_req(reqs, nreq, blk, 0);
@@ -1330,7 +1364,7 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(g
   // next kernel only); nothing in the pair pass depends on them
   const int blk = (int)blockIdx.x - side_blocks(nreq, ev_blocks);
   if (blk < 0) {
-    side_block<D, true>(reqs, nreq, ev_blocks, s_acc);
+    side_block<D, true>(reqs, nreq, ev_blocks, kFixGrid, s_acc);
     return;
   }
   const int rid = find_req(reqs, nreq, blk, 0);
@@ -1530,7 +1564,7 @@ __global__ void __launch_bounds__(kRedThreads) k_reduce1(const ReqDesc* __restri
 // finalize blocks' sums, the flagged rows' terms and (gradient calls) the
 // gradient pass's two moment sums, all in a fixed order.
 // out8 = [ell, 6 gradients, status].  kRedThreads threads.
-template <int D, bool MIX>
+template <int D, bool MIX, bool GRAD>
 __device__ __forceinline__ void final_block(const ReqDesc& rq, double* pool) {
   const KParams& kp = rq.kp;
   const int tid = threadIdx.x;
@@ -1553,13 +1587,31 @@ __device__ __forceinline__ void final_block(const ReqDesc& rq, double* pool) {
       }
     }
     const int cnt = glb(rq.status)[kStFlagCount];
+    const int segs = GRAD ? 1 : fix_segs(cnt, kp);
     for (int f = tid; f < cnt; f += kRedThreads) {
-      const auto fp = glb(rq.fixpart) + (int64_t)f * kFixStride;
-      double s[6];
+      double s[6], scale;
+      if constexpr (GRAD) {
+        const auto fp = glb(rq.fixpart) + (int64_t)f * kFixStride;
 #pragma unroll
-      for (int q = 0; q < 6; ++q) s[q] = fp[q];
-      const double lt = rate_terms<D>(kp, s, fp[6], v);
-      store_terms(rq, glb(rq.list)[f], s, lt, fp[6]);
+        for (int q = 0; q < 6; ++q) s[q] = fp[q];
+        scale = fp[6];
+      } else {
+        const auto fp = glb(rq.fixpart) + (int64_t)f * segs * kFixSegStride;
+        double m = -INFINITY;
+        for (int g = 0; g < segs; ++g) m = fmax(m, fp[g * kFixSegStride + 6]);
+#pragma unroll
+        for (int q = 0; q < 6; ++q) s[q] = 0.0;
+        for (int g = 0; g < segs && m > -INFINITY; ++g) {
+          const double mg = fp[g * kFixSegStride + 6];
+          if (!(mg > -INFINITY)) continue;
+          const double w = exp(mg - m);
+#pragma unroll
+          for (int q = 0; q < 6; ++q) s[q] += fp[g * kFixSegStride + q] * w;
+        }
+        scale = m > -INFINITY ? m : 0.0;
+      }
+      const double lt = rate_terms<D>(kp, s, scale, v);
+      store_terms(rq, glb(rq.list)[f], s, lt, scale);
     }
   }
   // mixed sums are in bandwidth units and carry 1/tau_x, float64 ones 1/tau_x^2
@@ -1586,7 +1638,7 @@ __device__ __forceinline__ void final_block(const ReqDesc& rq, double* pool) {
 template <int D, bool MIX>
 __global__ void __launch_bounds__(kRedThreads) k_final(const ReqDesc* __restrict__ reqs) {
   __shared__ double s_pool[kRedWaves * 8];
-  final_block<D, MIX>(reqs[blockIdx.x], s_pool);
+  final_block<D, MIX, false>(reqs[blockIdx.x], s_pool);
 }
 
 // grad_x = row partials + column partials + fix-up terms, in a fixed order
@@ -1605,7 +1657,7 @@ __global__ void __launch_bounds__(kRedThreads) k_reduce2(const ReqDesc* __restri
   constexpr int kMeet = kRedWaves * D * kRedEv, kFlagged = kFixChunk * (D + 2);
   __shared__ double s_pool[kMeet > kFlagged ? kMeet : kFlagged];
   if ((int)blockIdx.x < nreq) {
-    final_block<D, MIX>(reqs[blockIdx.x], s_pool);
+    final_block<D, MIX, true>(reqs[blockIdx.x], s_pool);
     return;
   }
   const int blk = blockIdx.x - nreq;

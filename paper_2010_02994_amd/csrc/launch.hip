@@ -36,7 +36,7 @@ static bool launch_phases(const ReqDesc* reqs, int nreq, const BatchGrid& g, boo
   mark_stage(s, 4);
   const int side = side_blocks(nreq, g.ev_blocks);
   if (!grad) {
-    k_side<D, MIX><<<side, kEvBlock, 0, s>>>(reqs, nreq, g.ev_blocks);
+    k_side<D><<<g.ev_blocks + nreq * fix_grid(g.ev_blocks / nreq), kEvBlock, 0, s>>>(reqs, nreq, g.ev_blocks);
     for (int k = 5; k <= 7; ++k) mark_stage(s, k);
     k_final<D, MIX><<<nreq, kRedThreads, 0, s>>>(reqs);
     mark_stage(s, 8);

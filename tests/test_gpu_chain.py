@@ -121,3 +121,62 @@ def test_mixed_scales_beyond_float32(params, scale, n, d, cull):
     assert np.all(np.isfinite(gp))
     d_row = np.linalg.norm(gx - ref.gx, axis=1)
     assert np.all(d_row <= 3e-4 * ref.row_scale)
+
+
+@pytest.mark.parametrize("prec,spacing", [("mixed", 20.0), ("fp64", 37.0)])
+@pytest.mark.parametrize("core,far", [(200, 1), (130, 65), (40, 1100), (0, 96), (4200, 1), (9000, 130), (18000, 700), (33000, 3)])
+def test_flagged_rows_without_a_gradient(prec, spacing, core, far):
+    """Log-likelihood and per-event terms of calls whose flagged rows are split
+    into partner segments (one up to 4,095 events, then two, four, eight and,
+    with few rows, 16): the log-likelihood at the precision's tolerance, and
+    the flagged rows' terms, which are float64 sums in both precisions, at
+    float64's."""
+    import oracle
+    import torch
+
+    from paper_2010_02994_amd import api
+    x, t, p = isolated_case(core + far, core, far, spacing)
+    xd, td = torch.tensor(x, device="cuda:0"), torch.tensor(t, device="cuda:0")
+    say(f"case flagged rows without a gradient core={core} far={far} prec={prec}")
+    terms, ll = api.event_terms(xd, td, p, prec=prec)
+    info, flags = api.diagnostics(xd, td, p, prec=prec)
+    assert info["flagged_rows"] == far and np.array_equal(flags != 0, np.abs(x).max(axis=1) > spacing / 2)
+    _, ref, _, _ = oracle.loglik_grad(x, t, p, threads=True, want_grad_x=False)
+    tol = {"mixed": 1e-5, "fp64": 1e-10}[prec]
+    assert abs(ll - ref) <= tol * abs(ref)
+    assert api.loglik(xd, td, p, prec=prec) == ll
+    rows = np.flatnonzero(flags)
+    got, want = terms.cpu().numpy()[rows], oracle.event_terms(x, t, p, rows=rows)
+    assert np.all(np.abs(got[:, 2:] - want[:, 2:]) <= 1e-10 * np.maximum(1.0, np.abs(want[:, 2:])))
+    # rates of exp(-spacing^2 / 2), down to 1e-297: the exponent's rounding, up to
+    # 700 ulp(1), is the value's relative error
+    assert np.all(np.abs(got[:, :2] - want[:, :2]) <= 1e-10 * np.abs(want[:, :2]))
+
+
+def test_one_flagged_row_costs_little_without_a_gradient():
+    """At N = 50,000 the exact recomputation of one row, split over the chip,
+    adds under 5 % to a log-likelihood (one workgroup took 180 us, 11 %)."""
+    import torch
+
+    from paper_2010_02994_amd import api
+    w = W.config2(seed=3, n=50000, same_density=True)
+    td, xs = torch.tensor(w.t, device="cuda:0"), []
+    for far in (0, 1):
+        x = w.x.copy()
+        if far:
+            x[20000] = x.max(axis=0) + 60.0 * max(w.params[1], w.params[5])
+        xs.append(torch.tensor(x, device="cuda:0"))
+    us = ([], [])
+    for _ in range(40):   # in turn; the medians of the later half
+        for far in (0, 1):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            api.loglik(xs[far], td, w.params, prec="fp64")
+            b.record()
+            b.synchronize()
+            us[far].append(a.elapsed_time(b) * 1e3)
+            info, _ = api.diagnostics(xs[far], td, w.params, prec="fp64")
+            assert info["flagged_rows"] == far
+    without, with_one = (float(np.median(v[20:])) for v in us)
+    say(f"  us: {without:.0f} and with one flagged row {with_one:.0f}")
+    assert with_one <= 1.05 * without
