@@ -607,7 +607,9 @@ __device__ __forceinline__ int fix_segs(int cnt, const KParams& kp) {
 // 7: log lambda_i, 8: t_i, 9 ..: x_i, 17 ..: the gradient vector.  (Rows split
 // over 16 partner segments, merged by every workgroup of the last reduction, cost it
 // 14 us at N = 50,000 with about 40 flagged rows; whole rows cost nothing there, and
-// their 160 us a row and workgroup at that size hide behind the gradient pass.)
+// their 136 us a row and workgroup at that size hide behind the gradient pass, or behind
+// most of it where culling makes that short: N = 50,000, a two-day bandwidth, one flagged
+// row 309 us a call, none 289.)
 //
 // Calls without a gradient have no pass to hide behind: fix_segs segments of the partners
 // a row, each a task of its own, fixpart[(f * segs + g) * 8 + q]: q < 6 the segment's sums,
@@ -674,13 +676,24 @@ __device__ __forceinline__ void fix_rows(const ReqDesc& rq, int bx, int nbx, dou
 #pragma unroll
     for (int q = 0; q < D; ++q) xi[q] = x[(int64_t)i * D + q];
     const double ti = t[i];
+    // each partner's place is read a step ahead, so its latency lies beside the previous
+    // one's arithmetic (a row of 50,000 partners 165 -> 136 us)
+    double xn[D], tn = 0.0;
+    const auto read = [&](int j) {
+      const int jc = min(j, kp.n - 1);
+#pragma unroll
+      for (int q = 0; q < D; ++q) xn[q] = x[(int64_t)jc * D + q];
+      tn = t[jc];
+    };
     double m = -INFINITY;
+    read(j0 + tid);
     for (int j = j0 + tid; j < j1; j += nt) {
-      if (j == i) continue;
       double r2 = 0;
 #pragma unroll
-      for (int q = 0; q < D; ++q) { const double dx = xi[q] - x[(int64_t)j * D + q]; r2 += dx * dx; }
-      const double dt = ti - t[j];
+      for (int q = 0; q < D; ++q) { const double dx = xi[q] - xn[q]; r2 += dx * dx; }
+      const double dt = ti - tn;
+      read(j + nt);
+      if (j == i) continue;
       if (dt != 0.0) m = fmax(m, kp.log_cbg - kp.alpha * r2 - kp.beta * dt * dt);
       if (dt > 0.0) m = fmax(m, kp.log_cse - kp.omega * dt - kp.gamma * r2);
     }
@@ -695,12 +708,14 @@ __device__ __forceinline__ void fix_rows(const ReqDesc& rq, int bx, int nbx, dou
     double a[NA];
 #pragma unroll
     for (int q = 0; q < NA; ++q) a[q] = 0.0;
+    read(j0 + tid);
     for (int j = j0 + tid; j < j1; j += nt) {
-      if (j == i) continue;
       double dx[D], r2 = 0;
 #pragma unroll
-      for (int q = 0; q < D; ++q) { dx[q] = x[(int64_t)j * D + q] - xi[q]; r2 += dx[q] * dx[q]; }
-      const double dt = ti - t[j];
+      for (int q = 0; q < D; ++q) { dx[q] = xn[q] - xi[q]; r2 += dx[q] * dx[q]; }
+      const double dt = ti - tn;
+      read(j + nt);
+      if (j == i) continue;
       double c = 0.0;
       if (dt != 0.0) {
         const double e = exp(-kp.alpha * r2 - kp.beta * dt * dt - msub);

@@ -180,3 +180,36 @@ def test_one_flagged_row_costs_little_without_a_gradient():
     without, with_one = (float(np.median(v[20:])) for v in us)
     say(f"  us: {without:.0f} and with one flagged row {with_one:.0f}")
     assert with_one <= 1.05 * without
+
+
+def test_one_flagged_row_beside_a_short_gradient_pass():
+    """Culling with a short background bandwidth and fast decay leaves a
+    gradient pass shorter than a flagged row's recomputation beside it was:
+    the row adds under 11 % to the call (16 % before its partners were read a
+    step ahead)."""
+    import torch
+
+    from paper_2010_02994_amd import api
+    w = W.config2(seed=3, n=50000, same_density=True)
+    p = w.params.copy()
+    p[[1, 2, 4, 5]] = 40.0, 2.0, 2.0, 5.0
+    td, xs, us = torch.tensor(w.t, device="cuda:0"), [], ([], [])
+    for far in (0, 1):
+        x = w.x.copy()
+        if far:
+            x[20000] = x.max(axis=0) + 700.0
+        xs.append(torch.tensor(x, device="cuda:0"))
+    say("case one flagged row beside a short gradient pass")
+    for _ in range(60):   # in turn; the medians of the later half
+        for far in (0, 1):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            api.grad(xs[far], td, p, prec="mixed+cull")
+            b.record()
+            b.synchronize()
+            us[far].append(a.elapsed_time(b) * 1e3)
+            info, _ = api.diagnostics(xs[far], td, p, prec="mixed+cull")
+            assert info["flagged_rows"] == far
+    without, with_one = (float(np.median(v[30:])) for v in us)
+    say(f"  us: {without:.0f} and with one flagged row {with_one:.0f}")
+    assert with_one <= 1.11 * without
