@@ -348,29 +348,18 @@ __device__ __forceinline__ void pair_phi(R r2, R dist, R rs, const Args& a, cons
   }
 }
 
-// Lanes per workgroup and prefetched rows of a tile pass with C columns per
-// lane (the library runs it with C = 1 for float64 pairs when tiles are few;
-// many tiles, and float32 pairs, take the strips below).
-template <int C>
-struct TileShape {
-  static constexpr int kLanes = kTC / C;   // workgroup size
-  static constexpr int kWavesT = kLanes / 64;
-  static constexpr int kPre = kPrefetch;   // rows loaded ahead
-};
-
-// (Waves per SIMD: as many as the registers allow without spills.)
-template <int D, bool MIX, int C>
-__global__ void __launch_bounds__(TileShape<C>::kLanes, D <= 4 ? 4 : 3) k_bmds_tiles(Args a) {
-  using R = typename std::conditional<MIX, float, double>::type;
-  using TS = TileShape<C>;
-  constexpr int NL = TS::kLanes, NW = TS::kWavesT, PRE = TS::kPre;
+// Float64 pairs, few tiles: a workgroup per tile, one column per lane.  (Waves per SIMD: as
+// many as the registers allow without spills.)
+template <int D>
+__global__ void __launch_bounds__(kTC, D <= 4 ? 4 : 3) k_bmds_tiles(Args a) {
+  constexpr int NW = kTC / 64;
   using Sums = MfmaRowSums<D>;
-  static_assert(PRE % Sums::kGroup == 0, "row groups end with the prefetched rows");
-  __shared__ R s_x[kTR][D];
-  __shared__ R s_row[NW][kTR][D];   // the waves' row sums
-  __shared__ double sh[4 * NL];
-  __shared__ double s_exptab[MIX ? 1 : kExpTab];   // float64 pairs: 2^(j/kExpTab) for exp_tab
-  if constexpr (!MIX) fill_exp_table(s_exptab);
+  static_assert(kPrefetch % Sums::kGroup == 0, "row groups end with the prefetched rows");
+  __shared__ double s_x[kTR][D];
+  __shared__ double s_row[NW][kTR][D];   // the waves' row sums
+  __shared__ double sh[4 * kTC];
+  __shared__ double s_exptab[kExpTab];   // 2^(j/kExpTab) for exp_tab
+  fill_exp_table(s_exptab);
   const int64_t tile = blockIdx.x;
   int lo = 0, hi = a.nb - 1;   // band: largest I with band_offset(I) <= tile
   while (lo < hi) {
@@ -381,36 +370,25 @@ __global__ void __launch_bounds__(TileShape<C>::kLanes, D <= 4 ? 4 : 3) k_bmds_t
   const int I = lo;
   const int J = (int)(tile - band_offset(I));
   const int i0 = I * kTR;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  // columns of this lane: C runs of 64, so each row's loads stay coalesced
-  int jc[C], jl[C];
-#pragma unroll
-  for (int c = 0; c < C; ++c) {
-    jl[c] = w * 64 * C + c * 64 + lane;
-    jc[c] = J * kTC + jl[c];
-  }
+  const int w = threadIdx.x >> 6;
+  const int jc = J * kTC + threadIdx.x;   // this lane's column
   // the band's first tile also counts its rows' non-finite coordinates, so
   // every event is checked once
   int bad = 0;
-  for (int e = threadIdx.x; e < kTR * D; e += NL) {
+  for (int e = threadIdx.x; e < kTR * D; e += kTC) {
     const int r = e / D, q = e % D;
     const int i = i0 + r;
     const double xv = i < a.n ? a.x[(int64_t)i * D + q] : 0.0;
     if (J == 0 && !isfinite(xv)) ++bad;
-    s_x[r][q] = (R)xv;
+    s_x[r][q] = xv;
   }
-  R xj[C][D], g[C][D];
+  double xj[D], g[D];
   const int bad_x = bad;
-  // sums over this lane's pairs of (delta - d)^2, log Phi(z) and rho d/sigma:
-  // float32 micro-partials over the pairs of each group of prefetched rows
-  // (at most PRE x C terms), folded into float64
+  // sums over this lane's pairs of (delta - d)^2, log Phi(z) and rho d/sigma
   double a_res2, a_lphi, a_rz;
   int miss;
 #pragma unroll
-  for (int c = 0; c < C; ++c)
-#pragma unroll
-    for (int q = 0; q < D; ++q) xj[c][q] = jc[c] < a.n ? (R)a.x[(int64_t)jc[c] * D + q] : R(0);
-  const R inv_s2 = (R)a.inv_s2;
+  for (int q = 0; q < D; ++q) xj[q] = jc < a.n ? a.x[(int64_t)jc * D + q] : 0.0;
   __syncthreads();
   const int rows = min(kTR, a.n - i0);
   Sums sums;
@@ -420,93 +398,76 @@ again:
   miss = 0;
   bad = bad_x;
 #pragma unroll
-  for (int c = 0; c < C; ++c)
-#pragma unroll
-    for (int q = 0; q < D; ++q) g[c][q] = R(0);
-  for (int r0 = 0; r0 < rows; r0 += PRE) {
-    // the next rows' entries first, so PRE x C loads are in flight at once;
+  for (int q = 0; q < D; ++q) g[q] = 0.0;
+  for (int r0 = 0; r0 < rows; r0 += kPrefetch) {
+    // the next rows' entries first, so kPrefetch loads are in flight at once;
     // every load is issued (its address clamped into the matrix) and the
     // entries outside the triangle are masked afterwards, so no branch
     // separates the loads and each row waits only for its own entries
-    double v[PRE][C];
+    double v[kPrefetch];
 #pragma unroll
-    for (int u = 0; u < PRE; ++u) {
+    for (int u = 0; u < kPrefetch; ++u) {
       const int i = min(i0 + r0 + u, a.n - 1);
-#pragma unroll
-      for (int c = 0; c < C; ++c) v[u][c] = a.delta[(int64_t)i * a.n + min(jc[c], a.n - 1)];
+      v[u] = a.delta[(int64_t)i * a.n + min(jc, a.n - 1)];
     }
-    R m_res2 = R(0), m_lphi = R(0), m_rz = R(0);
+    double m_res2 = 0.0, m_lphi = 0.0, m_rz = 0.0;
 #pragma unroll
-    for (int u = 0; u < PRE; ++u) {
+    for (int u = 0; u < kPrefetch; ++u) {
       const int r = r0 + u;   // rows past the last add nothing (no column is below them)
-      R xi[D], gi[D];
+      double xi[D], gi[D];
 #pragma unroll
-      for (int q = 0; q < D; ++q) { xi[q] = s_x[r][q]; gi[q] = R(0); }
+      for (int q = 0; q < D; ++q) { xi[q] = s_x[r][q]; gi[q] = 0.0; }
+      const double dv = v[u];
+      if (jc < i0 + r && r < rows) {
+        if (isnan(dv)) {
+          miss += 1;
+        } else if (dv < 0.0 || isinf(dv)) {
+          bad += 1;
+        } else {
+          double diff[D], r2 = 0.0;
 #pragma unroll
-      for (int c = 0; c < C; ++c) {
-        const double dv = v[u][c];
-        if (jc[c] < i0 + r && r < rows) {
-          if (isnan(dv)) {
-            miss += 1;
-          } else if (dv < 0.0 || isinf(dv)) {
-            bad += 1;
-          } else {
-            R diff[D], r2 = R(0);
+          for (int q = 0; q < D; ++q) {
+            diff[q] = xi[q] - xj[q];
+            r2 += diff[q] * diff[q];
+          }
+          const double rs = rsqrt_f64(r2), dist = r2 * rs;
+          double lphi, rho_s;
+          pair_phi<double>(r2, dist, rs, a, s_exptab, lphi, rho_s);
+          const double res = dv - dist;
+          m_res2 = res * res + m_res2;
+          m_lphi += lphi;
+          m_rz = rho_s * dist + m_rz;
+          const double coef = (res * a.inv_s2 - rho_s) * rs;
 #pragma unroll
-            for (int q = 0; q < D; ++q) {
-              diff[q] = xi[q] - xj[c][q];
-              r2 += diff[q] * diff[q];
-            }
-            R rs, dist;
-            if constexpr (MIX) {
-              rs = r2 > 0.0f ? __builtin_amdgcn_rsqf(r2) : 0.0f;   // d = 0 adds no direction
-              dist = r2 * rs;
-            } else {
-              rs = rsqrt_f64(r2);
-              dist = r2 * rs;
-            }
-            R lphi, rho_s;
-            pair_phi<R>(r2, dist, rs, a, s_exptab, lphi, rho_s);
-            const R res = (R)dv - dist;
-            m_res2 = res * res + m_res2;
-            m_lphi += lphi;
-            m_rz = rho_s * dist + m_rz;
-            const R coef = (res * inv_s2 - rho_s) * rs;
-#pragma unroll
-            for (int q = 0; q < D; ++q) {
-              gi[q] = coef * diff[q] + gi[q];
-              g[c][q] = -coef * diff[q] + g[c][q];
-            }
+          for (int q = 0; q < D; ++q) {
+            gi[q] = coef * diff[q] + gi[q];
+            g[q] = -coef * diff[q] + g[q];
           }
         }
       }
       sums.add(gi, s_row[w], r, apart);
     }
-    a_res2 += (double)m_res2;
-    a_lphi += (double)m_lphi;
-    a_rz += (double)m_rz;
+    a_res2 += m_res2;
+    a_lphi += m_lphi;
+    a_rz += m_rz;
   }
   bool finite = true;
 #pragma unroll
-  for (int c = 0; c < C; ++c)
-#pragma unroll
-    for (int q = 0; q < D; ++q) finite = finite && fabs((double)g[c][q]) < HUGE_VAL;
+  for (int q = 0; q < D; ++q) finite = finite && fabs(g[q]) < HUGE_VAL;
   if (!apart && !__all(finite)) {
     apart = true;
     goto again;
   }
   __syncthreads();
-  for (int e = threadIdx.x; e < rows * D; e += NL) {
+  for (int e = threadIdx.x; e < rows * D; e += kTC) {
     const int r = e / D, q = e % D;
     double sum = 0.0;
 #pragma unroll
-    for (int ww = 0; ww < NW; ++ww) sum += (double)s_row[ww][r][q];
+    for (int ww = 0; ww < NW; ++ww) sum += s_row[ww][r][q];
     static_cast<double*>(a.prow)[(tile * kTR + r) * D + q] = sum;
   }
 #pragma unroll
-  for (int c = 0; c < C; ++c)
-#pragma unroll
-    for (int q = 0; q < D; ++q) static_cast<double*>(a.pcol)[(tile * kTC + jl[c]) * D + q] = (double)g[c][q];
+  for (int q = 0; q < D; ++q) static_cast<double*>(a.pcol)[(tile * kTC + threadIdx.x) * D + q] = g[q];
   // the summands -(delta - d)^2/(2 sigma^2) - log Phi(z) and the sigma terms
   // (delta - d)^2/sigma^3 + rho z/sigma of this lane's pairs
   double tot[4] = {-0.5 * a.inv_s2 * a_res2 - a_lphi, a.inv_sigma * (a.inv_s2 * a_res2 + a_rz), (double)miss,
@@ -958,7 +919,7 @@ static void launch(const Args& a, int prec, hipStream_t s, int phase) {
             <<<nseg, kTC / kStripColsFp64, 0, s>>>(a, static_cast<const double*>(a.xs), a.delta);
       }
     } else {   // float64 pairs, few tiles
-      k_bmds_tiles<D, false, 1><<<nt, TileShape<1>::kLanes, 0, s>>>(a);
+      k_bmds_tiles<D><<<nt, kTC, 0, s>>>(a);
     }
     if (phase == 1 || !a.grad_x || a.seg_k == 0) k_bmds_final<<<1, kFinalThreads, 0, s>>>(a);
   }

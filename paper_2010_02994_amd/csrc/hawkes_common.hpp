@@ -145,7 +145,7 @@ struct ReqDesc {
   void* rec;
   int* first;
   void* ps;
-  void* prow;       // row partials: float (mixed) or double
+  void* prow;       // row partials (float64 in both precisions)
   void* pcol;
   double* sums;
   int* flags;
@@ -156,7 +156,7 @@ struct ReqDesc {
   double* bpart;
   double* fixpart;
   double* terms;    // optional, n x 4: per-event terms (null: none)
-  double* mompart;  // items x 2: per-item moment sums of the mixed gradient pass
+  double* mompart;  // items x 2: per-item moment sums of the gradient pass
   double* out_host; // optional host-pinned copy of out8, written by the gradient call's last kernel (null: none)
   int blk_items;    // first block of this request in a pair-pass launch
   int blk_ev;       // first block in a per-event launch (kEvBlock events per block)

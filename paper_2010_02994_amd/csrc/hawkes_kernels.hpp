@@ -40,8 +40,6 @@ template <int D> struct Traits<D, false> {
 
 // ------------------------------------------------------------------ helpers
 
-__device__ __forceinline__ float exp_pair(float z) { return __builtin_amdgcn_exp2f(z); }
-
 #ifndef HK_FP64_UNROLL
 #define HK_FP64_UNROLL 4   // column steps per loop trip in the float64 passes
 #endif

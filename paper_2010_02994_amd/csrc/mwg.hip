@@ -65,7 +65,7 @@ struct Step {
   double* mrow;         // nmove: moved rows' sums
   double* mpart;        // nchunk x nmove: their chunk sums (at most n x kSeg / 2)
   double* part;         // npart: listed rows' segment sums
-  int* state;           // [accepted, list length]
+  int* nlisted;         // length of the list
 };
 
 // Contributions of event j to row i, without the pair weights: background
@@ -511,7 +511,7 @@ __global__ void __launch_bounds__(kBlock) k_mwg_exact(Step s) {
       const int c = s.bcount[b];
       for (int k = 0; k < c; ++k) s.list[pos++] = s.stage[(int64_t)b * s.rows + k];
     }
-    if (tid == 0) s.state[1] = L.cnt;
+    if (tid == 0) *s.nlisted = L.cnt;
   }
   if (L.cnt == 0) return;
   fill_exp_table(s_exptab);
@@ -569,7 +569,7 @@ __global__ void __launch_bounds__(kBlock) k_mwg_settle(Step s) {
     if (bad) atomicOr(&s_bad, 1);
     else settle_row((int)j, s.mrow[(int64_t)k * 2 + 0], s.mrow[(int64_t)k * 2 + 1]);
   }
-  const int cnt = s.state[1];
+  const int cnt = *s.nlisted;
   const int segs = segs_for(cnt, s);
   // G lanes per listed row (segs / 4, at most a wave): they add strided
   // segments, a butterfly within the group combines them (the same fixed
@@ -596,7 +596,6 @@ __global__ void __launch_bounds__(kBlock) k_mwg_settle(Step s) {
     s.out3[0] = bad ? NAN : tot;
     s.out3[1] = accept ? 1.0 : 0.0;
     s.out3[2] = bad ? (double)HAWKES_EDATA : 0.0;
-    s.state[0] = accept ? 1 : 0;
   }
   if (!accept) return;
   const int i = base + tid;
@@ -666,7 +665,7 @@ static int64_t shared_pairs(int64_t n) { return kSeg * n - (n > 2048 ? n / 32 : 
 
 // Workspace pieces for n events, in order.
 struct Pieces {
-  size_t new_a, new_b, dlog, flag, bpart, bcount, stage, list, part, state, total;
+  size_t new_a, new_b, dlog, flag, bpart, bcount, stage, list, part, nlisted, total;
 };
 static Pieces pieces(int64_t n) {
   const size_t nrb = (size_t)((n + kBlock / kRowLanesMany - 1) / (kBlock / kRowLanesMany));
@@ -682,7 +681,7 @@ static Pieces pieces(int64_t n) {
   p.stage = take(sizeof(int) * (size_t)((n + kBlock - 1) / kBlock * kBlock));
   p.list = take(sizeof(int) * (size_t)n);
   p.part = take(sizeof(double) * 2 * (size_t)shared_pairs(n));
-  p.state = take(sizeof(int) * 16);
+  p.nlisted = take(sizeof(int));
   p.total = o;
   return p;
 }
@@ -748,7 +747,7 @@ int hawkes_mwg_step(double* x, const double* t, int64_t n, int d, const hawkes_p
   s.mpart = s.mrow + 2 * nmove;
   s.part = s.mpart + 2 * nmove * s.nchunk;
   s.npart = shared_pairs(n) - nmove * (s.nchunk + 1);
-  s.state = reinterpret_cast<int*>(w + pc.state);
+  s.nlisted = reinterpret_cast<int*>(w + pc.nlisted);
   hipStream_t st = static_cast<hipStream_t>(stream);
   (void)hipGetLastError();
   switch (d) {
