@@ -160,7 +160,8 @@ int hawkes_diagnostics(const void* ws /* device */, size_t ws_bytes, int64_t n, 
  * its own copy until the process ends), so the call allocates nothing and
  * creates no stream; the scalars come back through a
  * pooled pinned buffer only if one already exists (else by a copy).  Limit: hawkes_workspace_bytes(n, d,
- * prec) <= HAWKES_NOALLOC_SCRATCH_BYTES (n <= 17,920 at d = 2, 17,658 at d = 6), else
+ * prec) <= HAWKES_NOALLOC_SCRATCH_BYTES (n <= 17,920 up to d = 5, 17,658 at d = 6 in
+ * float64, 15,360 at d = 8), else
  * HAWKES_ENOMEM and nothing runs.  Every call on one GPU shares its array,
  * which keeps the last call's contents (each call writes every part it
  * reads), so calls that overlap on one GPU -- from two threads, or on two

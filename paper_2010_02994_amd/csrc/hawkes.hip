@@ -67,7 +67,8 @@ static int tiles_per_item(int64_t n) {
   // slower); below that, fewer tiles per item as long as the chip is not full
   // of waves, at the price of more row partials for the reductions: one tile up
   // to 3,900 tiles (N = 10,000 mixed: 119 us against 127, 137 and 133 with 2, 3
-  // and 4; N = 15,000: 184 against 189 with 2), two up to 7,800 (N = 20,000:
+  // and 4; make_layout takes two from N = 11,784 at D = 2 on, for the static
+  // scratch: N = 15,000 189 us, 184 with one), two up to 7,800 (N = 20,000:
   // 284 us against 292 with 1 and 300 with 4), then four
   const int64_t fill = (tiles + kTargetItems - 1) / kTargetItems;
   const int64_t small = std::min<int64_t>(4, (tiles + 3899) / 3900);
@@ -80,9 +81,9 @@ static int tiles_per_item(int64_t n) {
 // 66.3 us, 2,925 78.4 and 68.9, 5,000 101.8 and 96.4, 10,000 221.9 and 219.8,
 // 30,000 1,240 and 1,264; four groups gain 1 us at N <= 2,925 and lose beyond.
 // At D = 6 the groups measured equal at N = 4,733 (122 us) and slower above
-// (their rows' state needs more registers than a 512-thread workgroup leaves),
-// and in mixed precision, whose chains are short, within 4 % either way at
-// N <= 5,000 and slower above: neither is split.
+// (the split kernels are compiled for four waves per SIMD, 128 registers, which
+// rows of that width pass), and in mixed precision, whose chains are short, within
+// 4 % either way at N <= 5,000 and slower above: neither is split.
 static int split_for(int64_t n, int nb, int d, bool mixed) {
   int64_t tiles = 0;
   for (int b = 0; b < nb; ++b) tiles += (std::min<int64_t>(n, (int64_t)(b + 1) * kBandRows) + kTile - 1) / kTile;

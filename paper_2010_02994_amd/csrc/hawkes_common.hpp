@@ -39,13 +39,12 @@ constexpr int kRowsPerLane = HK_ROWS_PER_LANE;  // rows each lane owns in the pa
 constexpr int kBandRows = kThreads * kRowsPerLane;  // rows per band (512)
 constexpr int kTile = 64;               // columns per tile (one wave width)
 constexpr int kMaxD = 8;
-constexpr int kFixGrid = 128;            // workgroups per request for the fix-ups of flagged rows
+constexpr int kFixGrid = 128;            // workgroups per request for the flagged rows of a gradient call
 constexpr int kFixStride = 9 + 2 * kMaxD;   // doubles per flagged row
 constexpr int kEvBlock = 256;           // events per block of the per-event kernels
 constexpr int kRedEv = 64;              // events per workgroup of the partial-sum reductions
 constexpr int kRedWaves = 16;           // waves per reduction workgroup (each sums a stride of partials)
 constexpr int kRedThreads = 64 * kRedWaves;
-// float32 pair passes: steps whose exps are issued together (rate, gradient)
 // Waves per SIMD the mixed passes are compiled for: the register budget
 // (512 / waves per lane) must hold the rows' state, which grows with D, or
 // the kernel spills to scratch.  The set values apply at D <= 2; wider
@@ -61,6 +60,7 @@ constexpr int kMaxSplitD = 4;
 // Column tiles of a work item of band `band`.
 __host__ __device__ inline int item_tiles(int band, int b_fine, int L) { return band < b_fine ? 1 : L; }
 
+// float32 pair passes: steps whose exps are issued together (rate, gradient)
 constexpr int kRateExpSteps = HK_RATE_EXP_STEPS;
 constexpr int kGradExpSteps = HK_GRAD_EXP_STEPS;
 
@@ -123,10 +123,10 @@ struct KParams {
   double inv_tx, inv_tt;      // 1/tau_x, 1/tau_t (packing scales)
   double sigma_main;          // natural log of the scale the main pass sums carry (-S ln 2, or 0)
   double flag_floor;          // a row is recomputed when lambda~ < cmax * 2^flag_floor
-  // exact culling (optional): beyond these time distances (records' time
-  // units) the background, or the excitation, term of a pair is exactly zero
   int ru1;                    // the rate pass accumulates the background moments R, U (else the gradient pass
                               // forms their parameter-gradient terms: gradient calls)
+  // exact culling (optional): beyond these time distances (records' time
+  // units) the background, or the excitation, term of a pair is exactly zero
   float cull_bgf, cull_sef;   // mixed records: bandwidth units of tau_t
   double cull_bg, cull_se;    // float64 records: time units
 };

@@ -51,6 +51,22 @@ __global__ void __launch_bounds__(256) k_peak(float* out, double* out64, float s
         asm volatile("v_add_f32 %0, %0, %1" : "+v"(a[c]) : "v"(cst));
       } else if constexpr (KIND == 9) {     // v_exp_f64 is absent: v_ldexp_f64
         asm volatile("v_ldexp_f64 %0, %0, %1" : "+v"(d[c]) : "v"(0));
+      } else if constexpr (KIND == 10) {    // v_mul_f32
+        asm volatile("v_mul_f32 %0, %0, %1" : "+v"(a[c]) : "v"(b));
+      } else if constexpr (KIND == 11) {    // v_fma_f32 with a scalar operand
+        asm volatile("v_fma_f32 %0, %0, %1, %2" : "+v"(a[c]) : "s"(seed), "v"(cst));
+      } else if constexpr (KIND == 12) {    // v_mul_f32 with a scalar operand
+        asm volatile("v_mul_f32 %0, %1, %0" : "+v"(a[c]) : "s"(seed));
+      } else if constexpr (KIND == 13) {    // v_max_f32
+        asm volatile("v_max_f32 %0, %0, %1" : "+v"(a[c]) : "v"(b));
+      } else if constexpr (KIND == 14) {    // v_add_f32 with a DPP rotation
+        asm volatile("v_add_f32_dpp %0, %0, %1 wave_rol:1 row_mask:0xf bank_mask:0xf" : "+v"(a[c]) : "v"(cst));
+      } else if constexpr (KIND == 15) {    // v_rsq_f32
+        asm volatile("v_rsq_f32 %0, %0" : "+v"(a[c]));
+      } else if constexpr (KIND == 16) {    // v_mul_f64
+        asm volatile("v_mul_f64 %0, %0, %1" : "+v"(d[c]) : "v"((double)b));
+      } else if constexpr (KIND == 17) {    // v_rsq_f64
+        asm volatile("v_rsq_f64 %0, %0" : "+v"(d[c]));
       }
     }
   }
@@ -167,9 +183,17 @@ int main(int argc, char** argv) {
   CHECK(hipMalloc(&o, sizeof(float) * grid * 256)); CHECK(hipMalloc(&o64, sizeof(double) * grid * 256));
   run<0>("v_exp_f32", 1, grid, o, o64);
   run<1>("v_fma_f32", 1, grid, o, o64);
+  run<11>("v_fma_f32, scalar operand", 1, grid, o, o64);
   run<8>("v_add_f32", 1, grid, o, o64);
+  run<10>("v_mul_f32", 1, grid, o, o64);
+  run<12>("v_mul_f32, scalar operand", 1, grid, o, o64);
+  run<13>("v_max_f32", 1, grid, o, o64);
+  run<14>("v_add_f32, DPP rotation", 1, grid, o, o64);
+  run<15>("v_rsq_f32", 1, grid, o, o64);
   run<2>("v_fma_f64", 1, grid, o, o64);
   run<3>("v_add_f64", 1, grid, o, o64);
+  run<16>("v_mul_f64", 1, grid, o, o64);
+  run<17>("v_rsq_f64", 1, grid, o, o64);
   run<9>("v_ldexp_f64", 1, grid, o, o64);
   run<4>("v_cvt_f32_i32+v_cvt_i32_f32", 2, grid, o, o64);
   run<5>("v_cvt_f64_f32+v_cvt_f32_f64", 2, grid, o, o64);
