@@ -180,3 +180,11 @@ def test_mwg_workspace_size(n):
     nrb = (n + 255) // 256
     most = 3 * up(8 * n) + 2 * up(4 * n) + up(8 * nrb) + up(4 * nrb) + up(4 * nrb * 256) + up(512 * n) + up(64)
     assert 0 < _lib.lib().hawkes_mwg_workspace_bytes(n) <= most
+
+
+@pytest.mark.parametrize("d,prec,most", [(1, "fp64", 17920), (5, "mixed", 17920), (6, "mixed", 17920), (6, "fp64", 17658),
+                                         (7, "fp64", 16384), (8, "mixed", 15360), (8, "fp64", 15360)])
+def test_static_scratch_limit(d, prec, most):
+    """Every size up to the stated limit fits the static scratch; the next does not."""
+    size = lambda n: _lib.lib().hawkes_workspace_bytes(ctypes.c_int64(n), d, PREC[prec])
+    assert max(size(n) for n in range(2, most + 1)) <= 64 << 20 < size(most + 1)
