@@ -31,6 +31,12 @@ constexpr int kSeg = 32;          // partner segments (workspace per event) of e
 constexpr int kMaxSeg = 512;      // at most, when few rows are listed
 constexpr int kExactGrid = 512;   // workgroups of the exact-row kernel's listed rows (grid-stride over tasks)
 constexpr int kListThreads = 1024;
+// Steps of fewer than kManyMoved moved events over at most this many events are two
+// launches instead of three: the decision kernel (k_mwg_settle_few) merges the moved
+// rows' chunk sums and recomputes the listed rows itself, kFewGrid workgroups.
+constexpr int kFewEvents = 8192;
+constexpr int kFewGrid = 128;
+constexpr int kFewSegs = 32;   // partner segments of a listed row there, at most
 
 struct Model {
   double mu0, theta;
@@ -65,7 +71,7 @@ struct Step {
   double* mrow;         // nmove: moved rows' sums
   double* mpart;        // nchunk x nmove: their chunk sums (at most n x kSeg / 2)
   double* part;         // npart: listed rows' segment sums
-  int* nlisted;         // length of the list
+  int* nlisted;         // length of the list; [1]: workgroups of k_mwg_settle_few that are done with it
 };
 
 // Contributions of event j to row i, without the pair weights: background
@@ -259,6 +265,7 @@ __device__ __forceinline__ void moved_change(const Step& s, int blk) {
   if (tid == 0) {
     s.bcount[blk] = total;
     s.bpart[blk] = bs;
+    if (blk == 0) s.nlisted[1] = 0;
   }
 }
 
@@ -471,11 +478,6 @@ __device__ __forceinline__ void listed_sums(const Step& s, int r, int j0, int j1
 // The listed rows, split into (row, partner segment) tasks over a fixed grid, and
 // (after them, one wave per row) the moved rows' chunk sums added in a fixed order.
 // Workgroup 0 also writes the list and its length, which the decision kernel reads.
-// (Small steps without this launch, whose decision kernel merged the moved rows' sums and
-// recomputed the listed rows in every one of its workgroups, saved about 1 us where no row
-// was listed, one event at N = 2,925, and had no bound where some were: a first event moved
-// away from 300 events of the next day 2.0 ms instead of 0.1, from 8,191 at N = 8,192 104 ms
-// instead of 1.8; 7 moved events at N = 8,000, D = 6 92 us instead of 20.)
 constexpr int kMergeRows = kBlock / 64;
 template <int D>
 __global__ void __launch_bounds__(kBlock) k_mwg_exact(Step s) {
@@ -616,6 +618,144 @@ __global__ void __launch_bounds__(kBlock) k_mwg_settle(Step s) {
   tp[3] = s.m.theta * nb / lam1;
 }
 
+// Two-launch steps.  Every workgroup merges the moved rows' chunk sums (32 lanes a row).
+// Where no row is listed, which the counts of k_mwg_rows tell all workgroups alike, each
+// decides and updates its own rows as in k_mwg_settle.  Else they split the listed rows
+// into (row, partner segment) tasks, and the last one to finish adds the segments,
+// decides and updates every row: only it writes, after all others have read.  (The
+// device-wide fence that this takes writes back the L2 of each die, so it is left to steps
+// that list a row.)  Which workgroup is the last changes no bit of the sums.
+//
+// Two launches against three, one moved event at N = 2,925: 8.7 us a step against 10.4 on
+// the device, and 9.5 against 10.7 to 12.2 where the host's launches bound it.  With rows
+// listed (the first event moved away from that many of the next day), three launches and
+// two: N = 2,925 1 row 15.5 and 15.6, 30 19.8 and 17.5, 300 101 and 36; N = 8,192 10 rows
+// 15.4 and 17.2, 300 100 and 60, 8,191 1,817 and 868.  (Every workgroup recomputing all
+// listed rows, so that none needs a fence: 1 row 18, 30 214, 300 2,045; N = 8,192, 8,191 rows
+// 104,000.)  128 workgroups: with 64 300 rows 49, with 256 1 row 18.2.
+template <int D>
+__global__ void __launch_bounds__(kBlock) k_mwg_settle_few(Step s) {
+  constexpr int LM = kBlock / kManyMoved;   // lanes per moved row
+  static_assert(LM <= 64, "a moved row's lanes are one wave's");
+  __shared__ double sh[2 * kBlock];
+  __shared__ double s_exptab[kExpTab];   // 2^(j/kExpTab) for exp_tab
+  __shared__ double s_ma[kManyMoved], s_mb[kManyMoved], s_mdl[kManyMoved];
+  __shared__ int s_scan[kBlock];
+  __shared__ int s_wtot[kBlock / 64];
+  __shared__ int s_bad, s_last;
+  const int tid = threadIdx.x;
+  if (tid == 0) s_bad = 0;
+  // what the decision needs is read first, so that no load waits behind the barriers
+  const double thresh = *s.thresh;
+  double acc = 0.0;   // this thread's part of the sum of log-rate changes
+  for (int b = tid; b < s.nrb; b += kBlock) acc += s.bpart[b];
+  const int km = tid / LM;   // this thread's moved row
+  double ma = 0.0, mb = 0.0;
+  if (km < s.nmove)
+    for (int c = tid % LM; c < s.nchunk; c += LM) {
+      ma += s.mpart[((int64_t)c * s.nmove + km) * 2 + 0];
+      mb += s.mpart[((int64_t)c * s.nmove + km) * 2 + 1];
+    }
+  int own, lo, hi;
+  const Listed L = listed_rows(s, s_scan, s_wtot, own, lo, hi);   // (its barriers order s_bad)
+  const bool listed = L.cnt > 0;
+  const int first = listed ? 0 : blockIdx.x * kBlock, end = listed ? s.n : min(s.n, first + kBlock);
+  if (first >= s.n) return;   // nothing listed and no rows of its own
+#pragma unroll
+  for (int o = LM / 2; o > 0; o >>= 1) {
+    ma += __shfl_xor(ma, o);
+    mb += __shfl_xor(mb, o);
+  }
+  if (km < s.nmove && tid % LM == 0) {
+    const int64_t j = s.idx[km];
+    bool bad = j < 0 || j >= s.n || (km > 0 && s.idx[km - 1] >= j);
+#pragma unroll
+    for (int q = 0; q < D; ++q) bad = bad || !isfinite(s.xnew[(int64_t)km * D + q]);
+    if (bad) {
+      atomicOr(&s_bad, 1);
+    } else {
+      s_ma[km] = ma;
+      s_mb[km] = mb;
+      s_mdl[km] = log(s.m.mu0 * ma + s.m.theta * mb) - s.dlog[j];
+      acc += s_mdl[km];
+    }
+  }
+  int segs = 1;
+  while (segs < kFewSegs && L.cnt * segs * 2 <= kFewGrid && 2 * segs * kBlock <= s.n) segs *= 2;
+  // each listed row's segments added by as many lanes, use(row, a, b, log-rate change) by the
+  // first of them
+  const auto for_listed = [&](auto use) {
+    for (int e0 = 0; e0 < L.cnt; e0 += kBlock / segs) {
+      const int e = e0 + tid / segs, sg = tid % segs;
+      double a = 0.0, b = 0.0;
+      if (e < L.cnt) {
+        a = s.part[((int64_t)e * segs + sg) * 2 + 0];
+        b = s.part[((int64_t)e * segs + sg) * 2 + 1];
+      }
+      for (int o = segs / 2; o > 0; o >>= 1) {
+        a += __shfl_xor(a, o);
+        b += __shfl_xor(b, o);
+      }
+      if (e < L.cnt && sg == 0) {
+        const int r = listed_row(s, L, e);
+        use(r, a, b, log(s.m.mu0 * a + s.m.theta * b) - s.dlog[r]);
+      }
+    }
+  };
+  if (listed) {
+    fill_exp_table(s_exptab);
+    __syncthreads();
+    const int seg = (s.n + segs - 1) / segs;
+    for (int task = blockIdx.x; task < L.cnt * segs; task += gridDim.x) {
+      const int e = task / segs, j0 = task % segs * seg;
+      double ab[2];
+      listed_sums<D>(s, listed_row(s, L, e), j0, min(s.n, j0 + seg), s_exptab, ab);
+      block_sum_n(ab, sh);
+      if (tid == 0) {
+        s.part[(int64_t)task * 2 + 0] = ab[0];
+        s.part[(int64_t)task * 2 + 1] = ab[1];
+      }
+    }
+    __syncthreads();   // all of this workgroup's reads are done
+    if (tid == 0)
+      s_last = __hip_atomic_fetch_add(&s.nlisted[1], 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == (int)gridDim.x - 1;
+    __syncthreads();
+    if (!s_last) return;
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    for_listed([&](int, double, double, double dl) { acc += dl; });
+  }
+  const double tot = block_sum(acc, sh);   // also orders the LDS writes above
+  const bool bad = s_bad != 0;
+  const bool accept = !bad && tot > thresh;
+  if (first == 0 && tid == 0) {
+    s.out3[0] = bad ? NAN : tot;
+    s.out3[1] = accept ? 1.0 : 0.0;
+    s.out3[2] = bad ? (double)HAWKES_EDATA : 0.0;
+  }
+  if (!accept) return;
+  const auto update = [&](int i, double na, double nb, double dl) {
+    double* tp = s.terms + (int64_t)i * 4;
+    tp[0] = na;
+    tp[1] = nb;
+    tp[2] = tp[2] + dl;
+    tp[3] = s.m.theta * nb / (s.m.mu0 * na + s.m.theta * nb);
+  };
+  for (int i = first + tid; i < end; i += kBlock) {
+    if (s.flag[i] != 0) continue;
+    const double na = s.new_a[i], nb = s.new_b[i];
+    if (na != s.terms[(int64_t)i * 4 + 0] || nb != s.terms[(int64_t)i * 4 + 1]) update(i, na, nb, s.dlog[i]);
+  }
+  for_listed(update);
+  if (tid < s.nmove) {
+    const int64_t j = s.idx[tid];
+    if (j >= first && j < end) {
+      update((int)j, s_ma[tid], s_mb[tid], s_mdl[tid]);
+#pragma unroll
+      for (int q = 0; q < D; ++q) s.x[j * D + q] = s.xnew[(int64_t)tid * D + q];
+    }
+  }
+}
+
 // Log-likelihood and its derivatives in mu0 and theta at new weights, every
 // other parameter as when the terms were computed (one workgroup):
 //   ell = sum_i log(mu0 a_i + theta b_i) - sum_i (mu0 C_i + theta E_i)
@@ -681,7 +821,7 @@ static Pieces pieces(int64_t n) {
   p.stage = take(sizeof(int) * (size_t)((n + kBlock - 1) / kBlock * kBlock));
   p.list = take(sizeof(int) * (size_t)n);
   p.part = take(sizeof(double) * 2 * (size_t)shared_pairs(n));
-  p.nlisted = take(sizeof(int));
+  p.nlisted = take(2 * sizeof(int));
   p.total = o;
   return p;
 }
@@ -692,6 +832,11 @@ static void launch(const Step& s, hipStream_t st) {
   const int nset = (s.n + kBlock - 1) / kBlock;
   if (s.nmove >= kManyMoved) k_mwg_rows<D, kRowLanesMany><<<grid, kBlock, 0, st>>>(s);
   else k_mwg_rows<D, 1><<<grid, kBlock, 0, st>>>(s);
+  if (s.n <= kFewEvents && s.nmove < kManyMoved) {
+    static_assert(kFewEvents <= kFewGrid * kBlock, "every row has a workgroup");
+    k_mwg_settle_few<D><<<kFewGrid, kBlock, 0, st>>>(s);
+    return;
+  }
   k_mwg_exact<D><<<kExactGrid + (s.nmove + kMergeRows - 1) / kMergeRows, kBlock, 0, st>>>(s);
   k_mwg_settle<D><<<nset, kBlock, 0, st>>>(s);
 }

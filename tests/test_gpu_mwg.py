@@ -312,7 +312,7 @@ def test_mwg_moved_row_sums(n, nmove):
     test_mwg_block_sizes(n, 2, nmove)
 
 
-@pytest.mark.parametrize("n,next_day", [(2925, 3), (2925, 300), (8192, 8191)])
+@pytest.mark.parametrize("n,next_day", [(500, 3), (2925, 3), (2925, 300), (8192, 10), (8192, 8191)])
 def test_mwg_many_rows_that_lose_their_one_source(n, next_day):
     """Whole-day times: the first event, alone on its day, excites the
     `next_day` events of the next one, which excite each other no more than
