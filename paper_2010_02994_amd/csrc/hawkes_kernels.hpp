@@ -1052,9 +1052,9 @@ constexpr float kHalfLog2e = (float)(0.5 * 1.4426950408889634074);   // mA = mB
 
 // A constant of the pair loop in a vector register.  A float32 operation with
 // a scalar-register operand issues at half the rate of one on vector registers
-// or literals (measured: 52 against 100 lanes per CU and clock for a multiply
-// or an add, 56 against 80 for a fused multiply-add), and the exponents take
-// four such operations per pair.
+// or literals (the peaks microbenchmark: 61 against 112 lanes per CU and clock for
+// a multiply, 59 against 114 for a fused multiply-add), and the exponents take four
+// such operations per pair.
 __device__ __forceinline__ float in_vgpr(float v) {
   asm("" : "+v"(v));
   return v;
