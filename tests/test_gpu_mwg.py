@@ -395,3 +395,48 @@ def test_mwg_moved_and_listed_rows_share_the_workspace(n, nmove):
     assert np.array_equal(xd.cpu().numpy(), x1)
     _check_terms(terms.cpu().numpy(), oracle.event_terms(x1, t, p), "fp64", p, f"shared nmove{nmove}")
     assert torch.all(ws[:guard] == 0x5a).item() and torch.all(ws[guard + size:] == 0x5a).item()
+
+
+@pytest.mark.parametrize("next_day", [0, 40])
+def test_mwg_few_moved_steps_replay_from_a_graph(next_day):
+    """Two steps of one moved event (there and back), with and without rows to
+    recompute, captured once and replayed with eager work between: every
+    replay's locations, terms and outputs equal the eager steps' bit for bit."""
+    import torch
+    from paper_2010_02994_amd import api
+    n = 1500
+    rng = np.random.default_rng(next_day)
+    x = 0.5 * rng.standard_normal((n, 2))
+    t = np.concatenate([[0.0], np.full(next_day, 1.0), 2.0 + np.sort(np.floor(rng.uniform(0, 300, n - 1 - next_day)))])
+    p = np.array([0.5, 1.0, 5.0, 0.4, 0.2, 1.0])
+    x0, td = _dev(x), _dev(t)
+    terms0, _ = api.event_terms(x0, td, p, prec="fp64")
+    xd, terms = x0.clone(), terms0.clone()
+    idx, there, back, always = _dev(np.array([0])), _dev(x[:1] + 5.0), _dev(x[:1]), _dev(np.array([-np.inf]))
+    outs = torch.zeros((2, 3), dtype=torch.float64, device="cuda:0")
+
+    def steps():
+        for k, place in enumerate((there, back)):
+            api.mwg_step(xd, td, p, terms, idx, place, always, out3=outs[k])
+
+    say(f"case mwg graph next_day={next_day}")
+    steps()
+    torch.cuda.synchronize()
+    want = [v.clone() for v in (xd, terms, outs)]
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):   # warm the capture stream's workspace outside the capture
+        steps()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        steps()
+    for _ in range(4):
+        xd.copy_(x0)
+        terms.copy_(terms0)
+        outs.zero_()
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip((xd, terms, outs), want))
+        steps()
+        torch.cuda.synchronize()
